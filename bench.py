@@ -597,10 +597,14 @@ def bench_step(torch, gslic, args, dev, workload, steps, warmup, with_plain=Fals
     }
     work = {
         "project": ("hbm", 4.0 * 14 * n + 4.0 * (F - 14) * n + 64.0 * n_vis + 8.0 * V * n, 0),
-        # 20 B per key and pass (4 read up, 8 read + 8 written down); the first pass reads no values
+        # the counting reads every pair's 16-B word once
+        "scan": ("hbm", 16.0 * V * n, 0),
+        # the placement reads it again with the depth and the lists take 4 B per instance (the
+        # 8-B entries between the two are not counted)
+        "duplicate": ("hbm", 20.0 * V * n + 4.0 * n_inst, 0),
+        # images of more tiles than the counting lists take: 20 B per key and pass (4 read up, 8
+        # read + 8 written down); the first pass reads no values
         "depth_sort": ("hbm", (4 * 20.0 - 4.0) * V * n, 0),
-        "scan": ("hbm", 12.0 * V * n, 0),
-        "duplicate": ("hbm", 24.0 * n_vis + 8.0 * n_inst, 0),
         "sort": ("hbm", (tile_passes * 20.0 - 4.0) * n_inst, 0),
         "ranges": ("hbm", 4.0 * n_inst + 8.0 * T_total, 0),
         # HBM minimum: each visible record once, 8 B of indices per entry, 20 B per pixel out
@@ -618,7 +622,7 @@ def bench_step(torch, gslic, args, dev, workload, steps, warmup, with_plain=Fals
              "blend": f"k_blend_fwd<{fpx},false>",
              "project_backward": f"k_project_bwd<{sh},true,{'true' if len(cams) > 1 else 'false'}>",
              "project": f"k_project_fwd<{sh}>",
-             "loss": "k_ssim_tile", "duplicate": "k_dup_lb"}
+             "loss": "k_ssim_tile"}
     tag = f"{workload}_{n // 1000}k_sh{sh}_{args.width}x{args.height}"
     kernel_table = {}
     for k, ms_k in per.items():

@@ -355,16 +355,17 @@ gs_status gs_check_overflow(gs_map* map, void* stream, int32_t* overflow);
  * Stage order: GS_STAGE_* below. */
 enum {
   GS_STAGE_PROJECT = 0,       /* per-Gaussian projection and tile count */
-  GS_STAGE_SCAN = 1,          /* exclusive scan of tile counts in depth order */
-  GS_STAGE_DUPLICATE = 2,     /* tile id of every instance, emitted in depth order */
-  GS_STAGE_SORT = 3,          /* stable radix sort of the instances by tile */
-  GS_STAGE_RANGES = 4,        /* per-tile [start, end) */
+  GS_STAGE_SCAN = 1,          /* instance counts, tile ranges and positions */
+  GS_STAGE_DUPLICATE = 2,     /* the tiles' lists: placement and order by depth */
+  GS_STAGE_SORT = 3,          /* images of more tiles than the counting lists take only:
+                                 stable radix sort of the instances by tile */
+  GS_STAGE_RANGES = 4,        /* such images only: per-tile [start, end) */
   GS_STAGE_BLEND = 5,         /* forward blend */
   GS_STAGE_LOSS = 6,          /* L1 + D-SSIM and its gradient */
   GS_STAGE_BLEND_BACKWARD = 7,
   GS_STAGE_PROJECT_BACKWARD = 8,
   GS_STAGE_ADAM = 9,
-  GS_STAGE_DEPTH_SORT = 10,   /* radix sort of (view, Gaussian) pairs by depth */
+  GS_STAGE_DEPTH_SORT = 10,   /* such images only: radix sort of (view, Gaussian) pairs by depth */
   GS_NUM_STAGES = 11
 };
 gs_status gs_set_stage_timing(gs_map* map, int32_t enable);

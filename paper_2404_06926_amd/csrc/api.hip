@@ -85,11 +85,13 @@ struct gs_map {
   // workspace
   DevBuf rec, counts, offsets, scan_tmp, g2d, keys[2], vals[2], sort_tmp, ranges, pixT, pixN, loss_tmp;
   DevBuf dkey[2], dval[2];     // depth-sort keys / (view, Gaussian) ids, double-buffered
+  DevBuf list_g, list_e;       // per instance in blend order: its Gaussian; its emission index (deterministic)
+  DevBuf tl_pairs, tl_space, tl_entries, tl_merged;  // tile lists by counting (tilelist.hip)
   DevBuf emit_g, inst_off;     // Gaussian of each emission index; first emission index per pair
   DevBuf block_start;           // instance-parallel binning: first pair per emission block
   DevBuf split_slot, split_extra, split_state;  // long lists cut into chunks (blend)
   DevBuf inst_grad, exp_part;  // deterministic backward: per-instance gradients, per-tile exposure sums
-  DevBuf dbg_g;                // Gaussian index per instance in blend order (inspection only)
+  DevBuf dbg_t;                // tile of each instance in blend order (inspection only)
   DevBuf gr_rgb, gr_T, gr_flags, gr_off, gr_tmp, gr_d2;  // map growth: render, selection, scan, sky
   bool deterministic = false;
   bool fused_step = true;      // gs_step applies Adam inside the projection backward
@@ -111,7 +113,7 @@ struct gs_map {
   bool have_render = false;
   ViewsArg last_va{};
   int32_t last_N = 0;
-  int sorted = 0;
+  const uint32_t* last_list_e = nullptr;  // emission index per instance (deterministic renders)
   bool last_det = false;       // the last render wrote what the deterministic backward reads
   // keyframe window
   std::vector<KeyframeSlot> kf;
@@ -224,15 +226,30 @@ gs_status grow_capacity(gs_map* m, int64_t need, hipStream_t s) {
   return GS_OK;
 }
 
-gs_status ensure_instances(gs_map* m, int64_t nc, int64_t vn, hipStream_t s) {
-  for (int b = 0; b < 2; ++b) {
-    GS_TRY(ensure(m, m->keys[b], (size_t)nc * 4, s));
-    GS_TRY(ensure(m, m->vals[b], (size_t)nc * 4, s));
+// Buffers for nc instances: those of the lists by counting, or (sorted) of the tile sort, whose
+// temporary the depth sort of vn pairs shares.
+gs_status ensure_instances(gs_map* m, int64_t nc, bool sorted, int64_t vn, hipStream_t s) {
+  GS_TRY(ensure(m, m->list_g, (size_t)nc * 4, s));
+  if (!sorted) {
+    GS_TRY(ensure(m, m->tl_entries, (size_t)nc * 8, s));
+    GS_TRY(ensure(m, m->tl_merged, (size_t)nc * 8, s));
   }
-  GS_TRY(ensure(m, m->emit_g, (size_t)nc * 4, s));
-  GS_TRY(ensure(m, m->block_start, (size_t)block_start_elems(nc) * 4, s));
-  if (m->deterministic) GS_TRY(ensure(m, m->inst_grad, (size_t)nc * 12 * 4, s));
-  GS_TRY(ensure(m, m->sort_tmp, (size_t)sort_temp_elems(std::max<int64_t>(nc, vn)) * 4, s));
+  if (m->deterministic) {
+    GS_TRY(ensure(m, m->inst_grad, (size_t)nc * 12 * 4, s));
+    if (!sorted) {
+      GS_TRY(ensure(m, m->list_e, (size_t)nc * 4, s));
+      GS_TRY(ensure(m, m->emit_g, (size_t)nc * 4, s));
+    }
+  }
+  if (sorted) {
+    for (int b = 0; b < 2; ++b) {
+      GS_TRY(ensure(m, m->keys[b], (size_t)nc * 4, s));
+      GS_TRY(ensure(m, m->vals[b], (size_t)nc * 4, s));
+    }
+    GS_TRY(ensure(m, m->emit_g, (size_t)nc * 4, s));
+    GS_TRY(ensure(m, m->block_start, (size_t)block_start_elems(nc) * 4, s));
+    GS_TRY(ensure(m, m->sort_tmp, (size_t)sort_temp_elems(std::max<int64_t>(nc, vn)) * 4, s));
+  }
   if (nc > m->inst_cap) m->inst_cap = nc;
   return GS_OK;
 }
@@ -460,9 +477,10 @@ gs_status gs_destroy_map(gs_map* m) {
   dev_free(m, m->d_nvn, 64, s);
   DevBuf* bufs[] = {&m->rec, &m->counts, &m->offsets, &m->scan_tmp, &m->g2d, &m->keys[0], &m->keys[1],
                     &m->vals[0], &m->vals[1], &m->sort_tmp, &m->ranges, &m->pixT, &m->pixN, &m->loss_tmp,
-                    &m->dkey[0], &m->dkey[1], &m->dval[0], &m->dval[1], &m->emit_g, &m->inst_off,
+                    &m->dkey[0], &m->dkey[1], &m->dval[0], &m->dval[1], &m->emit_g, &m->inst_off, &m->list_g, &m->list_e,
+                    &m->tl_pairs, &m->tl_space, &m->tl_entries, &m->tl_merged,
                     &m->block_start, &m->split_slot, &m->split_extra, &m->split_state,
-                    &m->inst_grad, &m->exp_part, &m->dbg_g, &m->gr_rgb, &m->gr_T, &m->gr_flags,
+                    &m->inst_grad, &m->exp_part, &m->dbg_t, &m->gr_rgb, &m->gr_T, &m->gr_flags,
                     &m->gr_off, &m->gr_tmp, &m->gr_d2, &m->ar_rgb, &m->ar_T, &m->ar_nc, &m->ar_dl,
                     &m->pend_xyz, &m->pend_rgb};
   for (DevBuf* b : bufs) dev_free(m, b->ptr, b->bytes, s);
@@ -610,17 +628,25 @@ gs_status gs_render(gs_map* m, int32_t nv, const gs_view* views, const gs_frame*
   // workspace
   GS_TRY(ensure(m, m->rec, (size_t)std::max<int64_t>(vn, 1) * kRecFloats * 4, s));
   GS_TRY(ensure(m, m->counts, (size_t)std::max<int64_t>(vn, 1) * 4, s));
-  GS_TRY(ensure(m, m->offsets, (size_t)std::max<int64_t>(vn, 1) * 4, s));
-  GS_TRY(ensure(m, m->scan_tmp, (size_t)scan_temp_elems(std::max<int64_t>(vn, 1)) * 4, s));
-  GS_TRY(ensure(m, m->g2d, (size_t)std::max<int64_t>(vn, 1) * kGradFloats * 4, s, true));
-  for (int b = 0; b < 2; ++b) {
-    GS_TRY(ensure(m, m->dkey[b], (size_t)std::max<int64_t>(vn, 1) * 4, s));
-    GS_TRY(ensure(m, m->dval[b], (size_t)std::max<int64_t>(vn, 1) * 4, s));
+  // the lists by counting, or by sorting where a view has more tiles than they take
+  const bool sorted = !tile_lists_fit(va, N, m->deterministic ? std::max<int64_t>(m->inst_cap, vn) : 0);
+  if (sorted) {
+    GS_TRY(ensure(m, m->offsets, (size_t)std::max<int64_t>(vn, 1) * 4, s));
+    GS_TRY(ensure(m, m->dkey[1], (size_t)std::max<int64_t>(vn, 1) * 4, s));
+    for (int b = 0; b < 2; ++b) GS_TRY(ensure(m, m->dval[b], (size_t)std::max<int64_t>(vn, 1) * 4, s));
+    GS_TRY(ensure(m, m->sort_tmp,
+                  (size_t)sort_temp_elems(std::max<int64_t>(std::max<int64_t>(vn, m->inst_cap), 1)) * 4, s));
+  } else {
+    GS_TRY(ensure(m, m->tl_pairs, (size_t)std::max<int64_t>(vn, 1) * 16, s));
+    GS_TRY(ensure(m, m->tl_space, (size_t)tile_space_bytes(va, N), s));
   }
-  GS_TRY(ensure(m, m->inst_off, (size_t)std::max<int64_t>(vn, 1) * 4, s));
+  if (sorted || m->deterministic) {
+    GS_TRY(ensure(m, m->scan_tmp, (size_t)scan_temp_elems(std::max<int64_t>(vn, 1)) * 4, s));
+    GS_TRY(ensure(m, m->inst_off, (size_t)std::max<int64_t>(vn, 1) * 4, s));
+  }
+  GS_TRY(ensure(m, m->g2d, (size_t)std::max<int64_t>(vn, 1) * kGradFloats * 4, s, true));
+  GS_TRY(ensure(m, m->dkey[0], (size_t)std::max<int64_t>(vn, 1) * 4, s));
   GS_TRY(ensure(m, m->exp_part, (size_t)std::max<int64_t>(tiles, 1) * 12 * 4, s));
-  GS_TRY(ensure(m, m->sort_tmp, (size_t)sort_temp_elems(std::max<int64_t>(std::max<int64_t>(vn, m->inst_cap), 1)) * 4,
-                s));
   GS_TRY(ensure(m, m->ranges, (size_t)tiles * 8 + 16, s));  // + the split counters
   if (m->split_par > 0) {
     const size_t par = (size_t)m->split_par;
@@ -645,73 +671,92 @@ gs_status gs_render(gs_map* m, int32_t nv, const gs_view* views, const gs_frame*
   uint32_t* dval[2] = {(uint32_t*)m->dval[0].ptr, (uint32_t*)m->dval[1].ptr};
   {
     StageTimer t(m, s, GS_STAGE_PROJECT);
-    // on the side: the pair count the depth sort reads, and the tile ranges (with the split
-    // counters after them) zeroed for this render
-    const ProjSide side{m->d_nvn, (uint32_t)vn, (uint32_t*)m->ranges.ptr, 2 * tiles + 2};
+    // on the side: the pairs' words for the lists by counting; for the tile sort the pair
+    // count its depth sort reads, and the tile ranges (with the split counters after them)
+    // zeroed for this render
+    const ProjSide side = sorted ? ProjSide{m->d_nvn, (uint32_t)vn, (uint32_t*)m->ranges.ptr, 2 * tiles + 2, nullptr}
+                                 : ProjSide{nullptr, 0u, nullptr, 0, (uint4*)m->tl_pairs.ptr};
     GS_HIP(project_forward(m->deg, params_of(m), m->cap, N, va, m->desc.near_z, rec, counts, dkey[0], side, s));
   }
-  int dwhich = 0;
-  {
+  const uint32_t* order = nullptr;
+  if (sorted) {
     StageTimer t(m, s, GS_STAGE_DEPTH_SORT);
+    int dwhich = 0;
     GS_HIP(radix_sort_u32(dkey, dval, m->d_nvn, vn, 32, (uint32_t*)m->sort_tmp.ptr, &dwhich, s, true));
-  }
-  const uint32_t* order = dval[dwhich];
-  // the instance buffers of the current capacity exist before the scan of the counts, which
-  // marks the emission blocks' first pairs for that capacity
-  if (m->inst_cap > 0) GS_TRY(ensure_instances(m, m->inst_cap, vn, s));
-  const int64_t marked_cap = m->inst_cap;
-  {
-    StageTimer t(m, s, GS_STAGE_SCAN);
-    if (vn > 0)
-      GS_HIP(scan_counts(counts, order, offsets, vn, (uint32_t*)m->scan_tmp.ptr, m->d_ninst,
-                         (uint32_t*)m->block_start.ptr, marked_cap, s));
-    else
-      GS_HIP(fill_u32(m->d_ninst, 0u, 1, s));
+    order = dval[dwhich];
   }
   if (m->sync_plan && m->capturing) return fail(GS_ERR_STATE, "capture needs sync_plan = 0");
+  if (!m->sync_plan && m->inst_cap == 0)
+    return fail(GS_ERR_STATE, "sync_plan = 0 needs an instance capacity (gs_set_instance_policy)");
+  // the instance buffers of the current capacity
+  if (m->inst_cap > 0) GS_TRY(ensure_instances(m, m->inst_cap, sorted, vn, s));
+  const int64_t marked_cap = m->inst_cap;
+  uint2* ranges = (uint2*)m->ranges.ptr;
+  uint32_t* inst_off = (uint32_t*)m->inst_off.ptr;
+  m->last_sp = split_arg(m, tiles);
+  {
+    StageTimer t(m, s, GS_STAGE_SCAN);
+    if (!sorted) {
+      // with a planned render nothing is dropped: the buffers grow to the count below
+      GS_HIP(tile_lists_plan(rec, (const uint4*)m->tl_pairs.ptr, N, va, m->tl_space.ptr,
+                             m->sync_plan ? INT64_MAX : m->inst_cap, ranges, m->d_ninst, m->d_overflow,
+                             m->last_sp.par > 0 ? m->last_sp.counts : nullptr, s));
+      if (m->deterministic) GS_HIP(exclusive_scan(counts, inst_off, vn, (uint32_t*)m->scan_tmp.ptr, s));
+    } else if (vn > 0) {
+      GS_HIP(scan_counts(counts, order, offsets, vn, (uint32_t*)m->scan_tmp.ptr, m->d_ninst,
+                         (uint32_t*)m->block_start.ptr, marked_cap, s));
+    } else {
+      GS_HIP(fill_u32(m->d_ninst, 0u, 1, s));
+    }
+  }
   if (m->sync_plan) {
     GS_HIP(hipMemcpyAsync(m->h_pinned, m->d_ninst, 4, hipMemcpyDeviceToHost, s));
     GS_HIP(hipStreamSynchronize(s));
     const int64_t need = m->h_pinned[0];
-    if (need > m->inst_cap) GS_TRY(ensure_instances(m, std::max<int64_t>(need + need / 4, 1 << 16), vn, s));
-  } else if (m->inst_cap == 0) {
-    return fail(GS_ERR_STATE, "sync_plan = 0 needs an instance capacity (gs_set_instance_policy)");
+    const int64_t cap = need > m->inst_cap ? std::max<int64_t>(need + need / 4, 1 << 16) : m->inst_cap;
+    GS_TRY(ensure_instances(m, cap, sorted, vn, s));
+    // a deterministic render of more instances than an entry's id holds takes the tile sort
+    if (!sorted && !tile_lists_fit(va, N, m->deterministic ? need : 0)) return gs_render(m, nv, views, frames, stream);
   }
-  GS_TRY(ensure_instances(m, m->inst_cap, vn, s));
   // the backward of this render checks these: a render that dropped its instances has none
   va.n_inst = m->d_ninst;
   va.inst_cap = m->inst_cap;
-  uint32_t* keys[2] = {(uint32_t*)m->keys[0].ptr, (uint32_t*)m->keys[1].ptr};
-  uint32_t* vals[2] = {(uint32_t*)m->vals[0].ptr, (uint32_t*)m->vals[1].ptr};
-  {
+  if (!sorted) {
     StageTimer t(m, s, GS_STAGE_DUPLICATE);
-    GS_HIP(duplicate_keys(rec, counts, order, offsets, m->d_ninst, N, va, keys[0], (uint32_t*)m->emit_g.ptr, (uint32_t*)m->inst_off.ptr, m->deterministic,
-                          (uint32_t*)m->block_start.ptr, marked_cap > 0 && marked_cap == m->inst_cap, m->inst_cap,
-                          m->d_overflow, s));
-  }
-  int which = 0;
-  {
-    // stable sort by tile id; one extra bit keeps the sentinel id above every real tile
-    StageTimer t(m, s, GS_STAGE_SORT);
-    GS_HIP(radix_sort_u32(keys, vals, m->d_ninst, m->inst_cap, bits_for(tiles + 1), (uint32_t*)m->sort_tmp.ptr,
-                          &which, s, true));
-  }
-  uint2* ranges = (uint2*)m->ranges.ptr;
-  {
+    m->last_list_e = m->deterministic ? (const uint32_t*)m->list_e.ptr : nullptr;
+    GS_HIP(tile_lists_build(rec, (const uint4*)m->tl_pairs.ptr, dkey[0], inst_off, N, va, m->tl_space.ptr, ranges,
+                            (uint64_t*)m->tl_entries.ptr, (uint64_t*)m->tl_merged.ptr, (uint32_t*)m->emit_g.ptr,
+                            (uint32_t*)m->list_g.ptr, m->deterministic ? (uint32_t*)m->list_e.ptr : nullptr, m->last_sp, s));
+  } else {
+    uint32_t* keys[2] = {(uint32_t*)m->keys[0].ptr, (uint32_t*)m->keys[1].ptr};
+    uint32_t* vals[2] = {(uint32_t*)m->vals[0].ptr, (uint32_t*)m->vals[1].ptr};
+    {
+      StageTimer t(m, s, GS_STAGE_DUPLICATE);
+      GS_HIP(duplicate_keys(rec, counts, order, offsets, m->d_ninst, N, va, keys[0], (uint32_t*)m->emit_g.ptr,
+                            inst_off, m->deterministic, (uint32_t*)m->block_start.ptr,
+                            marked_cap > 0 && marked_cap == m->inst_cap, m->inst_cap, m->d_overflow, s));
+    }
+    int which = 0;
+    {
+      // stable sort by tile id; one extra bit keeps the sentinel id above every real tile
+      StageTimer t(m, s, GS_STAGE_SORT);
+      GS_HIP(radix_sort_u32(keys, vals, m->d_ninst, m->inst_cap, bits_for(tiles + 1), (uint32_t*)m->sort_tmp.ptr,
+                            &which, s, true));
+      m->last_list_e = vals[which];
+      GS_HIP(gather_gaussians(vals[which], (const uint32_t*)m->emit_g.ptr, m->d_ninst, m->inst_cap,
+                              (uint32_t*)m->list_g.ptr, s));
+    }
     StageTimer t(m, s, GS_STAGE_RANGES);
     GS_HIP(tile_ranges(keys[which], m->d_ninst, m->inst_cap, ranges, tiles, s));
-    m->last_sp = split_arg(m, tiles);
     GS_HIP(split_items(ranges, (int32_t)tiles, m->last_sp, s));
   }
   {
     StageTimer t(m, s, GS_STAGE_BLEND);
-    GS_HIP(blend_forward(va, rec, N, vals[which], (const uint32_t*)m->emit_g.ptr, ranges, m->last_sp, m->fwd_px,
-                         s));
+    GS_HIP(blend_forward(va, rec, N, (const uint32_t*)m->list_g.ptr, ranges, m->last_sp, m->fwd_px, s));
   }
   m->have_render = true;
   m->last_va = va;
   m->last_N = N;
-  m->sorted = which;
   m->last_det = m->deterministic;
   if (!m->capturing) m->render_gen += 1;
   return GS_OK;
@@ -757,11 +802,11 @@ static gs_status backward_impl(gs_map* m, int32_t nv, const float* const* dL_drg
     // deterministic when the render was (it wrote every pair's first emission index)
     float* ig = m->last_det ? (float*)m->inst_grad.ptr : nullptr;
     if (m->bwd_mode == 1 && !maps)
-      GS_HIP(blend_backward_per_gaussian(va, rec, N, (const uint32_t*)m->vals[m->sorted].ptr,
-                                         (const uint32_t*)m->emit_g.ptr, (const uint2*)m->ranges.ptr, g2d, ig,
+      GS_HIP(blend_backward_per_gaussian(va, rec, N, (const uint32_t*)m->list_g.ptr, m->last_list_e,
+                                         (const uint2*)m->ranges.ptr, g2d, ig,
                                          (float*)m->exp_part.ptr, m->last_sp, s));
     else
-      GS_HIP(blend_backward(va, rec, N, (const uint32_t*)m->vals[m->sorted].ptr, (const uint32_t*)m->emit_g.ptr,
+      GS_HIP(blend_backward(va, rec, N, (const uint32_t*)m->list_g.ptr, m->last_list_e,
                             (const uint2*)m->ranges.ptr, g2d, ig, (float*)m->exp_part.ptr, m->last_sp,
                             m->bwd_px, s));
   }
@@ -976,7 +1021,6 @@ gs_status gs_submit_keyframe(gs_map* m, const gs_view* view, const float* image,
   // again with planning, so every job applies `iters` steps.
   if (iters > 0) {
     const bool plan_before = m->sync_plan;
-    const int64_t vn = (int64_t)nk * m->n;
     int it = 0;
     auto restore = [&](gs_status st) {
       m->sync_plan = plan_before;
@@ -1002,7 +1046,7 @@ gs_status gs_submit_keyframe(gs_map* m, const gs_view* view, const float* image,
           const int64_t scaled = m->serve_peak * nk / m->serve_views;
           est = std::max<int64_t>(est, scaled + scaled / 4 + (1 << 16));
         }
-        gs_status st = ensure_instances(m, est, vn, s);
+        gs_status st = ensure_instances(m, est, false, 0, s);
         if (st != GS_OK) return restore(st);
         m->sync_plan = false;
         for (; it < iters; ++it) {
@@ -1354,14 +1398,14 @@ gs_status gs_debug_last_render(gs_map* m, void* stream, const uint32_t** keys, c
   hipStream_t s = (hipStream_t)stream;
   GS_HIP(hipMemcpyAsync(m->h_pinned, m->d_ninst, 4, hipMemcpyDeviceToHost, s));
   GS_HIP(hipStreamSynchronize(s));
-  if (keys) *keys = (const uint32_t*)m->keys[m->sorted].ptr;
-  if (vals) {
-    GS_TRY(ensure(m, m->dbg_g, (size_t)std::max<int64_t>(m->inst_cap, 1) * 4, s));
-    GS_HIP(gather_gaussians((const uint32_t*)m->vals[m->sorted].ptr, (const uint32_t*)m->emit_g.ptr, m->d_ninst,
-                            m->inst_cap, (uint32_t*)m->dbg_g.ptr, s));
+  if (keys) {
+    const int64_t held = std::max<int64_t>(m->inst_cap, 1);
+    GS_TRY(ensure(m, m->dbg_t, (size_t)held * 4, s));
+    GS_HIP(list_tiles((const uint2*)m->ranges.ptr, m->last_va.total_tiles, held, (uint32_t*)m->dbg_t.ptr, s));
     GS_HIP(hipStreamSynchronize(s));
-    *vals = (const uint32_t*)m->dbg_g.ptr;
+    *keys = (const uint32_t*)m->dbg_t.ptr;
   }
+  if (vals) *vals = (const uint32_t*)m->list_g.ptr;
   if (n_inst) *n_inst = m->h_pinned[0];
   if (ranges) *ranges = (const uint32_t*)m->ranges.ptr;
   if (n_tiles) *n_tiles = m->last_va.total_tiles;
@@ -1375,7 +1419,7 @@ gs_status gs_set_instance_policy(gs_map* m, int32_t sync_plan, int64_t capacity)
   if (capacity < 0 || capacity > (int64_t)UINT32_MAX) return fail(GS_ERR_INVALID, "capacity out of range");
   if (capacity > m->inst_cap) {
     hipStream_t s = nullptr;
-    GS_TRY(ensure_instances(m, capacity, 0, s));
+    GS_TRY(ensure_instances(m, capacity, false, 0, s));
     GS_HIP(hipStreamSynchronize(s));
   }
   m->sync_plan = sync_plan != 0;

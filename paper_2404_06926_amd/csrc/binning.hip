@@ -1,4 +1,5 @@
-// Tile binning (Sec. III-A depth order, Sec. III-D.2 footprint tiles).
+// Tile binning by radix sorts (Sec. III-A depth order, Sec. III-D.2 footprint tiles), for the
+// images whose cells do not fit the counters of tilelist.hip, and the scans.
 //
 // The order the blend needs is (global tile, depth, Gaussian index). It is reached in two
 // small sorts instead of one wide one:
@@ -229,18 +230,6 @@ __device__ __forceinline__ uint32_t sort_count(const uint32_t* n_dev, int64_t ca
   return (int64_t)n <= cap ? n : 0u;
 }
 
-// Logical index of this block among G. Workgroups are dispatched to the eight XCDs in
-// turn (block b to XCD b mod 8); the logical order numbers each XCD's blocks
-// consecutively, so that blocks owning neighbouring runs of keys share an L2: in the down
-// sweep a digit's output run of one block ends where the next block's begins, and the two
-// halves of a 32-B sector they share meet in that L2 instead of reaching HBM as two
-// partial writes.
-__device__ __forceinline__ int sort_block(int G) {
-  const int b = (int)blockIdx.x, x = b & 7, j = b >> 3;
-  const int q = G >> 3, r = G & 7;  // XCDs 0 .. r-1 take q + 1 blocks, the others q
-  return x < r ? x * (q + 1) + j : r * (q + 1) + (x - r) * q + j;
-}
-
 // Tiles [t0, t1) of logical block g among G for n keys.
 __device__ __forceinline__ void sort_share(uint32_t n, int G, int g, int64_t& t0, int64_t& t1) {
   const int64_t nt = ((int64_t)n + kSortTile - 1) / kSortTile;
@@ -271,7 +260,7 @@ k_radix_up(const K* __restrict__ keys, const uint32_t* __restrict__ n_dev, int64
   for (int d = lane; d < 256; d += 64) s_h[wid][d] = 0;
   __syncthreads();
   const uint32_t n = sort_count(n_dev, cap);
-  const int g = sort_block(G);
+  const int g = xcd_block((int)blockIdx.x, G);
   int64_t t0, t1;
   sort_share(n, G, g, t0, t1);
   // the next tile's keys are loaded while this one is counted
@@ -342,7 +331,7 @@ k_radix_down(const K* __restrict__ kin, const uint32_t* __restrict__ vin, K* __r
   __shared__ uint32_t s_val[kSortTile];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const uint32_t n = sort_count(n_dev, cap);
-  const int g = sort_block(G);
+  const int g = xcd_block((int)blockIdx.x, G);
   int64_t t0, t1;
   sort_share(n, G, g, t0, t1);
   if (t0 >= t1) return;
@@ -506,21 +495,6 @@ k_block_starts(const uint32_t* __restrict__ offsets, const uint32_t* __restrict_
   const int64_t o = offsets[k];
   const int64_t e = min(k + 1 < n_pairs ? (int64_t)offsets[k + 1] : total, min(total, capacity));
   for (int64_t b = (o + kLb - 1) / kLb; b * kLb < e; ++b) block_start[b] = (uint32_t)k;
-}
-
-// position of the r-th set bit (r counted from 0) of a 32-bit word that has more than r
-__device__ __forceinline__ int nth_set_bit32(uint32_t w, uint32_t r) {
-  int pos = 0;
-#pragma unroll
-  for (int sh = 16; sh >= 1; sh >>= 1) {
-    const uint32_t c = (uint32_t)__popc(w & ((1u << sh) - 1u));
-    if (r >= c) {
-      r -= c;
-      w >>= sh;
-      pos += sh;
-    }
-  }
-  return pos;
 }
 
 __global__ void __launch_bounds__(kLbThreads)

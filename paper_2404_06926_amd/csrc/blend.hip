@@ -300,8 +300,8 @@ k_split_merge(ViewsArg va, const uint2* __restrict__ ranges, SplitArg sp) {
 // Pass 1 of a split tile: block b takes chunk extra[b].y - 1 of tile extra[b].x (every
 // chunk but the last), one pixel per lane as k_blend_fwd with PX = 1.
 __global__ void __launch_bounds__(kBlendBlock)
-k_blend_trans(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32_t* __restrict__ vals,
-              const uint32_t* __restrict__ emit_g, const uint2* __restrict__ ranges, SplitArg sp) {
+k_blend_trans(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32_t* __restrict__ list_g,
+              const uint2* __restrict__ ranges, SplitArg sp) {
   constexpr int NT = kBlendBlock, NW = NT / 64;
   __shared__ float4 s_a[NT];  // mx, my, A, B
   __shared__ float2 s_b[NT];  // C, o
@@ -335,7 +335,7 @@ k_blend_trans(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint
     const int kk = base + (int)threadIdx.x;
     uint32_t qm = 0;
     if (kk < end) {
-      const uint32_t g = emit_g[vals[rg.x + kk]];
+      const uint32_t g = list_g[rg.x + kk];
       const float4* r = vrec + (size_t)g * 4;
       const float4 r0 = r[0], r1 = r[1], r2 = r[2];
       s_a[threadIdx.x] = blend_stage_a(r0);
@@ -365,34 +365,12 @@ k_blend_trans(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint
   split_field(sp, slot0 + c, 0)[ly * kTile + lx] = fabsf(T);
 }
 
-// Items of a render: every tile longer than the chunk length and than `balance` times the
-// mean list takes ceil(n / L) state slots and lists its chunks >= 1 as extra items. counts[0..1]
-// are zero on entry.
+// The chunks of every tile (split_tile); counts[0..1] are zero on entry.
 __global__ void k_split_items(const uint2* __restrict__ ranges, int32_t n_tiles, SplitArg sp) {
   const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
   if (t >= n_tiles) return;
   const uint2 r = ranges[t];
-  const uint32_t n = r.y > r.x ? r.y - r.x : 0u;
-  const uint32_t n_inst = *sp.n_inst;
-  const uint32_t L = chunk_len(n_inst, sp.par, sp.min_len);
-  // lists within `balance` times the mean keep the launch balanced without a split
-  const float keep = sp.balance * (float)n_inst / (float)n_tiles;
-  uint32_t slot = kNoSlot;
-  if (n > L && (float)n > keep) {
-    const uint32_t nch = (n + L - 1u) / L;
-    const uint32_t s0 = atomicAdd(&sp.counts[1], nch);
-    const uint32_t e0 = atomicAdd(&sp.counts[0], nch - 1u);
-    const uint32_t par = (uint32_t)sp.par;
-    if (s0 + nch <= 2u * par && e0 + nch - 1u <= par) {
-      slot = s0;
-      for (uint32_t c = 1; c < nch; ++c) sp.extra[e0 + c - 1u] = make_uint2((uint32_t)t, c);
-    } else {
-      // cannot happen with L >= instances / par; kept consistent anyway: the tile is
-      // blended whole and its reserved items are marked empty
-      for (uint32_t c = 1; c < nch && e0 + c - 1u < par; ++c) sp.extra[e0 + c - 1u] = make_uint2(kNoSlot, 0u);
-    }
-  }
-  sp.tile_slot[t] = slot;
+  split_tile(sp, t, r.y > r.x ? r.y - r.x : 0u, *sp.n_inst, n_tiles, sp.counts);
 }
 
 hipError_t split_items(const uint2* ranges, int32_t n_tiles, const SplitArg& sp, hipStream_t s) {
@@ -404,8 +382,8 @@ hipError_t split_items(const uint2* ranges, int32_t n_tiles, const SplitArg& sp,
 // DEPTH: also accumulate the depth map D = sum d_i a_i T_i (Eq. 6) for views that ask.
 template <int PX, bool DEPTH>
 __global__ void __launch_bounds__(kBlendBlock / PX)
-k_blend_fwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32_t* __restrict__ vals,
-            const uint32_t* __restrict__ emit_g, const uint2* __restrict__ ranges, SplitArg sp) {
+k_blend_fwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32_t* __restrict__ list_g,
+            const uint2* __restrict__ ranges, SplitArg sp) {
   constexpr int NT = kBlendBlock / PX;
   // per entry: (mx, my, A, B), (C, o, r, g), (b, camera-frame depth, quadrant mask bits, -):
   // one 48-B record, so a wave-uniform entry index addresses all of it from one register
@@ -466,7 +444,7 @@ k_blend_fwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
     const int kk = base + (int)threadIdx.x;
     uint32_t qm = 0;
     if (kk < it.end) {
-      const uint32_t g = emit_g[vals[rg.x + kk]];
+      const uint32_t g = list_g[rg.x + kk];
       const float4* r = vrec + (size_t)g * 4;
       const float4 r0 = r[0], r1 = r[1], r2 = r[2];
       qm = quadrant_mask(r0, r1, r2.w, tx, ty);
@@ -558,8 +536,8 @@ k_blend_fwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
 // give a tenth gradient, dL/d(camera-frame depth) = sum_px a_i T_i dL/dD.
 template <int PX, bool DET, bool MAPS>
 __global__ void __launch_bounds__(kBlendBlock / PX)
-k_blend_bwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32_t* __restrict__ vals,
-            const uint32_t* __restrict__ emit_g, const uint2* __restrict__ ranges, float* __restrict__ g2d,
+k_blend_bwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32_t* __restrict__ list_g,
+            const uint32_t* __restrict__ list_e, const uint2* __restrict__ ranges, float* __restrict__ g2d,
             float* __restrict__ inst_grad, float* __restrict__ exp_part, SplitArg sp) {
   constexpr int NT = kBlendBlock / PX;
   constexpr int NW = NT / 64;
@@ -674,8 +652,7 @@ k_blend_bwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
     __syncthreads();
     uint32_t qm = 0;
     if ((int)threadIdx.x < cnt) {
-      const uint32_t e = vals[rg.x + base + threadIdx.x];
-      const uint32_t g = emit_g[e];
+      const uint32_t g = list_g[rg.x + base + threadIdx.x];
       const float4* r = vrec + (size_t)g * 4;
       const float4 r0 = r[0], r1 = r[1], r2 = r[2];
       s_r[threadIdx.x][0] = blend_stage_a(r0);
@@ -685,7 +662,7 @@ k_blend_bwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
       qm = quadrant_mask(r0, r1, r2.w, tx, ty);
       s_m[threadIdx.x] = (uint8_t)qm;
       if (DET) {
-        s_e[threadIdx.x] = e;
+        s_e[threadIdx.x] = list_e[rg.x + base + threadIdx.x];
 #pragma unroll
         for (int w = 0; w < NW; ++w)
 #pragma unroll
@@ -814,7 +791,7 @@ k_blend_bwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
   if (DET) {
     // entries past every pixel's last contributor carry no gradient
     for (int k = max(nmax, it.begin) + (int)threadIdx.x; k < it.end; k += NT) {
-      float4* dst = (float4*)(inst_grad + (size_t)vals[rg.x + k] * 12);
+      float4* dst = (float4*)(inst_grad + (size_t)list_e[rg.x + k] * 12);
       const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
       dst[0] = z;
       dst[1] = z;
@@ -864,42 +841,42 @@ __global__ void k_exposure_reduce(ViewsArg va, const float* __restrict__ exp_par
 
 
 template <int PX>
-static void launch_fwd(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* vals,
-                       const uint32_t* emit_g, const uint2* ranges, const SplitArg& sp, hipStream_t s) {
+static void launch_fwd(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* list_g,
+                       const uint2* ranges, const SplitArg& sp, hipStream_t s) {
   bool depth = false;
   for (int v = 0; v < va.n; ++v) depth = depth || va.v[v].out_depth != nullptr;
   if (depth)
-    hipLaunchKernelGGL((k_blend_fwd<PX, true>), item_grid(va, sp), dim3(kBlendBlock / PX), 0, s, va, rec, N, vals,
-                       emit_g, ranges, sp);
+    hipLaunchKernelGGL((k_blend_fwd<PX, true>), item_grid(va, sp), dim3(kBlendBlock / PX), 0, s, va, rec, N, list_g,
+                       ranges, sp);
   else
-    hipLaunchKernelGGL((k_blend_fwd<PX, false>), item_grid(va, sp), dim3(kBlendBlock / PX), 0, s, va, rec, N, vals,
-                       emit_g, ranges, sp);
+    hipLaunchKernelGGL((k_blend_fwd<PX, false>), item_grid(va, sp), dim3(kBlendBlock / PX), 0, s, va, rec, N, list_g,
+                       ranges, sp);
 }
 
 template <int PX, bool MAPS>
-static void launch_bwd_maps(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* vals,
-                            const uint32_t* emit_g, const uint2* ranges, float* g2d, float* inst_grad,
+static void launch_bwd_maps(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* list_g,
+                            const uint32_t* list_e, const uint2* ranges, float* g2d, float* inst_grad,
                             float* exp_part, const SplitArg& sp, hipStream_t s) {
   if (inst_grad) {
     hipLaunchKernelGGL((k_blend_bwd<PX, true, MAPS>), item_grid(va, sp), dim3(kBlendBlock / PX), 0, s, va, rec, N,
-                       vals, emit_g, ranges, g2d, inst_grad, exp_part, sp);
+                       list_g, list_e, ranges, g2d, inst_grad, exp_part, sp);
     hipLaunchKernelGGL(k_exposure_reduce, dim3(va.n), dim3(64), 0, s, va, exp_part);
   } else {
     hipLaunchKernelGGL((k_blend_bwd<PX, false, MAPS>), item_grid(va, sp), dim3(kBlendBlock / PX), 0, s, va, rec, N,
-                       vals, emit_g, ranges, g2d, inst_grad, exp_part, sp);
+                       list_g, list_e, ranges, g2d, inst_grad, exp_part, sp);
   }
 }
 
 template <int PX>
-static void launch_bwd(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* vals,
-                       const uint32_t* emit_g, const uint2* ranges, float* g2d, float* inst_grad, float* exp_part,
+static void launch_bwd(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* list_g,
+                       const uint32_t* list_e, const uint2* ranges, float* g2d, float* inst_grad, float* exp_part,
                        const SplitArg& sp, hipStream_t s) {
   bool maps = false;
   for (int v = 0; v < va.n; ++v) maps = maps || va.v[v].dl_ddepth != nullptr || va.v[v].dl_dopac != nullptr;
   if (maps)
-    launch_bwd_maps<PX, true>(va, rec, N, vals, emit_g, ranges, g2d, inst_grad, exp_part, sp, s);
+    launch_bwd_maps<PX, true>(va, rec, N, list_g, list_e, ranges, g2d, inst_grad, exp_part, sp, s);
   else
-    launch_bwd_maps<PX, false>(va, rec, N, vals, emit_g, ranges, g2d, inst_grad, exp_part, sp, s);
+    launch_bwd_maps<PX, false>(va, rec, N, list_g, list_e, ranges, g2d, inst_grad, exp_part, sp, s);
 }
 
 hipError_t exposure_reduce(const ViewsArg& va, const float* exp_part, hipStream_t s) {
@@ -907,18 +884,16 @@ hipError_t exposure_reduce(const ViewsArg& va, const float* exp_part, hipStream_
   return hipGetLastError();
 }
 
-hipError_t blend_forward(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* vals,
-                         const uint32_t* emit_g, const uint2* ranges, const SplitArg& sp, int px,
-                         hipStream_t s) {
+hipError_t blend_forward(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* list_g,
+                         const uint2* ranges, const SplitArg& sp, int px, hipStream_t s) {
   if (va.total_tiles <= 0) return hipSuccess;
   if (px != 1 && px != 2 && px != 4) return hipErrorInvalidValue;
   if (sp.par > 0)
-    hipLaunchKernelGGL(k_blend_trans, dim3((unsigned)sp.par), dim3(kBlendBlock), 0, s, va, rec, N, vals, emit_g,
-                       ranges, sp);
+    hipLaunchKernelGGL(k_blend_trans, dim3((unsigned)sp.par), dim3(kBlendBlock), 0, s, va, rec, N, list_g, ranges, sp);
   switch (px) {
-    case 1: launch_fwd<1>(va, rec, N, vals, emit_g, ranges, sp, s); break;
-    case 2: launch_fwd<2>(va, rec, N, vals, emit_g, ranges, sp, s); break;
-    default: launch_fwd<4>(va, rec, N, vals, emit_g, ranges, sp, s); break;
+    case 1: launch_fwd<1>(va, rec, N, list_g, ranges, sp, s); break;
+    case 2: launch_fwd<2>(va, rec, N, list_g, ranges, sp, s); break;
+    default: launch_fwd<4>(va, rec, N, list_g, ranges, sp, s); break;
   }
   if (sp.par > 0) {
     bool depth = false;
@@ -931,14 +906,14 @@ hipError_t blend_forward(const ViewsArg& va, const float4* rec, int32_t N, const
   return hipGetLastError();
 }
 
-hipError_t blend_backward(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* vals,
-                          const uint32_t* emit_g, const uint2* ranges, float* g2d, float* inst_grad,
+hipError_t blend_backward(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* list_g,
+                          const uint32_t* list_e, const uint2* ranges, float* g2d, float* inst_grad,
                           float* exp_part, const SplitArg& sp, int px, hipStream_t s) {
   if (va.total_tiles <= 0) return hipSuccess;
   switch (px) {
-    case 1: launch_bwd<1>(va, rec, N, vals, emit_g, ranges, g2d, inst_grad, exp_part, sp, s); break;
-    case 2: launch_bwd<2>(va, rec, N, vals, emit_g, ranges, g2d, inst_grad, exp_part, sp, s); break;
-    case 4: launch_bwd<4>(va, rec, N, vals, emit_g, ranges, g2d, inst_grad, exp_part, sp, s); break;
+    case 1: launch_bwd<1>(va, rec, N, list_g, list_e, ranges, g2d, inst_grad, exp_part, sp, s); break;
+    case 2: launch_bwd<2>(va, rec, N, list_g, list_e, ranges, g2d, inst_grad, exp_part, sp, s); break;
+    case 4: launch_bwd<4>(va, rec, N, list_g, list_e, ranges, g2d, inst_grad, exp_part, sp, s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -67,8 +67,8 @@ __device__ __forceinline__ float wave_sum_all(float x) {
 
 template <bool DET>
 __global__ void __launch_bounds__(256)
-k_blend_bwd_pg(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32_t* __restrict__ vals,
-               const uint32_t* __restrict__ emit_g, const uint2* __restrict__ ranges, float* __restrict__ g2d,
+k_blend_bwd_pg(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32_t* __restrict__ list_g,
+               const uint32_t* __restrict__ list_e, const uint2* __restrict__ ranges, float* __restrict__ g2d,
                float* __restrict__ inst_grad, float* __restrict__ exp_part, SplitArg sp) {
   // pixel slot ps = 64 w + lane: wave w owns the tile's 8x8 quadrant w
   __shared__ float s_T[256];          // transmittance after the current chunk
@@ -160,8 +160,8 @@ k_blend_bwd_pg(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uin
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = make_float4(0.f, 0.f, 0.f, 0.f);
     float c2 = 0.f;
     if (live) {
-      e_idx = vals[rg.x + j];
-      g = emit_g[e_idx];
+      g = list_g[rg.x + j];
+      if (DET) e_idx = list_e[rg.x + j];
       const float4* r = vrec + (size_t)g * 4;
       a = blend_stage_a(r[0]);
       b = r[1];
@@ -250,7 +250,7 @@ k_blend_bwd_pg(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uin
   if (DET) {
     // entries past every pixel's last contributor carry no gradient
     for (int k = max(nlist, it.begin) + (int)threadIdx.x; k < it.end; k += 256) {
-      float4* dst = (float4*)(inst_grad + (size_t)vals[rg.x + k] * 12);
+      float4* dst = (float4*)(inst_grad + (size_t)list_e[rg.x + k] * 12);
       const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
       dst[0] = z;
       dst[1] = z;
@@ -290,16 +290,16 @@ k_blend_bwd_pg(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uin
   }
 }
 
-hipError_t blend_backward_per_gaussian(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* vals,
-                                       const uint32_t* emit_g, const uint2* ranges, float* g2d, float* inst_grad,
+hipError_t blend_backward_per_gaussian(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* list_g,
+                                       const uint32_t* list_e, const uint2* ranges, float* g2d, float* inst_grad,
                                        float* exp_part, const SplitArg& sp, hipStream_t s) {
   if (va.total_tiles <= 0) return hipSuccess;
   if (inst_grad) {
-    hipLaunchKernelGGL(k_blend_bwd_pg<true>, item_grid(va, sp), dim3(256), 0, s, va, rec, N, vals, emit_g, ranges,
+    hipLaunchKernelGGL(k_blend_bwd_pg<true>, item_grid(va, sp), dim3(256), 0, s, va, rec, N, list_g, list_e, ranges,
                        g2d, inst_grad, exp_part, sp);
     return exposure_reduce(va, exp_part, s);
   } else
-    hipLaunchKernelGGL(k_blend_bwd_pg<false>, item_grid(va, sp), dim3(256), 0, s, va, rec, N, vals, emit_g, ranges,
+    hipLaunchKernelGGL(k_blend_bwd_pg<false>, item_grid(va, sp), dim3(256), 0, s, va, rec, N, list_g, list_e, ranges,
                        g2d, inst_grad, exp_part, sp);
   return hipGetLastError();
 }

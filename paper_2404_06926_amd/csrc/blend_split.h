@@ -79,6 +79,32 @@ __device__ __forceinline__ void chunk_range(int n, int nch, int c, int& begin, i
   end = (int)((int64_t)(c + 1) * n / nch);
 }
 
+// Items of tile t (n entries): a tile longer than the chunk length and than `balance` times
+// the mean list takes ceil(n / L) state slots and lists its chunks >= 1 as extra items.
+// cnt[0..1]: extra items and slots taken so far (in LDS or device memory).
+__device__ __forceinline__ void split_tile(const SplitArg& sp, int t, uint32_t n, uint32_t n_inst, int32_t n_tiles,
+                                           uint32_t* cnt) {
+  const uint32_t L = chunk_len(n_inst, sp.par, sp.min_len);
+  // lists within `balance` times the mean keep the launch balanced without a split
+  const float keep = sp.balance * (float)n_inst / (float)n_tiles;
+  uint32_t slot = kNoSlot;
+  if (n > L && (float)n > keep) {
+    const uint32_t nch = (n + L - 1u) / L;
+    const uint32_t s0 = atomicAdd(&cnt[1], nch);
+    const uint32_t e0 = atomicAdd(&cnt[0], nch - 1u);
+    const uint32_t par = (uint32_t)sp.par;
+    if (s0 + nch <= 2u * par && e0 + nch - 1u <= par) {
+      slot = s0;
+      for (uint32_t c = 1; c < nch; ++c) sp.extra[e0 + c - 1u] = make_uint2((uint32_t)t, c);
+    } else {
+      // cannot happen with L >= instances / par; kept consistent anyway: the tile is
+      // blended whole and its reserved items are marked empty
+      for (uint32_t c = 1; c < nch && e0 + c - 1u < par; ++c) sp.extra[e0 + c - 1u] = make_uint2(kNoSlot, 0u);
+    }
+  }
+  sp.tile_slot[t] = slot;
+}
+
 struct BlendItem {
   int tile, c, nch, begin, end;  // chunk c of nch covers list positions [begin, end)
   uint32_t slot0;                // first state slot of the tile, kNoSlot if not split

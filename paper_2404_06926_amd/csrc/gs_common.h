@@ -111,6 +111,42 @@ struct LossFinish {
 //            the rectangle (complete when the rectangle has at most 64 tiles)
 // Only records whose tile count is > 0 are written.
 
+// Orders a wave's LDS accesses on either side (a wave executes its LDS instructions in
+// order; the fences keep the compiler from moving accesses across and make it wait for
+// the earlier ones).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// position of the r-th set bit (r counted from 0) of a 32-bit word that has more than r
+__device__ __forceinline__ int nth_set_bit32(uint32_t w, uint32_t r) {
+  int pos = 0;
+#pragma unroll
+  for (int sh = 16; sh >= 1; sh >>= 1) {
+    const uint32_t c = (uint32_t)__popc(w & ((1u << sh) - 1u));
+    if (r >= c) {
+      r -= c;
+      w >>= sh;
+      pos += sh;
+    }
+  }
+  return pos;
+}
+
+// Logical index of block b among G (b = 0 at a block index that is a multiple of 8).
+// Workgroups are dispatched to the eight XCDs in turn (block b to XCD b mod 8); the logical
+// order numbers each XCD's blocks consecutively, so that blocks owning neighbouring runs of
+// output share an L2: where one block's run of a digit (sort) or tile (lists) ends the next
+// block's begins, and the two parts of a line they share meet in that L2 instead of reaching
+// HBM as partial writes.
+__device__ __forceinline__ int xcd_block(int b, int G) {
+  const int x = b & 7, j = b >> 3;
+  const int q = G >> 3, r = G & 7;  // XCDs 0 .. r-1 take q + 1 blocks, the others q
+  return x < r ? x * (q + 1) + j : r * (q + 1) + (x - r) * q + j;
+}
+
 __device__ __forceinline__ int view_of_tile(const ViewsArg& va, int tile) {
   int v = 0;
   for (int k = 1; k < va.n; ++k)

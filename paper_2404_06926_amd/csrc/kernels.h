@@ -39,6 +39,9 @@ struct ProjSide {
   uint32_t nvn_value;
   uint32_t* zero;
   int64_t n_zero;
+  // nullptr, or per (view, Gaussian) pair word: the tile rectangle and hit mask of its record,
+  // zero without a tile (view-major, read contiguously by the tile lists)
+  uint4* pairs;
 };
 hipError_t project_forward(int deg, const float* P, int64_t cap, int32_t N, const ViewsArg& va, float near_z,
                            float4* rec, uint32_t* counts, uint32_t* dkey, const ProjSide& side, hipStream_t s);
@@ -80,6 +83,27 @@ hipError_t radix_sort_u32(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* 
 hipError_t tile_ranges(const uint32_t* tiles, const uint32_t* n_dev, int64_t cap, uint2* ranges, int64_t n_tiles,
                        hipStream_t s);
 
+struct SplitArg;
+// tile lists by counting (tilelist.hip), for views whose cells fit the kernels' LDS and ids
+// that fit an entry (tile_lists_fit; max_instances: of a deterministic render, else 0).
+// pairs: the projection's pair words. space: tile_space_bytes (16-B aligned).
+bool tile_lists_fit(const ViewsArg& va, int64_t N, int64_t max_instances);
+int64_t tile_space_bytes(const ViewsArg& va, int32_t N);
+// Tile ranges and *n_inst; overflow as in duplicate_keys, the ranges being empty when more
+// than cap instances are needed. split_counts: the split's counters (or nullptr), cleared.
+hipError_t tile_lists_plan(const float4* rec, const uint4* pairs, int32_t N, const ViewsArg& va, void* space,
+                           int64_t cap, uint2* ranges, uint32_t* n_inst, uint32_t* overflow, uint32_t* split_counts,
+                           hipStream_t s);
+// list_g: Gaussian of every instance. list_e: nullptr, or its emission index, from inst_off,
+// the first emission index of every pair (emit_g: workspace of one word per instance then).
+// entries, merged: 8 B per instance. va.n_inst and va.inst_cap are set. Also the work items of
+// long lists (sp).
+hipError_t tile_lists_build(const float4* rec, const uint4* pairs, const uint32_t* dkey, const uint32_t* inst_off,
+                            int32_t N, const ViewsArg& va, void* space, const uint2* ranges, uint64_t* entries,
+                            uint64_t* merged, uint32_t* emit_g, uint32_t* list_g, uint32_t* list_e,
+                            const SplitArg& sp, hipStream_t s);
+hipError_t list_tiles(const uint2* ranges, int64_t n_tiles, int64_t cap, uint32_t* tiles, hipStream_t s);
+
 // blending (blend.hip)
 // Long tile lists are split into chunks that separate workgroups blend: a tile whose list
 // is longer than `balance` times the mean list and than the chunk length L = max(min_len,
@@ -93,7 +117,7 @@ constexpr int kSplitFields = 7;   // per chunk and pixel: see blend.hip
 struct SplitArg {
   uint32_t* tile_slot;      // per tile: first state slot of a split tile, kNoSlot otherwise
   uint2* extra;             // (tile, chunk) of every chunk >= 1 of a split tile, [0, counts[0])
-  uint32_t* counts;         // [0] extra chunks, [1] slots taken; zero before split_items
+  uint32_t* counts;         // [0] extra chunks, [1] slots taken
   const uint32_t* n_inst;   // instance count of the render
   float* state;             // kSplitFields x 256 floats per slot (2 par slots)
   int32_t par;              // 0: no tile is split
@@ -102,24 +126,24 @@ struct SplitArg {
 };
 hipError_t split_items(const uint2* ranges, int32_t n_tiles, const SplitArg& sp, hipStream_t s);
 
-// vals: emission index of each instance in blend order; emit_g: Gaussian of each emission index.
+// list_g: Gaussian of each instance in blend order; list_e: its emission index (read by the
+// deterministic backward only).
 // px: pixels per lane (1, 2 or 4), see blend.hip.
-hipError_t blend_forward(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* vals,
-                         const uint32_t* emit_g, const uint2* ranges, const SplitArg& sp, int px,
-                         hipStream_t s);
+hipError_t blend_forward(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* list_g,
+                         const uint2* ranges, const SplitArg& sp, int px, hipStream_t s);
 // Gradients of (mean2d, conic, opacity, colour, depth) per (view, Gaussian): with inst_grad == nullptr
 // they are added to g2d with wave-reduced atomics; otherwise every instance's gradient is
 // written to inst_grad[emission index] (12 floats, fixed-order reduction, deterministic).
 // sp: the split of the render whose lists and saved state this backward uses.
-hipError_t blend_backward(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* vals,
-                          const uint32_t* emit_g, const uint2* ranges, float* g2d, float* inst_grad,
+hipError_t blend_backward(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* list_g,
+                          const uint32_t* list_e, const uint2* ranges, float* g2d, float* inst_grad,
                           float* exp_part, const SplitArg& sp, int px, hipStream_t s);
 
 // Per-Gaussian form of blend_backward (blend_pg.hip): colour and exposure gradients only
 // (no depth / opacity maps); the chunks of split tiles (sp, as in blend_backward) are
 // separate work items.
-hipError_t blend_backward_per_gaussian(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* vals,
-                                       const uint32_t* emit_g, const uint2* ranges, float* g2d, float* inst_grad,
+hipError_t blend_backward_per_gaussian(const ViewsArg& va, const float4* rec, int32_t N, const uint32_t* list_g,
+                                       const uint32_t* list_e, const uint2* ranges, float* g2d, float* inst_grad,
                                        float* exp_part, const SplitArg& sp, hipStream_t s);
 // fixed-order reduction of the per-tile exposure partials of the deterministic backward
 hipError_t exposure_reduce(const ViewsArg& va, const float* exp_part, hipStream_t s);

@@ -16,15 +16,6 @@
 
 namespace gs {
 
-// Orders a wave's LDS accesses on either side (a wave executes its LDS instructions in
-// order; the fences keep the compiler from moving accesses across and make it wait for
-// the earlier ones).
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Tile tests of a wave: the tests of all its rectangles of up to 64 tiles (the hit mask's
 // width) are laid end to end, 64 (pair, tile) tests per step, so that the work per step
 // does not depend on how unevenly the rectangle sizes fall over the lanes; larger
@@ -142,6 +133,10 @@ k_project_fwd(const float* __restrict__ P, int64_t cap, int32_t N, ViewsArg va, 
     counts[vi] = cnt;
     // depth-sort key of the pair: float bits of a positive depth, largest key when unused
     dkey[vi] = cnt ? __float_as_uint(kp.zh) : 0xffffffffu;
+    const uint4 word = cnt ? make_uint4((uint32_t)r[0] | ((uint32_t)r[1] << 16), (uint32_t)r[2] | ((uint32_t)r[3] << 16),
+                                        (uint32_t)hits, (uint32_t)(hits >> 32))
+                           : make_uint4(0u, 0u, 0u, 0u);
+    if (side.pairs) side.pairs[vi] = word;
     if (cnt == 0) continue;
     // view-dependent colour: max(0, sum_k sh_k Y_k(dir) + 0.5)
     float dx = m0 - V.campos[0], dy = m1 - V.campos[1], dz = m2 - V.campos[2];
@@ -163,9 +158,8 @@ k_project_fwd(const float* __restrict__ P, int64_t cap, int32_t N, ViewsArg va, 
     o[0] = make_float4(kp.mx, kp.my, kp.A, kp.B);
     o[1] = make_float4(kp.C, kp.o, col[0], col[1]);
     o[2] = make_float4(col[2], kp.zh, 0.0f, kp.thr);
-    o[3] = make_float4(__uint_as_float((uint32_t)r[0] | ((uint32_t)r[1] << 16)),
-                       __uint_as_float((uint32_t)r[2] | ((uint32_t)r[3] << 16)), __uint_as_float((uint32_t)hits),
-                       __uint_as_float((uint32_t)(hits >> 32)));
+    o[3] = make_float4(__uint_as_float(word.x), __uint_as_float(word.y), __uint_as_float(word.z),
+                       __uint_as_float(word.w));
   }
 }
 

@@ -1,0 +1,963 @@
+// Tile lists by counting and one small sort per cell of 2x2 tiles (Sec. III-A depth order,
+// Sec. III-D.2 footprint tiles).
+//
+// Input: per (view, Gaussian) pair its depth and the tiles it reaches. Output: every tile's
+// Gaussians by (depth, index), consecutive in one array in tile order, and the tiles' ranges:
+//   k_cell_count    each block counts its pairs' entries per cell, and the hits of the cell's
+//                   four tiles, in LDS -> its row of the view's matrices;
+//   k_cell_colscan  exclusive prefix of every cell's entries over the rows, and the totals;
+//   k_cell_offsets  exclusive scans of the totals (one block): tile ranges, cell starts, the
+//                   instance count, overflow, and the chunks of long lists;
+//   k_cell_place    each block walks its pairs again and writes one entry (depth, Gaussian,
+//                   which of the four tiles) per cell it reaches at the cell's next position,
+//                   in any order within the block;
+//   k_cell_sort     one block per cell orders its entries in LDS and deals them out to its
+//                   tiles' lists by ballots (two sizes of block); cells of more than kSortMost
+//                   entries are ordered in chunks, merged and dealt out by k_cell_merge.
+// (depth, Gaussian) is unique in a cell, so the lists do not depend on the order of arrival.
+//
+// Why cells: what bounds the placement is not its bytes but the scattered writes, which L2
+// writes back as partial lines (one 8-B entry per hit: 272 MB written for 55 MB of entries at
+// 6.9 M hits, 97 us; one per cell: 114 MB, 44 us), and a Gaussian reaches two to three times
+// fewer cells than tiles, which the sort gains as well.
+//
+// Measured against the path it replaced where it applies (a depth sort of the pairs by four
+// radix passes, a scan of the counts in that order, an emission, two radix passes by tile id,
+// the ranges), in us: 1M Gaussians at 1280x720 (6.9 M instances) 257 -> 142; eight views of 1M
+// (41.6 M) 1416 -> 735; 3M at 1920x1200 (35.9 M) 917 -> 550; a street map of 520k with a long
+// horizon (0.7 M) 149 -> 106; 10k at 256x192 (17.8 k) 99 -> 34, of which most were launches
+// (20 -> 6). At 1M the counting takes 27, the column and total scans 16, the placement 44 and
+// the sort 40. Counting and placing issue VALU work for about half of their time.
+//
+// The LDS counters bound the cells of a view (tile_lists_fit); larger images take the radix
+// path (binning.hip).
+#include "blend_split.h"
+#include "gs_common.h"
+#include "kernels.h"
+
+namespace gs {
+
+constexpr int kTlThreads = 512;          // of the counting and placing blocks
+constexpr int kTlMaxCells = 13000;       // 12 B of counters each: within a CU's 160 KiB of LDS
+constexpr int kTlMaxPairs = 32768;       // of one block: its hits per tile are counted in 16 bits
+constexpr int kTlMaskBits = 4;           // entry: depth bits << 32 | Gaussian << 4 | tiles
+constexpr int64_t kTlMaxId = int64_t(1) << (32 - kTlMaskBits);
+
+__host__ __device__ __forceinline__ int cells_of(int tiles) { return (tiles + 1) >> 1; }
+__device__ __forceinline__ int view_cells(const ViewDev& V) { return cells_of(V.tiles_x) * cells_of(V.tiles_y); }
+
+// Cells of the views, all views together; first cell of each view in `base` if given.
+static int64_t cells_total(const ViewsArg& va, int32_t* base = nullptr) {
+  int64_t c = 0;
+  for (int v = 0; v < va.n; ++v) {
+    if (base) base[v] = (int32_t)c;
+    c += (int64_t)cells_of(va.v[v].tiles_x) * cells_of(va.v[v].tiles_y);
+  }
+  return c;
+}
+
+static int max_cells(const ViewsArg& va) {
+  int c = 1;
+  for (int v = 0; v < va.n; ++v) c = std::max(c, cells_of(va.v[v].tiles_x) * cells_of(va.v[v].tiles_y));
+  return c;
+}
+
+bool tile_lists_fit(const ViewsArg& va, int64_t N, int64_t max_instances) {
+  for (int v = 0; v < va.n; ++v)
+    if ((int64_t)cells_of(va.v[v].tiles_x) * cells_of(va.v[v].tiles_y) > kTlMaxCells) return false;
+  return N < kTlMaxId && max_instances < kTlMaxId;
+}
+
+// How the views' pairs fall to the blocks: view v's are shared by blocks [block[v],
+// block[v + 1]), each with a matrix row of the view's cells from word `matrix[v]` on; its
+// cells are numbered from cell[v].
+struct CellBase {
+  int32_t cell[kMaxViews];
+  int32_t block[kMaxViews + 1];
+  int64_t matrix[kMaxViews];
+};
+
+// Blocks: two of 512 lanes per CU with one view, four with several, shared out by the views'
+// cells (a view's entries grow with its size) plus an even part (its pairs do not); at least
+// 256 pairs each, since a block writes and reads a matrix row whatever its share. A view's
+// count is a multiple of eight (xcd_block).
+static CellBase cell_base(const ViewsArg& va, int32_t N) {
+  CellBase b{};
+  const int64_t cells = cells_total(va, b.cell), grid = va.n > 1 ? 1024 : 512;
+  const int64_t fewest = ((int64_t)N + kTlMaxPairs - 1) / kTlMaxPairs, most = std::max<int64_t>(1, ((int64_t)N + 255) / 256);
+  int64_t words = 0;
+  for (int v = 0; v < va.n; ++v) {
+    const int64_t nc = (int64_t)cells_of(va.v[v].tiles_x) * cells_of(va.v[v].tiles_y);
+    const int64_t share = va.n > 1 ? grid * (nc * va.n + cells) / (2 * cells * va.n) : grid;
+    int64_t G = std::min(std::max(share, fewest), most);
+    if (va.n > 1) G = (G + 7) & ~int64_t(7);
+    b.block[v + 1] = b.block[v] + (int32_t)G;
+    b.matrix[v] = words;
+    words += G * nc;
+  }
+  return b;
+}
+static int64_t matrix_words(const ViewsArg& va, const CellBase& b) {
+  const ViewDev& V = va.v[va.n - 1];
+  return b.matrix[va.n - 1] +
+         (int64_t)(b.block[va.n] - b.block[va.n - 1]) * cells_of(V.tiles_x) * cells_of(V.tiles_y);
+}
+
+// The block's view, its number in the view and the view's blocks.
+__device__ __forceinline__ int view_of_block(const CellBase& cb, int n_views, int& g, int& G) {
+  int v = 0;
+  for (int k = 1; k < n_views; ++k)
+    if ((int)blockIdx.x >= cb.block[k]) v = k;
+  G = cb.block[v + 1] - cb.block[v];
+  g = xcd_block((int)blockIdx.x - cb.block[v], G);
+  return v;
+}
+
+// Workspace: per cell and block the packed hits (8 B) and the entries (4 B), then per cell its
+// first entry (one more at the end), per tile its hits, and the sort's work items.
+constexpr int kSortExtra = 1024;
+constexpr uint32_t kAlone = 0xFFFFFFFFu;
+struct TlSpace {
+  uint64_t* hits;
+  uint32_t* entries;
+  uint32_t* start;
+  uint32_t* totals;
+  uint2* extra;      // (cell, chunk >= 1) of cells ordered in chunks
+  uint32_t* count;   // extra items
+  uint32_t* alone;   // per chunked cell: kAlone where its first block orders every chunk, else
+                     // the merging blocks that have finished
+};
+int64_t tile_space_bytes(const ViewsArg& va, int32_t N) {
+  const int64_t c = cells_total(va), m = matrix_words(va, cell_base(va, N));
+  return 12 * m + 4 * (2 * c + 1 + va.total_tiles) + 8 * kSortExtra + 256;
+}
+static TlSpace tl_space(void* ws, const ViewsArg& va, const CellBase& cb) {
+  const int64_t c = cells_total(va), m = matrix_words(va, cb);
+  TlSpace t;
+  t.hits = (uint64_t*)ws;
+  t.extra = (uint2*)(t.hits + m);
+  t.entries = (uint32_t*)(t.extra + kSortExtra);
+  t.start = t.entries + m;
+  t.totals = t.start + c + 1;
+  t.alone = t.totals + va.total_tiles;
+  t.count = t.alone + c;
+  return t;
+}
+
+// Tile rectangle of a pair's 16-B word: x0 | y0 << 16, x1 | y1 << 16, 64-bit hit mask.
+struct PairRect {
+  int x0, y0, rw, rh;
+};
+__device__ __forceinline__ PairRect pair_rect(uint32_t a, uint32_t b) {
+  PairRect r;
+  r.x0 = (int)(a & 0xffffu);
+  r.y0 = (int)(a >> 16);
+  r.rw = (int)(b & 0xffffu) - r.x0 + 1;
+  r.rh = (int)(b >> 16) - r.y0 + 1;
+  return r;
+}
+
+// Inclusive sum over the wave with DPP row operations.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+// Calls entry(cell, tiles, lane of the pair, hits of the pair in its earlier cells, the pair's
+// d and e) once for every cell that one of the wave's 64 pairs reaches (q: the lane's pair
+// word, zero without hits; rp: its record; d, e: values that travel with it). tiles: bit
+// 2 row + column per tile of the cell. A pair's cells come in row-major order. HITS = false:
+// the earlier cells' hits are not needed. `own_row`: 64 B of LDS of this wave.
+//
+// The cells of the rectangles of up to 64 tiles are laid end to end over the lanes, 64 a step,
+// whatever the pairs' sizes (in index order a wave's largest pair has about ten times the
+// mean). A lane's owner is the last pair that starts at or before it: the last start mark in
+// the step, or the pair that holds the step's first cell. Larger rectangles are walked by the
+// whole wave one at a time, 16 cells a step, with the tile predicate evaluated again.
+template <bool HITS, typename F>
+__device__ __forceinline__ void for_each_cell(uint4 q, const float4* __restrict__ rp, uint32_t d, uint32_t e,
+                                              int cells_x, uint8_t* own_row, F entry) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t upto = ~0ull >> (63 - lane);
+  const PairRect r = pair_rect(q.x, q.y);
+  const bool large = r.rw * r.rh > 64;
+  const int hits = large ? 0 : __popc(q.z) + __popc(q.w);
+  const int ncw = ((r.x0 + r.rw - 1) >> 1) - (r.x0 >> 1) + 1, nch = ((r.y0 + r.rh - 1) >> 1) - (r.y0 >> 1) + 1;
+  const int a = hits ? ncw * nch : 0;  // at most 33 x 1, 25 for 8 x 8
+  const int end = wave_scan(a);
+  const int beg = end - a;
+  const int hbeg = HITS ? wave_scan(hits) - hits : 0;
+  const int total = __builtin_amdgcn_readlane(end, 63);
+  int done = 0;  // hits of the steps before
+  for (int base = 0; base < total; base += 64) {  // wave-uniform
+    own_row[lane] = 0xff;
+    wave_lds_sync();
+    if (a > 0 && beg >= base && beg < base + 64) own_row[beg - base] = (uint8_t)lane;
+    wave_lds_sync();
+    const int mark = own_row[lane];
+    const int first = __popcll(__ballot(end <= base));
+    const uint64_t before = __ballot(mark != 0xff) & upto;
+    const int own = before ? __shfl(mark, 63 - __clzll((long long)before), 64) : first;
+    wave_lds_sync();  // the row is rewritten in the next step
+    const uint32_t qx = __shfl(q.x, own), qy = __shfl(q.y, own), mlo = __shfl(q.z, own), mhi = __shfl(q.w, own);
+    const int k = base + lane - __shfl(beg, own), ohb = HITS ? __shfl(hbeg, own) : 0;
+    const uint32_t od = __shfl(d, own), oe = __shfl(e, own);
+    const PairRect o = pair_rect(qx, qy);
+    const int cx0 = o.x0 >> 1, cw = ((o.x0 + o.rw - 1) >> 1) - cx0 + 1;
+    // row and column of cell k < 64 among cw <= 33: the quotient's fractional part is a
+    // multiple of 1 / cw and k * rcp(cw) is within 64 x 2^-23 of k / cw, so adding 1 / 128
+    // before truncating gives the exact quotient
+    const int cr = (int)fmaf((float)k, __builtin_amdgcn_rcpf((float)cw), 1.0f / 128.0f);
+    const int cx = cx0 + k - cr * cw, cy = (o.y0 >> 1) + cr;
+    // the cell's tiles in the mask: columns dx, dx + 1 of rows dy, dy + 1 (-1: left of or above
+    // the rectangle)
+    const int dx = 2 * cx - o.x0, dy = 2 * cy - o.y0;
+    const uint64_t mask = (uint64_t)mhi << 32 | mlo;
+    const uint32_t cols = (dx >= 0 ? 1u : 0u) | (dx + 1 < o.rw ? 2u : 0u);
+    uint32_t tiles = 0;
+#pragma unroll
+    for (int row = 0; row < 2; ++row) {
+      const int y = dy + row, p = y * o.rw + dx;
+      // (p = -1 only in row 0 of the rectangle, one column left of it)
+      const uint32_t two = p >= 0 ? (uint32_t)(mask >> (p & 63)) & 3u : ((uint32_t)mask & 1u) << 1;
+      if (y >= 0 && y < o.rh) tiles |= (two & cols) << (2 * row);
+    }
+    if (base + lane >= total) tiles = 0;
+    const int n = __popc(tiles), run = HITS ? wave_scan(n) : 0;
+    if (tiles) entry(cy * cells_x + cx, tiles, own, (uint32_t)(done + run - n - ohb), od, oe);
+    if (HITS) done += __builtin_amdgcn_readlane(run, 63);
+  }
+  const uint64_t larges = __ballot(large);
+  if (!larges) return;
+  float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f);
+  float C = 0.f, thr = 0.f;
+  if (large) {
+    r0 = rp[0];
+    C = rp[1].x;
+    thr = rp[2].w;
+  }
+  for (uint64_t todo = larges; todo; todo &= todo - 1) {
+    const int src = __ffsll((long long)todo) - 1;
+    const float mx = __shfl(r0.x, src), my = __shfl(r0.y, src), A = __shfl(r0.z, src), B = __shfl(r0.w, src);
+    const float Cs = __shfl(C, src), ts = __shfl(thr, src);
+    const int x0 = __shfl(r.x0, src), y0 = __shfl(r.y0, src), rw = __shfl(r.rw, src), rh = __shfl(r.rh, src);
+    const int cw = __shfl(ncw, src), cells = cw * __shfl(nch, src);
+    const uint32_t od = __shfl(d, src), oe = __shfl(e, src);
+    uint32_t seen = 0;
+    for (int c0 = 0; c0 < cells; c0 += 16) {
+      const int c = c0 + (lane >> 2);
+      const int cy = (y0 >> 1) + c / cw, cx = (x0 >> 1) + c % cw;
+      const int tx = 2 * cx + (lane & 1), ty = 2 * cy + ((lane >> 1) & 1);
+      const bool h = c < cells && tx >= x0 && tx < x0 + rw && ty >= y0 && ty < y0 + rh &&
+                     key_tile_hit(mx, my, A, B, Cs, ts, tx, ty);
+      const uint64_t m = __ballot(h);
+      const uint32_t tiles = (uint32_t)(m >> (lane & 60)) & 15u;
+      if ((lane & 3) == 0 && tiles)
+        entry(cy * cells_x + cx, tiles, src, seen + (uint32_t)__popcll(m & ((1ull << lane) - 1ull)), od, oe);
+      seen += (uint32_t)__popcll(m);
+    }
+  }
+}
+
+// Each block's row of both matrices.
+__global__ void __launch_bounds__(kTlThreads)
+k_cell_count(const float4* __restrict__ rec, const uint4* __restrict__ pairs, int32_t N, ViewsArg va, CellBase cb,
+             TlSpace ws) {
+  extern __shared__ uint64_t s_cells[];
+  __shared__ uint8_t s_own[kTlThreads];
+  int g, G;
+  const int v = view_of_block(cb, va.n, g, G);
+  const ViewDev& V = va.v[v];
+  const int nc = view_cells(V), cells_x = cells_of(V.tiles_x);
+  uint64_t* s_hits = s_cells;                       // [nc] four 16-bit counts
+  uint32_t* s_entries = (uint32_t*)(s_cells + nc);  // [nc]
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const size_t vb = (size_t)v * N;
+  const int p0 = (int)((int64_t)g * N / G), p1 = (int)((int64_t)(g + 1) * N / G);
+  const uint4 none = make_uint4(0u, 0u, 0u, 0u);
+  int k = p0 + wid * 64 + lane;
+  uint4 next = k < p1 ? pairs[vb + k] : none;
+  for (int c = (int)threadIdx.x; c < nc; c += kTlThreads) {
+    s_hits[c] = 0ull;
+    s_entries[c] = 0u;
+  }
+  __syncthreads();
+  for (int b = p0 + wid * 64; b < p1; b += kTlThreads) {
+    const uint4 q = next;
+    const float4* rp = rec + (vb + k) * 4;
+    k += kTlThreads;
+    next = k < p1 ? pairs[vb + k] : none;
+    for_each_cell<false>(q, rp, 0u, 0u, cells_x, s_own + wid * 64,
+                  [&](int c, uint32_t tiles, int, uint32_t, uint32_t, uint32_t) {
+                    atomicAdd(&s_entries[c], 1u);
+                    // bit b of the tiles to bit 16 b
+                    const uint32_t lo = (tiles & 1u) | (tiles & 2u) << 15, hi = ((tiles >> 2) & 1u) | (tiles & 8u) << 13;
+                    atomicAdd((unsigned long long*)&s_hits[c], (unsigned long long)hi << 32 | lo);
+                  });
+  }
+  __syncthreads();
+  const size_t row = (size_t)cb.matrix[v] + (size_t)g * nc;
+  for (int c = (int)threadIdx.x; c < nc; c += kTlThreads) {
+    ws.hits[row + c] = s_hits[c];
+    ws.entries[row + c] = s_entries[c];
+  }
+}
+
+__device__ __forceinline__ int view_of_cell(const CellBase& cb, int n_views, int cell) {
+  int v = 0;
+  for (int k = 1; k < n_views; ++k)
+    if (cell >= cb.cell[k]) v = k;
+  return v;
+}
+
+// Column prefix of the entries, totals of both: 16 cells per block, 64 lanes of it share a
+// cell's rows, eight rows' loads in flight together.
+constexpr int kTlSegs = 64, kTlCols = 16;
+__global__ void __launch_bounds__(kTlSegs * kTlCols)
+k_cell_colscan(ViewsArg va, CellBase cb, int n_cells, TlSpace ws) {
+  __shared__ uint32_t s_sum[5][kTlSegs][kTlCols];
+  const int lane = threadIdx.x % kTlCols, seg = threadIdx.x / kTlCols;
+  const int cell = (int)blockIdx.x * kTlCols + lane;
+  const bool ok = cell < n_cells;
+  const int v = ok ? view_of_cell(cb, va.n, cell) : 0;
+  const ViewDev& V = va.v[v];
+  const int nc = view_cells(V), lc = ok ? cell - cb.cell[v] : 0;
+  const int G = cb.block[v + 1] - cb.block[v];
+  const size_t col = (size_t)cb.matrix[v] + lc;
+  const int r0 = seg * G / kTlSegs, r1 = ok ? (seg + 1) * G / kTlSegs : r0;
+  uint32_t sum = 0, h[4] = {0u, 0u, 0u, 0u};
+  for (int r = r0; r < r1; r += 8) {
+    uint32_t x[8];
+    uint64_t y[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      x[k] = r + k < r1 ? ws.entries[col + (size_t)(r + k) * nc] : 0u;
+      y[k] = r + k < r1 ? ws.hits[col + (size_t)(r + k) * nc] : 0ull;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      sum += x[k];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) h[b] += (uint32_t)(y[k] >> (16 * b)) & 0xffffu;
+    }
+  }
+  s_sum[4][seg][lane] = sum;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) s_sum[b][seg][lane] = h[b];
+  __syncthreads();
+  if (!ok) return;
+  uint32_t run = 0;
+  for (int k = 0; k < seg; ++k) run += s_sum[4][k][lane];
+  if (seg == kTlSegs - 1) ws.start[cell] = run + sum;
+  for (int r = r0; r < r1; r += 8) {
+    uint32_t x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = r + k < r1 ? ws.entries[col + (size_t)(r + k) * nc] : 0u;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (r + k < r1) ws.entries[col + (size_t)(r + k) * nc] = run;
+      run += x[k];
+    }
+  }
+  if (seg < 4) {
+    const int cx = cells_of(V.tiles_x), tx = 2 * (lc % cx) + (seg & 1), ty = 2 * (lc / cx) + (seg >> 1);
+    if (tx < V.tiles_x && ty < V.tiles_y) {
+      uint32_t t = 0;
+      for (int k = 0; k < kTlSegs; ++k) t += s_sum[seg][k][lane];
+      ws.totals[V.tile_base + ty * V.tiles_x + tx] = t;
+    }
+  }
+}
+
+// Inclusive scan over a block of NT lanes, on top of `carry` (which moves past the block).
+template <int NT>
+__device__ __forceinline__ uint32_t block_scan(uint32_t x, uint32_t* s_warp, uint32_t& carry) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const uint32_t incl = (uint32_t)wave_scan((int)x);
+  __syncthreads();
+  if (lane == 63) s_warp[wid] = incl;
+  __syncthreads();
+  uint32_t r = carry + incl;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) {
+    const uint32_t s = s_warp[w];
+    if (w < wid) r += s;
+    carry += s;
+  }
+  return r;
+}
+
+// Cells are ordered by blocks of two sizes: up to 4096 and 16384 entries (four and one of them
+// fit a CU's LDS). Larger cells are ordered in chunks of at most the larger size. The chunks
+// after a cell's first are work items of their own, up to kSortExtra of them (a cell whose
+// chunks do not fit is left to its first block).
+template <bool LARGE>
+struct SortShape {
+  static constexpr int lo = 0, cap = 4096, threads = 512;
+};
+template <>
+struct SortShape<true> {
+  static constexpr int lo = 4096, cap = 16384, threads = 1024;
+};
+constexpr int kSortMost = SortShape<true>::cap;
+__device__ __forceinline__ int sort_chunks(uint32_t n) { return (int)((n + kSortMost - 1) / kSortMost); }
+
+// One block: exclusive scans of the tiles' hits to ranges (zero for empty tiles) and the
+// instance count, and of the cells' entries to their starts. With more than `cap` instances
+// the render is dropped (empty ranges and cells, overflow[0] |= 1). overflow[2] keeps the
+// largest need. Also the chunks of the largest cells.
+constexpr int kTlOffThreads = 1024;
+constexpr int kTlOffPer = 8;
+__global__ void __launch_bounds__(kTlOffThreads)
+k_cell_offsets(int32_t n_tiles, int32_t n_cells, int64_t cap, uint2* __restrict__ ranges, uint32_t* __restrict__ n_inst,
+               uint32_t* __restrict__ overflow, uint32_t* __restrict__ split_counts, TlSpace ws) {
+  __shared__ uint32_t s_warp[kTlOffThreads / 64];
+  __shared__ uint32_t s_extra;
+  if (threadIdx.x == 0) s_extra = 0u;
+  uint32_t total = 0;
+  for (int b = 0; b < n_tiles; b += kTlOffThreads * kTlOffPer) {
+    const int t0 = b + (int)threadIdx.x * kTlOffPer;
+    uint32_t x[kTlOffPer], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kTlOffPer; ++k) {
+      x[k] = t0 + k < n_tiles ? ws.totals[t0 + k] : 0u;
+      sum += x[k];
+    }
+    uint32_t run = block_scan<kTlOffThreads>(sum, s_warp, total) - sum;
+#pragma unroll
+    for (int k = 0; k < kTlOffPer; ++k) {
+      if (t0 + k < n_tiles) ranges[t0 + k] = x[k] ? make_uint2(run, run + x[k]) : make_uint2(0u, 0u);
+      run += x[k];
+    }
+  }
+  const bool dropped = (int64_t)total > cap;
+  if (threadIdx.x == 0) {
+    n_inst[0] = total;
+    if (dropped) atomicOr(overflow, 1u);
+    atomicMax(overflow + 2, total);
+  }
+  uint32_t carry = 0;
+  for (int b = 0; b < n_cells; b += kTlOffThreads * kTlOffPer) {
+    const int t0 = b + (int)threadIdx.x * kTlOffPer;
+    uint32_t x[kTlOffPer], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kTlOffPer; ++k) {
+      x[k] = t0 + k < n_cells && !dropped ? ws.start[t0 + k] : 0u;
+      sum += x[k];
+    }
+    uint32_t run = block_scan<kTlOffThreads>(sum, s_warp, carry) - sum;
+#pragma unroll
+    for (int k = 0; k < kTlOffPer; ++k) {
+      const int c = t0 + k;
+      if (c < n_cells) ws.start[c] = run;
+      run += x[k];
+      if (x[k] <= (uint32_t)kSortMost) continue;
+      const uint32_t more = (uint32_t)sort_chunks(x[k]) - 1u;
+      const uint32_t e0 = atomicAdd(&s_extra, more);
+      const bool fits = e0 + more <= (uint32_t)kSortExtra;
+      ws.alone[c] = fits ? 0u : kAlone;
+      // (items reserved but not used are marked empty)
+      for (uint32_t i = 0; i < more && e0 + i < (uint32_t)kSortExtra; ++i)
+        ws.extra[e0 + i] = fits ? make_uint2((uint32_t)c, i + 1u) : make_uint2(kNoSlot, 0u);
+    }
+  }
+  if (threadIdx.x == 0) ws.start[n_cells] = carry;
+  if (dropped)
+    for (int t = (int)threadIdx.x; t < n_tiles; t += kTlOffThreads) ranges[t] = make_uint2(0u, 0u);
+  __syncthreads();
+  if (threadIdx.x == 0) ws.count[0] = min(s_extra, (uint32_t)kSortExtra);
+  if (threadIdx.x < 2 && split_counts) split_counts[threadIdx.x] = 0u;  // (k_cell_sort takes the long lists)
+}
+
+// DET: the entry carries, instead of the Gaussian, the emission index of its first hit (the
+// pair's first one plus the pair's hits in earlier cells), which grows with the Gaussian, and
+// emit_g tells the Gaussian of it.
+template <bool DET>
+__global__ void __launch_bounds__(kTlThreads)
+k_cell_place(const float4* __restrict__ rec, const uint4* __restrict__ pairs, const uint32_t* __restrict__ dkey,
+             const uint32_t* __restrict__ inst_off, int32_t N, ViewsArg va, CellBase cb, TlSpace ws,
+             uint64_t* __restrict__ entries, uint32_t* __restrict__ emit_g) {
+  extern __shared__ uint32_t s_pos[];
+  __shared__ uint8_t s_own[kTlThreads];
+  if (render_dropped(va)) return;
+  int g, G;
+  const int v = view_of_block(cb, va.n, g, G);
+  const ViewDev& V = va.v[v];
+  const int nc = view_cells(V), cells_x = cells_of(V.tiles_x);
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const size_t vb = (size_t)v * N;
+  const int p0 = (int)((int64_t)g * N / G), p1 = (int)((int64_t)(g + 1) * N / G);
+  int k = p0 + wid * 64 + lane;
+  uint4 nq;
+  uint32_t nd, ne;
+  auto fetch = [&]() {
+    nq = make_uint4(0u, 0u, 0u, 0u);
+    nd = ne = 0u;
+    if (k < p1) {
+      nq = pairs[vb + k];
+      nd = dkey[vb + k];
+      if (DET) ne = inst_off[vb + k];
+    }
+  };
+  fetch();
+  const uint32_t* row = ws.entries + cb.matrix[v] + (size_t)g * nc;
+  for (int c = (int)threadIdx.x; c < nc; c += kTlThreads) s_pos[c] = row[c] + ws.start[cb.cell[v] + c];
+  __syncthreads();
+  for (int b = p0 + wid * 64; b < p1; b += kTlThreads) {
+    const uint4 q = nq;
+    const uint32_t d = nd, e0 = ne;
+    const float4* rp = rec + (vb + k) * 4;
+    k += kTlThreads;
+    fetch();
+    for_each_cell<DET>(q, rp, d, e0, cells_x, s_own + wid * 64,
+                  [&](int c, uint32_t tiles, int own, uint32_t idx, uint32_t od, uint32_t oe) {
+                    const uint32_t slot = atomicAdd(&s_pos[c], 1u);
+                    uint32_t id = (uint32_t)(b + own);
+                    if (DET) {
+                      emit_g[oe + idx] = id;
+                      id = oe + idx;
+                    }
+                    entries[slot] = (uint64_t)od << 32 | (id << kTlMaskBits) | tiles;
+                  });
+  }
+}
+
+// Orders n <= CAP entries of LDS: a bitonic network in the form whose comparators all point
+// the same way, so that entries past n count as larger than all others and are never touched.
+template <int NT>
+__device__ __forceinline__ void bitonic_sort(uint64_t* s, int n) {
+  auto exchange = [&](int i, int j) {
+    if (j < n) {
+      const uint64_t a = s[i], b = s[j];
+      if (b < a) {
+        s[i] = b;
+        s[j] = a;
+      }
+    }
+  };
+  for (int k = 2; (k >> 1) < n; k <<= 1) {
+    for (int h = k >> 1; h > 0; h >>= 1) {
+      __syncthreads();
+      // comparator p: i has bit h clear; its partner mirrors it in the first step of a merge
+      for (int p = (int)threadIdx.x;; p += NT) {
+        const int i = ((p & ~(h - 1)) << 1) | (p & (h - 1));
+        if (i >= n) break;
+        exchange(i, h == (k >> 1) ? i ^ (k - 1) : i | h);
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// One cell (or chunk of one) per block, in LDS. The entries are counted into as many coarse
+// bins as lanes, which cut the range of their depth bits evenly; each coarse bin is then cut
+// evenly into as many fine bins as half its entries, so that the fine bins follow the depths'
+// distribution. Both maps are monotone, so the bins are in order. The entries are scattered
+// to their fine bins' places and ranked inside their bin by comparing with its members. (One
+// level of 2048 even bins left up to 141 entries in a bin of a street scene's cells, whose
+// depths bunch up in front of a far sky: 63 and 85 us for the two sizes where this takes 21
+// and 25.) With a bin of more than kBinMost (clusters far narrower than a coarse bin, equal
+// depths) a bitonic network orders the entries instead, whose time does not depend on the
+// values.
+constexpr int kBinMost = 256;
+// Two fine bins share a word (16 bits each: CAP < 2^16); four 4096-entry blocks fit a CU.
+template <int NT, int CAP>
+struct __align__(16) SortLds {
+  uint64_t e[CAP];
+  uint32_t coarse[NT + 1];
+  uint32_t bin[CAP / 4 + 1];
+  uint32_t warp[NT / 64];
+  uint32_t lo, hi, most;
+};
+__device__ __forceinline__ uint32_t bin_value(const uint32_t* bins, uint32_t b) {
+  return (bins[b >> 1] >> (16 * (b & 1u))) & 0xffffu;
+}
+
+// Leaves the n entries of src in order in L.e (after a barrier).
+template <int NT, int CAP>
+__device__ __forceinline__ void sort_run(SortLds<NT, CAP>& L, const uint64_t* __restrict__ src, int n) {
+  constexpr int PER = CAP / NT, WORDS = CAP / 4 / NT;
+  static_assert(CAP % (4 * NT) == 0 && CAP < 65536, "whole words of bins per lane");
+  const int tid = (int)threadIdx.x;
+  uint64_t e[PER];
+  uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int i = tid + k * NT;
+    e[k] = i < n ? src[i] : ~0ull;
+    if (i < n) {
+      lo = min(lo, (uint32_t)(e[k] >> 32));
+      hi = max(hi, (uint32_t)(e[k] >> 32));
+    }
+  }
+  if (tid == 0) {
+    L.lo = 0xffffffffu;
+    L.hi = 0u;
+    L.most = 0u;
+  }
+  L.coarse[tid] = 0u;
+#pragma unroll
+  for (int k = 0; k < WORDS; ++k) L.bin[tid + k * NT] = 0u;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
+  }
+  __syncthreads();
+  if ((tid & 63) == 0 && lo <= hi) {
+    atomicMin(&L.lo, lo);
+    atomicMax(&L.hi, hi);
+  }
+  __syncthreads();
+  lo = L.lo;
+  // every step of the map is monotone: difference, conversion, product with a constant, floor
+  const float scale = (float)NT / ((float)(L.hi - lo) + 1.0f);
+  auto coarse_of = [&](uint64_t x, float& f) {
+    f = (float)((uint32_t)(x >> 32) - lo) * scale;
+    return min((uint32_t)f, (uint32_t)(NT - 1));
+  };
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    if (k * NT >= n) break;  // (uniform)
+    float f;
+    if (tid + k * NT < n) atomicAdd(&L.coarse[coarse_of(e[k], f)], 1u);
+  }
+  __syncthreads();
+  {
+    const uint32_t c = L.coarse[tid];
+    uint32_t carry = 0;
+    const uint32_t end = block_scan<NT>(c, L.warp, carry);
+    L.coarse[tid] = end - c;
+    if (tid == 0) L.coarse[NT] = (uint32_t)n;
+  }
+  __syncthreads();
+  uint32_t at[PER];  // fine bin, and the entry's number in it << 16
+  uint32_t most = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    at[k] = 0;
+    if (k * NT >= n) break;
+    if (tid + k * NT < n) {
+      float f;
+      const uint32_t b = coarse_of(e[k], f), s = L.coarse[b], c = L.coarse[b + 1] - s;
+      const uint32_t fine = (s + min((uint32_t)((f - (float)b) * (float)c), c - 1u)) >> 1;
+      const uint32_t sh = 16 * (fine & 1u);
+      const uint32_t rank = (atomicAdd(&L.bin[fine >> 1], 1u << sh) >> sh) & 0xffffu;
+      at[k] = fine | rank << 16;
+      most = max(most, rank + 1u);
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, o, 64));
+  if ((tid & 63) == 0 && most > 0u) atomicMax(&L.most, most);
+  __syncthreads();
+  if (L.most > (uint32_t)kBinMost) {
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (tid + k * NT < n) L.e[tid + k * NT] = e[k];
+    bitonic_sort<NT>(L.e, n);
+    return;
+  }
+  {
+    // exclusive scan of the bins, a run of 2 WORDS per lane
+    uint32_t c[WORDS], sum = 0, carry = 0;
+    uint32_t* run = L.bin + tid * WORDS;
+#pragma unroll
+    for (int k = 0; k < WORDS; ++k) {
+      c[k] = run[k];
+      sum += (c[k] & 0xffffu) + (c[k] >> 16);
+    }
+    uint32_t start = block_scan<NT>(sum, L.warp, carry) - sum;
+#pragma unroll
+    for (int k = 0; k < WORDS; ++k) {
+      const uint32_t second = start + (c[k] & 0xffffu);
+      run[k] = start | second << 16;
+      start = second + (c[k] >> 16);
+    }
+    if (tid == 0) L.bin[CAP / 4] = (uint32_t)n;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    if (k * NT >= n) break;
+    if (tid + k * NT < n) L.e[bin_value(L.bin, at[k] & 0xffffu) + (at[k] >> 16)] = e[k];
+  }
+  __syncthreads();
+  // rank inside the bin, four members' loads in flight together
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    if (k * NT >= n) break;
+    if (tid + k * NT < n) {
+      const uint32_t b = at[k] & 0xffffu, b0 = bin_value(L.bin, b), b1 = bin_value(L.bin, b + 1);
+      uint32_t p = b0;
+      for (uint32_t j = b0; j < b1; j += 4) {
+        uint64_t x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = L.e[min(j + u, b1 - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) p += (j + u < b1 && x[u] < e[k]) ? 1u : 0u;
+      }
+      at[k] = p;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    if (k * NT >= n) break;
+    if (tid + k * NT < n) L.e[at[k]] = e[k];
+  }
+  __syncthreads();
+}
+
+// Position in a chunked cell of entry e, which is entry i of chunk c: the entries before it in
+// its own chunk and in every other.
+__device__ __forceinline__ uint32_t merged_position(const uint64_t* __restrict__ list, int n, int nch, int c, int i,
+                                                    uint64_t e) {
+  uint32_t pos = (uint32_t)i;
+  for (int o = 0; o < nch; ++o) {
+    if (o == c) continue;
+    int a, b;
+    chunk_range(n, nch, o, a, b);
+    const int a0 = a;
+    while (a < b) {
+      const int mid = (a + b) >> 1;
+      if (list[mid] < e) a = mid + 1;
+      else b = mid;
+    }
+    pos += (uint32_t)(a - a0);
+  }
+  return pos;
+}
+
+// Where a cell's tiles' lists go.
+struct ListOut {
+  uint32_t* list_g;
+  uint32_t* list_e;          // nullptr unless deterministic
+  const uint32_t* emit_g;
+};
+
+// Deals the n ordered entries e of a cell out to its tiles' lists: each wave takes a run of
+// 64-entry groups, counts its run's hits per tile, and after a prefix over the waves places
+// them, a group at a time, by ballots. s_cnt: [waves][4].
+template <int NT>
+__device__ __forceinline__ void deal_cell(const uint64_t* e, int n, const ViewDev& V, int lc,
+                                          const uint2* __restrict__ ranges, uint32_t (*s_cnt)[4], const ListOut& o) {
+  constexpr int NW = NT / 64;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int groups = (n + 63) >> 6, per = (groups + NW - 1) / NW;
+  const int g0 = min(wid * per, groups), g1 = min(g0 + per, groups);
+  uint32_t cnt[4] = {0u, 0u, 0u, 0u};
+  for (int g = g0; g < g1; ++g) {
+    const int i = g * 64 + lane;
+    const uint32_t tiles = i < n ? (uint32_t)e[i] & 15u : 0u;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) cnt[b] += (uint32_t)__popcll(__ballot((tiles >> b) & 1u));
+  }
+  if (lane < 4) s_cnt[wid][lane] = lane == 0 ? cnt[0] : lane == 1 ? cnt[1] : lane == 2 ? cnt[2] : cnt[3];
+  __syncthreads();
+  const int cx = cells_of(V.tiles_x), tx = 2 * (lc % cx), ty = 2 * (lc / cx);
+  uint32_t at[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const int x = tx + (b & 1), y = ty + (b >> 1);
+    at[b] = x < V.tiles_x && y < V.tiles_y ? ranges[V.tile_base + y * V.tiles_x + x].x : 0u;
+    for (int w = 0; w < wid; ++w) at[b] += s_cnt[w][b];
+  }
+  const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
+  for (int g = g0; g < g1; ++g) {
+    const int i = g * 64 + lane;
+    const uint32_t low = i < n ? (uint32_t)e[i] : 0u;
+    const uint32_t tiles = low & 15u, id = low >> kTlMaskBits;
+    const uint32_t gid = o.list_e && tiles ? o.emit_g[id] : id;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const uint64_t m = __ballot((tiles >> b) & 1u);
+      if ((tiles >> b) & 1u) {
+        const uint32_t slot = at[b] + (uint32_t)__popcll(m & below);
+        o.list_g[slot] = gid;
+        if (o.list_e) o.list_e[slot] = id + (uint32_t)__popc(tiles & ((1u << b) - 1u));
+      }
+      at[b] += (uint32_t)__popcll(m);
+    }
+  }
+}
+
+// Entries first, first + step, ... of a chunked cell to their merged positions, chunk by chunk.
+__device__ __forceinline__ void merge_cell(const uint64_t* __restrict__ list, int n, int nch, int first, int step,
+                                           uint64_t* __restrict__ merged) {
+  for (int c = 0; c < nch; ++c) {
+    int a, b;
+    chunk_range(n, nch, c, a, b);
+    for (int i = a + first; i < b; i += step) {
+      const uint64_t e = list[i];
+      merged[merged_position(list, n, nch, c, i - a, e)] = e;
+    }
+  }
+}
+
+// Block c orders cell c's entries where their number is in the size's range; with the larger
+// size the blocks past the cells take the extra chunks. The smaller size (which every cell
+// passes) also marks the cell's long tile lists (split_tile).
+template <bool LARGE>
+__global__ void __launch_bounds__(SortShape<LARGE>::threads)
+k_cell_sort(ViewsArg va, CellBase cb, int32_t n_cells, const uint2* __restrict__ ranges, uint64_t* __restrict__ entries,
+            uint64_t* __restrict__ merged, TlSpace ws, ListOut o, SplitArg sp) {
+  using S = SortShape<LARGE>;
+  constexpr int NT = S::threads;
+  __shared__ SortLds<NT, S::cap> L;
+  __shared__ uint32_t s_cnt[NT / 64][4];
+  int cell = (int)blockIdx.x, c = 0;
+  if (LARGE && cell >= n_cells) {
+    const int x = cell - n_cells;
+    if (x >= (int)ws.count[0]) return;
+    const uint2 it = ws.extra[x];
+    if (it.x == kNoSlot) return;
+    cell = (int)it.x;
+    c = (int)it.y;
+  }
+  const uint32_t start = ws.start[cell];
+  const int n = (int)(ws.start[cell + 1] - start);
+  const int v = view_of_cell(cb, va.n, cell);
+  const ViewDev& V = va.v[v];
+  if (!LARGE && sp.par > 0 && threadIdx.x < 4) {
+    const int lc = cell - cb.cell[v], cx = cells_of(V.tiles_x);
+    const int tx = 2 * (lc % cx) + ((int)threadIdx.x & 1), ty = 2 * (lc / cx) + ((int)threadIdx.x >> 1);
+    if (tx < V.tiles_x && ty < V.tiles_y) {
+      const int t = V.tile_base + ty * V.tiles_x + tx;
+      const uint2 r = ranges[t];
+      split_tile(sp, t, r.y - r.x, *sp.n_inst, va.total_tiles, sp.counts);
+    }
+  }
+  if (n <= S::lo || (!LARGE && n > S::cap)) return;
+  uint64_t* list = entries + start;
+  const int nch = LARGE ? sort_chunks((uint32_t)n) : 1;
+  if (nch == 1) {
+    sort_run(L, list, n);
+    deal_cell<NT>(L.e, n, V, cell - cb.cell[v], ranges, s_cnt, o);
+    return;
+  }
+  const bool alone = ws.alone[cell] == kAlone;
+  const int c1 = alone ? nch : c + 1;
+  for (int k = c; k < c1; ++k) {
+    int a, b;
+    chunk_range(n, nch, k, a, b);
+    sort_run(L, list + a, b - a);
+    for (int i = (int)threadIdx.x; i < b - a; i += NT) list[a + i] = L.e[i];
+    __syncthreads();
+  }
+  if (!alone) return;
+  __threadfence_block();
+  __syncthreads();
+  merge_cell(list, n, nch, (int)threadIdx.x, NT, merged + start);
+  __threadfence_block();
+  __syncthreads();
+  deal_cell<NT>(merged + start, n, V, cell - cb.cell[v], ranges, s_cnt, o);
+}
+
+// Cells ordered in chunks (none in most renders): the blocks of row y of the grid merge the
+// chunks of cells y, y + rows, ... of the extra items (each cell's first item stands for it);
+// the last of them to finish deals the cell out. The release and acquire around the arrival
+// count are what makes the merged entries visible across the XCDs' L2s, and cost nothing
+// where no cell has chunks.
+constexpr int kMergeRows = 16, kMergeThreads = 1024, kMergeCols = 16;
+__global__ void __launch_bounds__(kMergeThreads)
+k_cell_merge(ViewsArg va, CellBase cb, const uint2* __restrict__ ranges, const uint64_t* __restrict__ entries,
+             uint64_t* __restrict__ merged, TlSpace ws, ListOut o) {
+  __shared__ uint32_t s_cnt[kMergeThreads / 64][4];
+  __shared__ uint32_t s_last;
+  const uint32_t count = ws.count[0];
+  uint32_t turn = 0;
+  for (uint32_t x = 0; x < count; ++x) {
+    const uint2 it = ws.extra[x];
+    if (it.x == kNoSlot || it.y != 1u) continue;
+    if (turn++ % kMergeRows != blockIdx.y) continue;
+    const int cell = (int)it.x;
+    const uint32_t start = ws.start[cell];
+    const int n = (int)(ws.start[cell + 1] - start);
+    merge_cell(entries + start, n, sort_chunks((uint32_t)n), (int)(blockIdx.x * kMergeThreads + threadIdx.x),
+               kMergeCols * kMergeThreads, merged + start);
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(&ws.alone[cell], 1u) == (uint32_t)kMergeCols - 1u ? 1u : 0u;
+    __syncthreads();
+    if (s_last) {
+      __threadfence();
+      const int v = view_of_cell(cb, va.n, cell);
+      deal_cell<kMergeThreads>(merged + start, n, va.v[v], cell - cb.cell[v], ranges, s_cnt, o);
+    }
+    __syncthreads();  // s_cnt and s_last are reused
+  }
+}
+
+// tile id of every instance, for inspection
+__global__ void __launch_bounds__(256)
+k_list_tiles(const uint2* __restrict__ ranges, int64_t cap, uint32_t* __restrict__ tiles) {
+  const uint2 r = ranges[blockIdx.x];
+  for (int64_t i = (int64_t)r.x + threadIdx.x; i < r.y && i < cap; i += 256) tiles[i] = blockIdx.x;
+}
+
+template <typename K>
+static hipError_t allow_lds(K kernel, size_t bytes) {
+  return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
+hipError_t tile_lists_plan(const float4* rec, const uint4* pairs, int32_t N, const ViewsArg& va, void* space,
+                           int64_t cap, uint2* ranges, uint32_t* n_inst, uint32_t* overflow, uint32_t* split_counts,
+                           hipStream_t s) {
+  const int nc = (int)cells_total(va);
+  const CellBase cb = cell_base(va, N);
+  const TlSpace ws = tl_space(space, va, cb);
+  const dim3 grid((unsigned)cb.block[va.n]);
+  const size_t lds = (size_t)max_cells(va) * 12;
+  hipError_t e = allow_lds(k_cell_count, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_cell_count, grid, dim3(kTlThreads), lds, s, rec, pairs, N, va, cb,
+                     ws);
+  hipLaunchKernelGGL(k_cell_colscan, dim3((unsigned)((nc + kTlCols - 1) / kTlCols)), dim3(kTlSegs * kTlCols), 0, s, va, cb,
+                     nc, ws);
+  hipLaunchKernelGGL(k_cell_offsets, dim3(1), dim3(kTlOffThreads), 0, s, va.total_tiles, nc, cap, ranges, n_inst,
+                     overflow, split_counts, ws);
+  return hipGetLastError();
+}
+
+hipError_t tile_lists_build(const float4* rec, const uint4* pairs, const uint32_t* dkey, const uint32_t* inst_off,
+                            int32_t N, const ViewsArg& va, void* space, const uint2* ranges, uint64_t* entries,
+                            uint64_t* merged, uint32_t* emit_g, uint32_t* list_g, uint32_t* list_e, const SplitArg& sp, hipStream_t s) {
+  const int nc = (int)cells_total(va);
+  const CellBase cb = cell_base(va, N);
+  const TlSpace ws = tl_space(space, va, cb);
+  const dim3 grid((unsigned)cb.block[va.n]);
+  const ListOut o{list_g, list_e, emit_g};
+  const size_t lds = (size_t)max_cells(va) * 4;
+  hipError_t e = list_e ? allow_lds(k_cell_place<true>, lds) : allow_lds(k_cell_place<false>, lds);
+  if (e != hipSuccess) return e;
+  if (list_e)
+    hipLaunchKernelGGL(k_cell_place<true>, grid, dim3(kTlThreads), lds, s, rec, pairs, dkey, inst_off, N, va, cb, ws,
+                       entries, emit_g);
+  else
+    hipLaunchKernelGGL(k_cell_place<false>, grid, dim3(kTlThreads), lds, s, rec, pairs, dkey, inst_off, N, va, cb, ws,
+                       entries, emit_g);
+  // a cell holds a Gaussian once: a small map has no cells for the larger blocks
+  hipLaunchKernelGGL(k_cell_sort<false>, dim3((unsigned)nc), dim3(SortShape<false>::threads), 0, s, va, cb, nc, ranges,
+                     entries, merged, ws, o, sp);
+  if (N > SortShape<false>::cap)
+    hipLaunchKernelGGL(k_cell_sort<true>, dim3((unsigned)(nc + (N > kSortMost ? kSortExtra : 0))),
+                       dim3(SortShape<true>::threads), 0, s, va, cb, nc, ranges, entries, merged, ws, o, sp);
+  if (N > kSortMost)
+    hipLaunchKernelGGL(k_cell_merge, dim3(kMergeCols, kMergeRows), dim3(kMergeThreads), 0, s, va, cb, ranges, entries,
+                       merged, ws, o);
+  return hipGetLastError();
+}
+
+hipError_t list_tiles(const uint2* ranges, int64_t n_tiles, int64_t cap, uint32_t* tiles, hipStream_t s) {
+  if (n_tiles <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_list_tiles, dim3((unsigned)n_tiles), dim3(256), 0, s, ranges, cap, tiles);
+  return hipGetLastError();
+}
+
+}  // namespace gs

@@ -1,0 +1,109 @@
+"""Tile lists (tilelist.hip, and the radix path for images of more tiles) at the sizes where
+their branches change, against the oracle's keys, order and ranges bit for bit: cells of more
+entries than the small and the large sorting block hold (chunks and their merge), depths too
+clustered for the bins (bitonic order, ties by index), images past the counters' LDS, and the
+deterministic render's emission indices."""
+import numpy as np
+import pytest
+
+from gpu_common import exposures, gpu_map, torch_mod
+from helpers import oview
+import oracle
+from paper_2404_06926_amd import scenes
+
+pytestmark = pytest.mark.gpu
+
+
+def _check_lists(params, deg, cams, deterministic=False):
+    torch = torch_mod()
+    m = gpu_map(params, deg)
+    m.set_deterministic(deterministic)
+    m.render(cams, exposures(cams))
+    torch.cuda.synchronize()
+    dbg = m.debug_last_render()
+    views = [oview(c) for c in cams]
+    projs = [oracle.project(params, deg, v) for v in views]
+    bins = oracle.bin_views(projs, views)
+    assert dbg["n_inst"] == bins["key"].shape[0]
+    np.testing.assert_array_equal(dbg["ranges"].cpu().numpy().astype(np.int64), bins["ranges"])
+    np.testing.assert_array_equal(dbg["vals"].cpu().numpy().view(np.uint32), bins["local_val"])
+    np.testing.assert_array_equal(dbg["tiles"].cpu().numpy().view(np.uint32).astype(np.uint64),
+                                  bins["key"] >> np.uint64(32))
+    return m, bins
+
+
+def _cell_sizes(bins, cams):
+    """Entries per cell of 2x2 tiles of the first view."""
+    tx, ty = -(-cams[0].width // 16), -(-cams[0].height // 16)
+    tiles = (bins["key"] >> np.uint64(32)).astype(np.int64)
+    first = tiles < tx * ty
+    t, g = tiles[first], bins["local_val"][first].astype(np.int64)
+    cell = (t // tx // 2) * ((tx + 1) // 2) + (t % tx) // 2
+    return np.bincount(np.unique(cell << 32 | g) >> 32)
+
+
+# (Gaussians, entries the largest cell must exceed, at most): one block's small size, its
+# large size, chunks with a merge
+@pytest.mark.parametrize("n,over,most", [(300, 0, 4096), (12_000, 4096, 16384), (60_000, 16384, 1 << 30)])
+@pytest.mark.parametrize("deterministic", [False, True])
+def test_lists_of_small_large_and_chunked_cells(n, over, most, deterministic):
+    cams = [scenes.pinhole(70, 45, 50.0), scenes.pinhole(33, 31, 30.0)]
+    cams[1].t = np.array([0.1, 0.05, 0.2], np.float32)
+    params = scenes.frustum_gaussians(n, 0, cams[0], seed=n)
+    print(f"{n} Gaussians over two small views, deterministic {deterministic}", flush=True)
+    _, bins = _check_lists(params, 0, cams, deterministic)
+    largest = _cell_sizes(bins, cams).max()
+    print(f"largest cell: {largest} entries", flush=True)
+    assert over < largest <= most
+
+
+# all depths equal (order by index alone), a few distinct depths, and a tight cluster with one
+# far outlier: more entries per bin than the bins take
+@pytest.mark.parametrize("shape", ["equal", "steps", "cluster"])
+@pytest.mark.parametrize("n", [700, 5000, 40_000])
+def test_lists_of_clustered_depths(shape, n):
+    cam = scenes.pinhole(48, 40, 40.0)
+    params = scenes.frustum_gaussians(n, 0, cam, seed=3 * n)
+    r = np.random.default_rng(n)
+    z = {"equal": np.full(n, 5.0), "steps": 5.0 + 0.25 * r.integers(0, 3, n),
+         "cluster": 5.0 + 1e-6 * r.random(n)}[shape].astype(np.float32)
+    if shape == "cluster":
+        z[n // 2] = 400.0
+    params[:, 0:2] *= (z / params[:, 2])[:, None]
+    params[:, 2] = z
+    print(f"{n} Gaussians, depths: {shape}", flush=True)
+    _check_lists(params, 0, [cam])
+
+
+# the last image whose cells fit the counters and one past it (radix path), the latter also
+# among two views and deterministic
+@pytest.mark.parametrize("width,height,views,deterministic",
+                         [(4160, 3200, 1, False), (4192, 3200, 1, False), (4192, 3200, 2, True)])
+def test_lists_of_large_images(width, height, views, deterministic):
+    cams = [scenes.pinhole(width, height, 3000.0), scenes.pinhole(90, 50, 60.0)][:views]
+    params = scenes.frustum_gaussians(3000, 0, cams[0], seed=9, log_scale_mean=-2.5)
+    print(f"{width}x{height}, {views} views, deterministic {deterministic}", flush=True)
+    _check_lists(params, 0, cams, deterministic)
+
+
+def test_deterministic_gradients_do_not_depend_on_the_lists_path():
+    """The per-instance records (emission indices) of the lists by counting and of the radix
+    path sum to the same gradients: one view alone, and beside a large image that sends the
+    batch through the radix path and gets no gradient."""
+    torch = torch_mod()
+    cam, big = scenes.pinhole(100, 75, 80.0), scenes.pinhole(4192, 3200, 3000.0)
+    params = scenes.frustum_gaussians(3000, 1, cam, seed=77, log_scale_mean=-2.0)
+    params[::50, 3:6] += 2.0  # some rectangles of more than 64 tiles in the large view
+    g = torch.randn(3, 75, 100, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    out = []
+    for cams in ([cam], [cam, big]):
+        m = gpu_map(params, 1)
+        m.set_deterministic(True)
+        m.render(cams)
+        m.render_backward([g] + [torch.zeros(3, c.height, c.width, device="cuda") for c in cams[1:]])
+        torch.cuda.synchronize()
+        out.append(m.grads().double().cpu().numpy())
+    # the sums run over the same records in another order: a few roundings of FP32 sums of at
+    # most ~50 terms, 50 x 2^-24 of the column's largest entry
+    scale = np.abs(out[0]).max(axis=1, keepdims=True)
+    assert (np.abs(out[0] - out[1]) <= 3e-6 * scale + 3e-6 * np.abs(out[0])).all()
