@@ -18,8 +18,9 @@
 // The forward saves per pixel the final transmittance and the list position after the
 // last contributor; the backward starts from them (no forward replay), walks the list
 // from that position down to 0, recovers T_i = T_{i+1} / (1 - alpha_i), keeps the colour
-// seen behind the current Gaussian, and reduces each Gaussian's nine gradient terms over
-// the 64 lanes of a wave with DPP row operations before one atomic add per wave and field.
+// seen behind the current Gaussian, and sums each Gaussian's nine gradient terms over the
+// pixels: with one pixel per lane four entries at a time (kRowEntries), else over the 64
+// lanes of a wave with DPP row operations.
 //
 // Long lists. A workgroup walks its tile's list serially per pixel, so a tile whose list
 // is much longer than the others (the horizon of a street scene gathers thousands of
@@ -177,6 +178,27 @@ __device__ __forceinline__ int term_of_lane(int lane) {
   return (((lane >> 2) & 1) << 2) | (((lane >> 3) & 1) << 1) | (lane & 1);
 }
 
+// Per-Gaussian sums of the backward, four list entries at a time (one pixel per lane). An
+// entry's gradient sums over a wave's 64 pixels are formed from two values per pixel, w =
+// alpha T and g = dL/dpower. The lanes leave these in LDS, a row of 64 floats each, and when
+// four entries are collected the wave turns: lane l takes entry l / 16 at the four pixels 4 (l
+// mod 16) .. + 3, which lie side by side in a row of the quadrant, forms the partial sums of
+// all terms over them, and the 16 lanes of an entry add up. The pixels' dL/d(colour) stay in
+// the lane's registers for the whole tile; the position moments need only the sums of g, i g
+// and i^2 g over the four pixels i = 0 .. 3 and the offsets of the first from the mean. Per
+// entry this takes 15 VALU instructions where products and a reduction of every entry by
+// itself take 34.
+//
+// The backward is bound by its waves' instruction issue and latency: with these sums, the
+// entries' masks in scalar registers and batches of 128 entries (64 in the deterministic
+// form, whose partial sums take more LDS) at eight waves per SIMD it went from 9.4e7 to
+// 6.6e7 VALU instructions and from 176 to 151 us per launch at 1M Gaussians and 1280x720,
+// from 1058 to 878 us for eight views, 85 to 69 us with the maps' gradients (160k, 641x511).
+// Tried and slower: the same sums as matrix products (eight entries' w and g as the rows of
+// FP32 16x16x4 MFMAs against the pixels' factors), 202 us: the products did not overlap with
+// the other waves' VALU work, and their factors and rows halved the waves in flight.
+constexpr int kRowEntries = 4;
+
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) x = max(x, (uint32_t)__shfl_xor((int)x, o, 64));
@@ -213,40 +235,28 @@ __device__ __forceinline__ uint32_t wave_quadrants(int w) {
   return PX == 1 ? (1u << w) : (PX == 2 ? ((1u << w) | (1u << (w + 2))) : 0xFu);
 }
 
-// Per-wave lists of the staged batch: the entries t < cnt whose quadrant mask meets wave
-// w's quadrants, in batch (depth) order, in s_list[w][0 .. s_len[w]). A wave then walks
-// only the entries that can reach its pixels: with pixel-sized footprints (long lists of
-// small Gaussians) most entries meet one quadrant. Called by every thread of the block.
-template <int PX, int NW, int NT>
-__device__ __forceinline__ void build_wave_lists(uint32_t m_own, int cnt, uint8_t (*s_list)[NT], int* s_len,
-                                                 uint32_t (*s_wc)[NW]) {
+// Which entries of the staged batch can reach each wave's pixels: bit t mod 64 of
+// s_mask[w][t / 64] for entry t, from its quadrant mask m (zero past the batch's end; lanes t
+// < 64 SEGS hold one entry each). A wave then walks only its set bits: with pixel-sized
+// footprints (long lists of small Gaussians) most entries meet one quadrant. The masks live in
+// scalar registers while they are walked, so finding the next entry reads no memory. Called
+// by every thread of the block, between barriers.
+template <int PX, int NW, int SEGS>
+__device__ __forceinline__ void build_wave_masks(uint32_t m, uint64_t (*s_mask)[SEGS]) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int t = threadIdx.x;
-  const uint32_t m = t < cnt ? m_own : 0u;
-  const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-  bool hit[NW];
-  uint32_t rank[NW];
+  if (wid >= SEGS) return;
 #pragma unroll
   for (int w2 = 0; w2 < NW; ++w2) {
-    hit[w2] = (m & wave_quadrants<PX>(w2)) != 0u;
-    const uint64_t b = __ballot(hit[w2]);
-    rank[w2] = (uint32_t)__popcll(b & lt);
-    if (lane == 0) s_wc[w2][wid] = (uint32_t)__popcll(b);
+    const uint64_t b = __ballot((m & wave_quadrants<PX>(w2)) != 0u);
+    if (lane == 0) s_mask[w2][wid] = b;
   }
-  __syncthreads();
-#pragma unroll
-  for (int w2 = 0; w2 < NW; ++w2) {
-    uint32_t off = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const uint32_t c = s_wc[w2][w];
-      if (w < wid) off += c;
-      tot += c;
-    }
-    if (hit[w2]) s_list[w2][off + rank[w2]] = (uint8_t)t;
-    if (t == 0) s_len[w2] = (int)tot;
-  }
-  __syncthreads();
+}
+
+// A wave-uniform 64-bit value to scalar registers.
+__device__ __forceinline__ uint64_t scalar64(uint64_t x) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+  return (uint64_t)hi << 32 | lo;
 }
 
 // One pixel's outputs from its pre-exposure colour (blended colour without background),
@@ -305,9 +315,7 @@ k_blend_trans(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint
   constexpr int NT = kBlendBlock, NW = NT / 64;
   __shared__ float4 s_a[NT];  // mx, my, A, B
   __shared__ float2 s_b[NT];  // C, o
-  __shared__ uint8_t s_list[NW][NT];
-  __shared__ int s_len[NW];
-  __shared__ uint32_t s_wc[NW][NW];
+  __shared__ uint64_t s_mask[NW][NT / 64];
   if (blockIdx.x >= min(sp.counts[0], (uint32_t)sp.par)) return;
   const uint2 e = sp.extra[blockIdx.x];
   if (e.x == kNoSlot) return;
@@ -342,24 +350,29 @@ k_blend_trans(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint
       s_b[threadIdx.x] = make_float2(blend_stage_c(r1.x), r1.y);
       qm = quadrant_mask(r0, r1, r2.w, tx, ty);
     }
-    build_wave_lists<1, NW, NT>(qm, min(NT, end - base), s_list, s_len, s_wc);
+    build_wave_masks<1, NW, NT / 64>(qm, s_mask);
+    __syncthreads();
     // wave-uniform and branch-free, as the forward's loop: a pixel that does not take an
     // entry keeps its T by selection
-    const int len = __builtin_amdgcn_readfirstlane(s_len[wid]);
-    for (int jj = 0; jj < len; ++jj) {
-      const bool live = !(T < 0.0f);
-      if (!__any(live)) break;
-      const int j = __builtin_amdgcn_readfirstlane((int)s_list[wid][jj]);
-      const float4 a = s_a[j];
-      const float2 b = s_b[j];
-      float dx, dy;
-      const float power = blend_power2(a.x, a.y, a.z, a.w, b.x, pxc, pyc, dx, dy);
-      const float alpha = fminf(kAlphaMax, b.y * blend_exp2(power));
-      const bool ok = live && !(power > 0.0f) && alpha >= kAlphaMin;
-      const float Tn = T * (1.0f - alpha);
-      // below the threshold every later chunk is dead for this pixel whatever lies in
-      // front: the product so far is kept, marked done
-      T = ok ? (Tn < kTMin ? -Tn : Tn) : T;
+    bool more = true;
+#pragma unroll 1
+    for (int seg = 0; seg < NT / 64 && more; ++seg) {
+      for (uint64_t todo = scalar64(s_mask[wid][seg]); todo; todo &= todo - 1) {
+        const bool live = !(T < 0.0f);
+        more = __any(live);
+        if (!more) break;
+        const int j = 64 * seg + __builtin_ctzll(todo);
+        const float4 a = s_a[j];
+        const float2 b = s_b[j];
+        float dx, dy;
+        const float power = blend_power2(a.x, a.y, a.z, a.w, b.x, pxc, pyc, dx, dy);
+        const float alpha = fminf(kAlphaMax, b.y * blend_exp2(power));
+        const bool ok = live && !(power > 0.0f) && alpha >= kAlphaMin;
+        const float Tn = T * (1.0f - alpha);
+        // below the threshold every later chunk is dead for this pixel whatever lies in
+        // front: the product so far is kept, marked done
+        T = ok ? (Tn < kTMin ? -Tn : Tn) : T;
+      }
     }
   }
   split_field(sp, slot0 + c, 0)[ly * kTile + lx] = fabsf(T);
@@ -388,9 +401,7 @@ k_blend_fwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
   // per entry: (mx, my, A, B), (C, o, r, g), (b, camera-frame depth, quadrant mask bits, -):
   // one 48-B record, so a wave-uniform entry index addresses all of it from one register
   __shared__ float4 s_r[NT][3];
-  __shared__ uint8_t s_list[NW_OF(PX)][NT];   // per-wave entry lists of the batch
-  __shared__ int s_len[NW_OF(PX)];
-  __shared__ uint32_t s_wc[NW_OF(PX)][NW_OF(PX)];
+  __shared__ uint64_t s_mask[NW_OF(PX)][NT / 64];   // per wave: the batch's entries to walk
   BlendItem it;
   if (!blend_item(sp, ranges, it)) return;
   const int tile = it.tile;
@@ -452,48 +463,52 @@ k_blend_fwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
       s_r[threadIdx.x][1] = make_float4(blend_stage_c(r1.x), r1.y, r1.z, r1.w);
       s_r[threadIdx.x][2] = make_float4(r2.x, r2.y, __uint_as_float(qm), 0.f);
     }
-    const int cnt = min(NT, it.end - base);
-    build_wave_lists<PX, NW_OF(PX), NT>(qm, cnt, s_list, s_len, s_wc);
-    // wave-uniform loop (list length and entry index scalar); a pixel that does not take an
+    build_wave_masks<PX, NW_OF(PX), NT / 64>(qm, s_mask);
+    __syncthreads();
+    // wave-uniform loop (entry index scalar); a pixel that does not take an
     // entry (done, outside the entry's quadrants, power > 0, alpha below the cut-off, or
     // stopping at it) runs the same arithmetic with weight 0, which adds exact zeros, and
     // keeps its T and last contributor by selection: no per-pixel branches
-    const int len = __builtin_amdgcn_readfirstlane(s_len[wid]);
-    for (int jj = 0; jj < len; ++jj) {
-      // one comparison per pixel gives both the wave's exit test and the pixel's own
-      bool live[PX], any_live = false;
+    bool more = true;
+#pragma unroll 1
+    for (int seg = 0; seg < NT / 64 && more; ++seg) {
+      for (uint64_t todo = scalar64(s_mask[wid][seg]); todo; todo &= todo - 1) {
+        // one comparison per pixel gives both the wave's exit test and the pixel's own
+        bool live[PX], any_live = false;
 #pragma unroll
-      for (int k = 0; k < PX; ++k) {
-        live[k] = !(T[k] < 0.0f);
-        any_live = any_live || live[k];
-      }
-      if (!__any(any_live)) break;
-      const int j = __builtin_amdgcn_readfirstlane((int)s_list[wid][jj]);
-      const float4 a = s_r[j][0];
-      const float4 b = s_r[j][1];
-      const float4 cr = s_r[j][2];
-      // with one pixel per lane a wave's list holds only entries that meet its quadrant
-      const uint32_t m = PX == 1 ? 1u : __float_as_uint(cr.z);
-      const uint32_t pos1 = (uint32_t)(base + j + 1);
+        for (int k = 0; k < PX; ++k) {
+          live[k] = !(T[k] < 0.0f);
+          any_live = any_live || live[k];
+        }
+        more = __any(any_live);
+        if (!more) break;
+        const int j = 64 * seg + __builtin_ctzll(todo);
+        const float4 a = s_r[j][0];
+        const float4 b = s_r[j][1];
+        const float4 cr = s_r[j][2];
+        // with one pixel per lane a wave's list holds only entries that meet its quadrant
+        const uint32_t m = PX == 1 ? 1u : __float_as_uint(cr.z);
+        const uint32_t pos1 = (uint32_t)(base + j + 1);
 #pragma unroll
-      for (int k = 0; k < PX; ++k) {
-        float dx, dy;
-        const float power = blend_power2(a.x, a.y, a.z, a.w, b.x, pxc[k], pyc[k], dx, dy);
-        const float alpha = fminf(kAlphaMax, b.y * blend_exp2(power));
-        const bool ok = (PX == 1 || ((m >> pixel_quadrant<PX>(wid, k)) & 1u)) && live[k] &&
-                        !(power > 0.0f) && alpha >= kAlphaMin;
-        const float Tn = T[k] * (1.0f - alpha);
-        const bool below = Tn < kTMin;
-        const bool take = ok && !below;
-        const float w = take ? alpha * T[k] : 0.0f;
-        C0[k] += b.z * w;
-        C1[k] += b.w * w;
-        C2[k] += cr.x * w;
-        Dm[k] += cr.y * w;  // (kept only where the depth is wanted: one FMA, no select)
-        // taken: T after the entry; stopping here: done, T kept (as -T)
-        const float Tnext = below ? -T[k] : Tn;
-        T[k] = ok ? Tnext : T[k];
-        last[k] = take ? pos1 : last[k];
+        for (int k = 0; k < PX; ++k) {
+          float dx, dy;
+          const float power = blend_power2(a.x, a.y, a.z, a.w, b.x, pxc[k], pyc[k], dx, dy);
+          const float alpha = fminf(kAlphaMax, b.y * blend_exp2(power));
+          const bool ok = (PX == 1 || ((m >> pixel_quadrant<PX>(wid, k)) & 1u)) && live[k] &&
+                          !(power > 0.0f) && alpha >= kAlphaMin;
+          const float Tn = T[k] * (1.0f - alpha);
+          const bool below = Tn < kTMin;
+          const bool take = ok && !below;
+          const float w = take ? alpha * T[k] : 0.0f;
+          C0[k] += b.z * w;
+          C1[k] += b.w * w;
+          C2[k] += cr.x * w;
+          Dm[k] += cr.y * w;  // (kept only where the depth is wanted: one FMA, no select)
+          // taken: T after the entry; stopping here: done, T kept (as -T)
+          const float Tnext = below ? -T[k] : Tn;
+          T[k] = ok ? Tnext : T[k];
+          last[k] = take ? pos1 : last[k];
+        }
       }
     }
   }
@@ -534,31 +549,35 @@ k_blend_fwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
 // MAPS: views may carry dL/dD and dL/dO (Eq. 6-7); they add to dL/dalpha through the same
 // behind-the-Gaussian recursion with d_i and 1 in place of the colour (no background), and
 // give a tenth gradient, dL/d(camera-frame depth) = sum_px a_i T_i dL/dD.
+// Waves per SIMD: as many as the batch's LDS leaves room for with one pixel per lane (at eight,
+// 64 VGPRs, the few values that spill lie outside the entry loop; 157 us at six).
 template <int PX, bool DET, bool MAPS>
 __global__ void __launch_bounds__(kBlendBlock / PX)
+    __attribute__((amdgpu_waves_per_eu(PX == 4 ? 4 : PX == 2 ? 5 : DET ? 5 : MAPS ? 7 : 8)))
 k_blend_bwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32_t* __restrict__ list_g,
             const uint32_t* __restrict__ list_e, const uint2* __restrict__ ranges, float* __restrict__ g2d,
             float* __restrict__ inst_grad, float* __restrict__ exp_part, SplitArg sp) {
   constexpr int NT = kBlendBlock / PX;
   constexpr int NW = NT / 64;
   constexpr int NG = MAPS ? 10 : 9;  // gradient terms per Gaussian
+  constexpr bool ROWS = PX == 1;       // sums of four entries at a time
+  constexpr int NB = ROWS ? (DET ? 64 : 128) : NT;  // list entries per batch (eight bits of rows_j each)
   // per entry: (mx, my, A, B), (C, o, r, g), (b, depth, -, -): one 48-B record, so a
   // wave-uniform entry index addresses all of it from one register
-  __shared__ float4 s_r[NT][3];
-  __shared__ uint32_t s_g[NT];
-  __shared__ uint32_t s_e[DET ? NT : 1];
-  __shared__ float s_part[DET ? NW : 1][DET ? NT : 1][NG];
-  __shared__ float s_acc[DET ? 1 : NT][NG];  // batch sums (DET = false), zero between batches
-  __shared__ uint8_t s_m[NT];
-  __shared__ uint8_t s_list[NW][NT];   // per-wave entry lists of the batch
-  __shared__ int s_len[NW];
-  __shared__ uint32_t s_wc[NW][NW];
+  __shared__ float4 s_r[NB][3];
+  __shared__ uint32_t s_g[NB];
+  __shared__ uint32_t s_e[DET ? NB : 1];
+  __shared__ float s_part[DET ? NW : 1][DET ? NB : 1][NG];
+  __shared__ float s_acc[DET ? 1 : NB][NG];  // batch sums (DET = false), zero between batches
+  __shared__ uint8_t s_m[ROWS ? 1 : NB];
+  __shared__ uint64_t s_mask[NW][NB / 64];   // per wave: the batch's entries to walk
   __shared__ float s_red[NW][12];
   __shared__ uint32_t s_wmax[NW];
+  __shared__ __align__(16) float s_rows[ROWS ? NW : 1][ROWS ? 2 * kRowEntries * 64 : 4];
   BlendItem it;
   if (render_dropped(va) || !blend_item(sp, ranges, it)) return;
   if (!DET)
-    for (int k = (int)threadIdx.x; k < NT * NG; k += NT) (&s_acc[0][0])[k] = 0.0f;
+    for (int k = (int)threadIdx.x; k < NB * NG; k += NT) (&s_acc[0][0])[k] = 0.0f;
   const int tile = it.tile;
   const bool split = it.slot0 != kNoSlot;
   const uint32_t slot = it.slot0 + (uint32_t)it.c;
@@ -573,7 +592,7 @@ k_blend_bwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
   const int64_t P = (int64_t)V.W * V.H;
 
   // per pixel: transmittance (recovered backwards), last contributor, dL/d(out), dL/d(pre)
-  float pxc[PX], pyc[PX], T[PX], g0[PX], g1[PX], g2[PX], G0[PX], G1[PX], G2[PX];
+  float pxc[PX], pyc[PX], T[PX], G0[PX], G1[PX], G2[PX];
   float B0[PX], B1[PX], B2[PX];  // colour seen behind the current Gaussian, normalised
   float gD[PX], gO[PX], BD[PX], BO[PX];  // map gradients and the maps seen behind (MAPS)
   uint32_t nc[PX];
@@ -588,30 +607,30 @@ k_blend_bwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
     pyc[k] = (float)py + 0.5f;
     inside[k] = px < V.W && py < V.H;
     T[k] = 1.0f;
-    g0[k] = g1[k] = g2[k] = 0.0f;
+    float g0 = 0.0f, g1 = 0.0f, g2 = 0.0f;
     gD[k] = gO[k] = BD[k] = BO[k] = 0.0f;
     nc[k] = 0;
     if (inside[k]) {
       const int64_t p = (int64_t)py * V.W + px;
       T[k] = V.out_T[p];
       nc[k] = V.out_nc[p];
-      g0[k] = V.dl_drgb[p];
-      g1[k] = V.dl_drgb[P + p];
-      g2[k] = V.dl_drgb[2 * P + p];
+      g0 = V.dl_drgb[p];
+      g1 = V.dl_drgb[P + p];
+      g2 = V.dl_drgb[2 * P + p];
       if (MAPS) {
         if (V.dl_ddepth) gD[k] = V.dl_ddepth[p];
         if (V.dl_dopac) gO[k] = V.dl_dopac[p];
       }
     }
     // dL/d(pre-exposure colour) = A^T g
-    G0[k] = g0[k];
-    G1[k] = g1[k];
-    G2[k] = g2[k];
+    G0[k] = g0;
+    G1[k] = g1;
+    G2[k] = g2;
     if (V.exposure) {
       const float* E = V.exposure;
-      G0[k] = E[0] * g0[k] + E[4] * g1[k] + E[8] * g2[k];
-      G1[k] = E[1] * g0[k] + E[5] * g1[k] + E[9] * g2[k];
-      G2[k] = E[2] * g0[k] + E[6] * g1[k] + E[10] * g2[k];
+      G0[k] = E[0] * g0 + E[4] * g1 + E[8] * g2;
+      G1[k] = E[1] * g0 + E[5] * g1 + E[9] * g2;
+      G2[k] = E[2] * g0 + E[6] * g1 + E[10] * g2;
     }
     B0[k] = V.bg[0];
     B1[k] = V.bg[1];
@@ -639,6 +658,58 @@ k_blend_bwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
   const int term = lane == 2 ? 8 : ((MAPS && lane == 3) ? NG - 1 : term_of_lane(lane));
   const bool takes = lane < 16 && (!(lane & 2) || lane == 2 || (MAPS && lane == 3));
   float* const acc_lane = &s_acc[0][0] + term;
+  float* const rows = &s_rows[ROWS ? wid : 0][0];
+  int n_rows = 0;           // entries collected
+  uint32_t rows_j = 0;      // their batch indices, eight bits each
+  const int re = lane >> 4, rp = 4 * (lane & 15);  // this lane's entry and first pixel
+  float4 F[NG - 6];         // its pixels' dL/d(pre-exposure colour) (and dL/dD)
+  const float rx = (float)(tx * kTile + 8 * (wid & 1) + (rp & 7)) + 0.5f;
+  const float ry = (float)(ty * kTile + 8 * (wid >> 1) + (rp >> 3)) + 0.5f;
+  if (ROWS) {
+    const float v[4] = {G0[0], G1[0], G2[0], gD[0]};
+#pragma unroll
+    for (int c = 0; c < NG - 6; ++c) rows[64 * c + lane] = v[c];
+    wave_lds_sync();
+#pragma unroll
+    for (int c = 0; c < NG - 6; ++c) F[c] = *(const float4*)(rows + 64 * c + rp);
+    wave_lds_sync();  // the rows are rewritten by the entries
+  }
+  // the gradient term that lane l of each 16 holds after the sums, and whether it takes one
+  const int rl = lane & 15;
+  const int rterm = rl == 2 ? 8 : ((MAPS && rl == 3) ? NG - 1 : term_of_lane(lane));
+  const bool rtakes = !(rl & 2) || rl == 2 || (MAPS && rl == 3);
+  auto flush = [&]() {
+    wave_lds_sync();
+    const int j = (int)((rows_j >> (8 * re)) & 0xffu);
+    const float2 m = *(const float2*)&s_r[j][0];
+    const float4 w = *(const float4*)(rows + 64 * re + rp), g = *(const float4*)(rows + 64 * (kRowEntries + re) + rp);
+    const float dx = rx - m.x, dy = ry - m.y;
+    const float s = (g.x + g.y) + (g.z + g.w);                           // sum of g
+    const float si = fmaf(3.f, g.w, fmaf(2.f, g.z, g.y));                // of i g
+    const float sii = fmaf(9.f, g.w, fmaf(4.f, g.z, g.y));               // of i^2 g
+    const float sx = fmaf(dx, s, si);                                    // of (dx + i) g
+    const float sy = dy * s;
+    float v[8] = {sx, sy, fmaf(dx, sx + si, sii), dy * sx, dy * sy, s, 0.f, 0.f};
+    auto dot = [&](const float4& f) { return fmaf(w.w, f.w, fmaf(w.z, f.z, fmaf(w.y, f.y, w.x * f.x))); };
+    v[6] = dot(F[0]);
+    v[7] = dot(F[1]);
+    float val = row_sum8_transposed(v, lane);
+    const float t8 = row_sum16(dot(F[2]));
+    val = rl == 2 ? t8 : val;
+    if (MAPS) {
+      const float t9 = row_sum16(dot(F[NG - 7]));
+      val = rl == 3 ? t9 : val;
+    }
+    if (rtakes && re < n_rows) {
+      if (DET)
+        s_part[wid][DET ? j : 0][rterm] = val;
+      else if (val != 0.0f)
+        __hip_atomic_fetch_add(&s_acc[DET ? 0 : j][rterm], val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    wave_lds_sync();
+    n_rows = 0;
+    rows_j = 0;
+  };
   const uint32_t wmax = wave_max_u32(ncmax);
   if (lane == 0) s_wmax[wid] = wmax;
   __syncthreads();
@@ -646,8 +717,8 @@ k_blend_bwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
 #pragma unroll
   for (int w = 0; w < NW; ++w) nmax = max(nmax, (int)s_wmax[w]);
 
-  for (int end = min(nmax, it.end); end > it.begin; end -= NT) {
-    const int base = __builtin_amdgcn_readfirstlane(max(it.begin, end - NT));
+  for (int end = min(nmax, it.end); end > it.begin; end -= NB) {
+    const int base = __builtin_amdgcn_readfirstlane(max(it.begin, end - NB));
     const int cnt = end - base;
     __syncthreads();
     uint32_t qm = 0;
@@ -660,7 +731,7 @@ k_blend_bwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
       s_r[threadIdx.x][2] = make_float4(r2.x, r2.y, 0.f, 0.f);
       s_g[threadIdx.x] = g;
       qm = quadrant_mask(r0, r1, r2.w, tx, ty);
-      s_m[threadIdx.x] = (uint8_t)qm;
+      if (!ROWS) s_m[threadIdx.x] = (uint8_t)qm;
       if (DET) {
         s_e[threadIdx.x] = list_e[rg.x + base + threadIdx.x];
 #pragma unroll
@@ -669,96 +740,120 @@ k_blend_bwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
           for (int f = 0; f < NG; ++f) s_part[w][threadIdx.x][f] = 0.f;
       }
     }
-    build_wave_lists<PX, NW, NT>(qm, cnt, s_list, s_len, s_wc);
+    build_wave_masks<PX, NW, NB / 64>(qm, s_mask);
+    __syncthreads();
     // entries at or past the wave's max are idle (wave-uniform bounds and entry index: a
     // scalar loop)
-    const int jtop = __builtin_amdgcn_readfirstlane(min(cnt, (int)wmax - base) - 1);
-    for (int jj = __builtin_amdgcn_readfirstlane(s_len[wid]) - 1; jj >= 0; --jj) {
-      const int j = __builtin_amdgcn_readfirstlane((int)s_list[wid][jj]);
-      if (j > jtop) continue;
-      const uint32_t m = PX == 1 ? 1u : s_m[j];  // (a wave's list meets its quadrant)
-      const int pos = base + j;
-      const float4 a = s_r[j][0];
-      const float4 b = s_r[j][1];
-      const float4 cr = s_r[j][2];
-      const float c2 = cr.x;
-      const float dep = MAPS ? cr.y : 0.0f;
-      // per-lane sums of the gradient terms over the lane's pixels (the first pixel sets
-      // them: adding to 0 would cost an operation, as 0 + x differs from x for x = -0)
-      float gv[NG];
-      auto add = [&](int k, int f, float x) { gv[f] = k == 0 ? x : gv[f] + x; };
-      bool any = false;
-      // Branch-free: a pixel that does not take this entry (outside the Gaussian's quadrant
-      // mask, past its last contributor, power > 0 or alpha below the cut-off) runs the same
-      // arithmetic with alpha = 0, which leaves its T and colour behind unchanged exactly
-      // (T is selected, B + 0 (c - B) = B) and adds exact zeros to the sums.
+    const int jend = __builtin_amdgcn_readfirstlane(min(cnt, (int)wmax - base));
+#pragma unroll 1
+    for (int seg = NB / 64 - 1; seg >= 0; --seg) {
+      const int keep = jend - 64 * seg;
+      if (keep <= 0) continue;
+      uint64_t todo = scalar64(s_mask[wid][seg]);
+      if (keep < 64) todo &= (1ull << keep) - 1ull;
+      while (todo) {
+        const int bit = 63 - __builtin_clzll(todo);
+        todo &= ~(1ull << bit);
+        const int j = 64 * seg + bit;
+        const uint32_t m = PX == 1 ? 1u : s_m[j];  // (a wave's list meets its quadrant)
+        const int pos = base + j;
+        const float4 a = s_r[j][0];
+        const float4 b = s_r[j][1];
+        const float4 cr = s_r[j][2];
+        const float c2 = cr.x;
+        const float dep = MAPS ? cr.y : 0.0f;
+        // per-lane sums of the gradient terms over the lane's pixels (the first pixel sets
+        // them: adding to 0 would cost an operation, as 0 + x differs from x for x = -0)
+        float gv[NG];
+        auto add = [&](int k, int f, float x) { gv[f] = k == 0 ? x : gv[f] + x; };
+        bool any = false;
+        // Branch-free: a pixel that does not take this entry (outside the Gaussian's quadrant
+        // mask, past its last contributor, power > 0 or alpha below the cut-off) runs the same
+        // arithmetic with alpha = 0, which leaves its T and colour behind unchanged exactly
+        // (T is selected, B + 0 (c - B) = B) and adds exact zeros to the sums.
 #pragma unroll
-      for (int k = 0; k < PX; ++k) {
-        float dx, dy;
-        const float power = blend_power2(a.x, a.y, a.z, a.w, b.x, pxc[k], pyc[k], dx, dy);
-        const float ex = blend_exp2(power);
-        const float araw = b.y * ex;
-        const float alpha = fminf(kAlphaMax, araw);
-        const bool on = (PX == 1 || ((m >> pixel_quadrant<PX>(wid, k)) & 1u)) && pos < (int)nc[k] &&
-                        power <= 0.0f && alpha >= kAlphaMin;
-        any = any || on;
-        const float al = on ? alpha : 0.0f;
-        // transmittance in front of this Gaussian (al = 0 leaves it as it is: the
-        // reciprocal of 1 is exactly 1)
-        T[k] = T[k] * __builtin_amdgcn_rcpf(1.0f - al);
-        const float w = al * T[k];
-        add(k, 6, w * G0[k]);
-        add(k, 7, w * G1[k]);
-        add(k, 8, w * G2[k]);
-        // colour in front minus colour behind, per channel: dL/dalpha's factors, and the
-        // step of the colour behind to the one in front of this Gaussian,
-        // B <- alpha c + (1 - alpha) B = B + alpha (c - B)
-        const float d0 = b.z - B0[k], d1 = b.w - B1[k], d2 = c2 - B2[k];
-        // dL/dalpha = T (c - B) . G (+ the maps' terms)
-        float dot = d0 * G0[k] + d1 * G1[k] + d2 * G2[k];
-        B0[k] = fmaf(al, d0, B0[k]);
-        B1[k] = fmaf(al, d1, B1[k]);
-        B2[k] = fmaf(al, d2, B2[k]);
-        if (MAPS) {
-          const float dd = dep - BD[k], dO = 1.0f - BO[k];
-          dot += dd * gD[k] + dO * gO[k];
-          BD[k] = fmaf(al, dd, BD[k]);
-          BO[k] = fmaf(al, dO, BO[k]);
-          add(k, 9, w * gD[k]);
+        for (int k = 0; k < PX; ++k) {
+          float dx, dy;
+          const float power = blend_power2(a.x, a.y, a.z, a.w, b.x, pxc[k], pyc[k], dx, dy);
+          const float ex = blend_exp2(power);
+          const float araw = b.y * ex;
+          const float alpha = fminf(kAlphaMax, araw);
+          const bool on = (PX == 1 || ((m >> pixel_quadrant<PX>(wid, k)) & 1u)) && pos < (int)nc[k] &&
+                          power <= 0.0f && alpha >= kAlphaMin;
+          any = any || on;
+          const float al = on ? alpha : 0.0f;
+          // transmittance in front of this Gaussian (al = 0 leaves it as it is: the
+          // reciprocal of 1 is exactly 1)
+          T[k] = T[k] * __builtin_amdgcn_rcpf(1.0f - al);
+          const float w = al * T[k];
+          if (!ROWS) {
+            add(k, 6, w * G0[k]);
+            add(k, 7, w * G1[k]);
+            add(k, 8, w * G2[k]);
+          }
+          // colour in front minus colour behind, per channel: dL/dalpha's factors, and the
+          // step of the colour behind to the one in front of this Gaussian,
+          // B <- alpha c + (1 - alpha) B = B + alpha (c - B)
+          const float d0 = b.z - B0[k], d1 = b.w - B1[k], d2 = c2 - B2[k];
+          // dL/dalpha = T (c - B) . G (+ the maps' terms), in one fixed order in every variant
+          float dot = __fmaf_rn(d2, G2[k], __fmaf_rn(d0, G0[k], __fmul_rn(d1, G1[k])));
+          B0[k] = fmaf(al, d0, B0[k]);
+          B1[k] = fmaf(al, d1, B1[k]);
+          B2[k] = fmaf(al, d2, B2[k]);
+          if (MAPS) {
+            const float dd = dep - BD[k], dO = 1.0f - BO[k];
+            dot = __fadd_rn(dot, __fmaf_rn(dd, gD[k], __fmul_rn(dO, gO[k])));
+            BD[k] = fmaf(al, dd, BD[k]);
+            BO[k] = fmaf(al, dO, BO[k]);
+            if (!ROWS) add(k, 9, w * gD[k]);
+          }
+          // dL/dpower = dL/dalpha * alpha = (alpha T) dot (no gradient through the clamp at
+          // kAlphaMax; selected to zero where the pixel does not take the entry, whose colour
+          // behind may not be finite there); its moments over the pixels, which the projection
+          // backward turns into the 2D mean, conic and opacity gradients
+          const float dpow = (on && araw <= kAlphaMax) ? w * dot : 0.0f;
+          if (ROWS) {
+            gv[0] = w;
+            gv[1] = dpow;
+            continue;
+          }
+          const float px_ = dpow * dx, py_ = dpow * dy;
+          add(k, 0, px_);
+          add(k, 1, py_);
+          add(k, 2, px_ * dx);
+          add(k, 3, px_ * dy);
+          add(k, 4, py_ * dy);
+          add(k, 5, dpow);
         }
-        // dL/dpower = dL/dalpha * alpha = (alpha T) dot (no gradient through the clamp at
-        // kAlphaMax; selected to zero where the pixel does not take the entry, whose colour
-        // behind may not be finite there); its moments over the pixels, which the projection
-        // backward turns into the 2D mean, conic and opacity gradients
-        const float dpow = (on && araw <= kAlphaMax) ? w * dot : 0.0f;
-        const float px_ = dpow * dx, py_ = dpow * dy;
-        add(k, 0, px_);
-        add(k, 1, py_);
-        add(k, 2, px_ * dx);
-        add(k, 3, px_ * dy);
-        add(k, 4, py_ * dy);
-        add(k, 5, dpow);
-      }
-      if (!__any(any)) continue;
-      // wave totals: terms 0..7 transposed within each row of 16 lanes, which leaves lanes
-      // 2 and 3 of a row as repeats; they take the row sums of terms 8 (and 9), then the
-      // rows are added. Lane L < 16 ends with the total of term `term` (see above), and the
-      // lanes that take one write or add it, one LDS instruction per entry.
-      float g8[8];
+        if (!__any(any)) continue;
+        if (ROWS) {
+          rows[64 * n_rows + lane] = gv[0];
+          rows[64 * (kRowEntries + n_rows) + lane] = gv[1];
+          rows_j |= (uint32_t)j << (8 * n_rows);
+          if (++n_rows == kRowEntries) flush();
+          continue;
+        }
+        // wave totals: terms 0..7 transposed within each row of 16 lanes, which leaves lanes
+        // 2 and 3 of a row as repeats; they take the row sums of terms 8 (and 9), then the
+        // rows are added. Lane L < 16 ends with the total of term `term` (see above), and the
+        // lanes that take one write or add it, one LDS instruction per entry.
+        float g8[8];
 #pragma unroll
-      for (int f = 0; f < 8; ++f) g8[f] = gv[f];
-      float val = row_sum8_transposed(g8, lane);   // (the cross-lane sums run on every lane)
-      const float t8 = row_sum16(gv[8]);
-      const float t9 = MAPS ? row_sum16(gv[NG - 1]) : 0.0f;
-      val = (lane & 15) == 2 ? t8 : val;
-      if (MAPS) val = (lane & 15) == 3 ? t9 : val;
-      val = add_rows(val);
-      if (DET) {
-        if (takes) s_part[wid][j][term] = val;
-      } else if (takes && val != 0.0f) {
-        __hip_atomic_fetch_add(acc_lane + j * NG, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        for (int f = 0; f < 8; ++f) g8[f] = gv[f];
+        float val = row_sum8_transposed(g8, lane);   // (the cross-lane sums run on every lane)
+        const float t8 = row_sum16(gv[8]);
+        const float t9 = MAPS ? row_sum16(gv[NG - 1]) : 0.0f;
+        val = (lane & 15) == 2 ? t8 : val;
+        if (MAPS) val = (lane & 15) == 3 ? t9 : val;
+        val = add_rows(val);
+        if (DET) {
+          if (takes) s_part[wid][j][term] = val;
+        } else if (takes && val != 0.0f) {
+          __hip_atomic_fetch_add(acc_lane + j * NG, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
       }
     }
+    if (ROWS && n_rows > 0) flush();
     if (!DET) {
       // the batch's sums to g2d; each read slot is cleared for the next batch
       __syncthreads();
@@ -805,9 +900,12 @@ k_blend_bwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
 #pragma unroll
     for (int k = 0; k < PX; ++k) {
       if (!inside[k]) continue;
-      e[0] += g0[k] * B0[k]; e[1] += g0[k] * B1[k]; e[2] += g0[k] * B2[k]; e[3] += g0[k];
-      e[4] += g1[k] * B0[k]; e[5] += g1[k] * B1[k]; e[6] += g1[k] * B2[k]; e[7] += g1[k];
-      e[8] += g2[k] * B0[k]; e[9] += g2[k] * B1[k]; e[10] += g2[k] * B2[k]; e[11] += g2[k];
+      // (read again: three registers less through the entry loop)
+      const int64_t p = (int64_t)(int)pyc[k] * V.W + (int)pxc[k];
+      const float g0 = V.dl_drgb[p], g1 = V.dl_drgb[P + p], g2 = V.dl_drgb[2 * P + p];
+      e[0] += g0 * B0[k]; e[1] += g0 * B1[k]; e[2] += g0 * B2[k]; e[3] += g0;
+      e[4] += g1 * B0[k]; e[5] += g1 * B1[k]; e[6] += g1 * B2[k]; e[7] += g1;
+      e[8] += g2 * B0[k]; e[9] += g2 * B1[k]; e[10] += g2 * B2[k]; e[11] += g2;
     }
 #pragma unroll
     for (int f = 0; f < 12; ++f) e[f] = wave_sum_to_63(e[f]);
