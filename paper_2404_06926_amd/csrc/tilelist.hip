@@ -113,6 +113,16 @@ __device__ __forceinline__ int view_of_block(const CellBase& cb, int n_views, in
   return v;
 }
 
+// Pair i of block g of G (from its first on, i < block_pairs): runs of kTlRun pairs go round
+// the blocks, so that Gaussians that lie side by side in the map (a depth image's, a street's
+// near ones with hundreds of cells each) spread over all of them.
+constexpr int kTlRun = 16;
+__device__ __forceinline__ int pair_of(int i, int g, int G) { return ((i / kTlRun) * G + g) * kTlRun + i % kTlRun; }
+__device__ __forceinline__ int block_pairs(int N, int g, int G) {
+  const int runs = (N + kTlRun - 1) / kTlRun;
+  return g < runs ? ((runs - 1 - g) / G + 1) * kTlRun : 0;  // (the last may reach past N)
+}
+
 // Workspace: per cell and block the packed hits (8 B) and the entries (4 B), then per cell its
 // first entry (one more at the end), per tile its hits, and the sort's work items.
 constexpr int kSortExtra = 1024;
@@ -177,11 +187,11 @@ __device__ __forceinline__ int wave_scan(int x) {
 // The cells of the rectangles of up to 64 tiles are laid end to end over the lanes, 64 a step,
 // whatever the pairs' sizes (in index order a wave's largest pair has about ten times the
 // mean). A lane's owner is the last pair that starts at or before it: the last start mark in
-// the step, or the pair that holds the step's first cell. Larger rectangles are walked by the
-// whole wave one at a time, 16 cells a step, with the tile predicate evaluated again.
+// the step, or the pair that holds the step's first cell. Larger rectangles are left to
+// for_each_large_cell: the lanes that hold one are returned.
 template <bool HITS, typename F>
-__device__ __forceinline__ void for_each_cell(uint4 q, const float4* __restrict__ rp, uint32_t d, uint32_t e,
-                                              int cells_x, uint8_t* own_row, F entry) {
+__device__ __forceinline__ uint64_t for_each_cell(uint4 q, uint32_t d, uint32_t e, int cells_x, uint8_t* own_row,
+                                                  F entry) {
   const int lane = threadIdx.x & 63;
   const uint64_t upto = ~0ull >> (63 - lane);
   const PairRect r = pair_rect(q.x, q.y);
@@ -232,36 +242,57 @@ __device__ __forceinline__ void for_each_cell(uint4 q, const float4* __restrict_
     if (tiles) entry(cy * cells_x + cx, tiles, own, (uint32_t)(done + run - n - ohb), od, oe);
     if (HITS) done += __builtin_amdgcn_readlane(run, 63);
   }
-  const uint64_t larges = __ballot(large);
-  if (!larges) return;
-  float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f);
-  float C = 0.f, thr = 0.f;
-  if (large) {
-    r0 = rp[0];
-    C = rp[1].x;
-    thr = rp[2].w;
+  return __ballot(large);
+}
+
+// The cells of one pair with a rectangle of more than 64 tiles: the tile predicate is
+// evaluated again, 16 cells a step, of which this wave takes steps s0, s0 + ds, ... (HITS: all
+// of them). q, rp: the pair's word and record (the same in every lane); entry as above,
+// without the lane.
+template <bool HITS, typename F>
+__device__ __forceinline__ void for_each_large_cell(uint4 q, const float4* __restrict__ rp, int cells_x, int s0, int ds,
+                                                    F entry) {
+  const int lane = threadIdx.x & 63;
+  const PairRect r = pair_rect(q.x, q.y);
+  const float4 r0 = rp[0];
+  const float C = rp[1].x, thr = rp[2].w;
+  const int cx0 = r.x0 >> 1, cy0 = r.y0 >> 1;
+  const int cw = ((r.x0 + r.rw - 1) >> 1) - cx0 + 1, cells = cw * (((r.y0 + r.rh - 1) >> 1) - cy0 + 1);
+  uint32_t seen = 0;
+  for (int c0 = 16 * s0; c0 < cells; c0 += 16 * ds) {
+    const int c = c0 + (lane >> 2);
+    const int cy = cy0 + c / cw, cx = cx0 + c % cw;
+    const int tx = 2 * cx + (lane & 1), ty = 2 * cy + ((lane >> 1) & 1);
+    const bool h = c < cells && tx >= r.x0 && tx < r.x0 + r.rw && ty >= r.y0 && ty < r.y0 + r.rh &&
+                   key_tile_hit(r0.x, r0.y, r0.z, r0.w, C, thr, tx, ty);
+    const uint64_t m = __ballot(h);
+    const uint32_t tiles = (uint32_t)(m >> (lane & 60)) & 15u;
+    if ((lane & 3) == 0 && tiles)
+      entry(cy * cells_x + cx, tiles, HITS ? seen + (uint32_t)__popcll(m & ((1ull << lane) - 1ull)) : 0u);
+    if (HITS) seen += (uint32_t)__popcll(m);
   }
-  for (uint64_t todo = larges; todo; todo &= todo - 1) {
-    const int src = __ffsll((long long)todo) - 1;
-    const float mx = __shfl(r0.x, src), my = __shfl(r0.y, src), A = __shfl(r0.z, src), B = __shfl(r0.w, src);
-    const float Cs = __shfl(C, src), ts = __shfl(thr, src);
-    const int x0 = __shfl(r.x0, src), y0 = __shfl(r.y0, src), rw = __shfl(r.rw, src), rh = __shfl(r.rh, src);
-    const int cw = __shfl(ncw, src), cells = cw * __shfl(nch, src);
-    const uint32_t od = __shfl(d, src), oe = __shfl(e, src);
-    uint32_t seen = 0;
-    for (int c0 = 0; c0 < cells; c0 += 16) {
-      const int c = c0 + (lane >> 2);
-      const int cy = (y0 >> 1) + c / cw, cx = (x0 >> 1) + c % cw;
-      const int tx = 2 * cx + (lane & 1), ty = 2 * cy + ((lane >> 1) & 1);
-      const bool h = c < cells && tx >= x0 && tx < x0 + rw && ty >= y0 && ty < y0 + rh &&
-                     key_tile_hit(mx, my, A, B, Cs, ts, tx, ty);
-      const uint64_t m = __ballot(h);
-      const uint32_t tiles = (uint32_t)(m >> (lane & 60)) & 15u;
-      if ((lane & 3) == 0 && tiles)
-        entry(cy * cells_x + cx, tiles, src, seen + (uint32_t)__popcll(m & ((1ull << lane) - 1ull)), od, oe);
-      seen += (uint32_t)__popcll(m);
-    }
-  }
+}
+
+// The large pairs of a block, collected while its waves walk the others and shared out to all
+// of them afterwards: a map's few near Gaussians cover hundreds of cells each and lie side by
+// side in it. Where the wave that met them walked them alone and a block's pairs were a run of
+// the map, count and place took 79 and 81 us at four views of 96k Gaussians (1477 such pairs)
+// at 1575x1033 and 41 and 38 at 520k Gaussians of a street at 1280x720; now 19 and 19, 12 and
+// 12. Both are needed: sharing alone left 86 and 89.
+constexpr int kLargeMost = 128;
+struct LargeList {
+  uint32_t n;
+  uint16_t pair[kLargeMost];  // their numbers in the block
+};
+// Puts the lanes' pairs of `larges` on the list; returns those that no longer fit.
+__device__ __forceinline__ uint64_t keep_large(LargeList& L, uint64_t larges, int pair) {
+  const int lane = threadIdx.x & 63;
+  uint32_t at = 0;
+  if (lane == 0) at = atomicAdd(&L.n, (uint32_t)__popcll(larges));
+  at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(larges & ((1ull << lane) - 1ull));
+  const bool mine = (larges >> lane) & 1ull;
+  if (mine && at < (uint32_t)kLargeMost) L.pair[at] = (uint16_t)pair;
+  return __ballot(mine && at >= (uint32_t)kLargeMost);
 }
 
 // Each block's row of both matrices.
@@ -270,6 +301,7 @@ k_cell_count(const float4* __restrict__ rec, const uint4* __restrict__ pairs, in
              TlSpace ws) {
   extern __shared__ uint64_t s_cells[];
   __shared__ uint8_t s_own[kTlThreads];
+  __shared__ LargeList s_large;
   int g, G;
   const int v = view_of_block(cb, va.n, g, G);
   const ViewDev& V = va.v[v];
@@ -278,28 +310,43 @@ k_cell_count(const float4* __restrict__ rec, const uint4* __restrict__ pairs, in
   uint32_t* s_entries = (uint32_t*)(s_cells + nc);  // [nc]
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const size_t vb = (size_t)v * N;
-  const int p0 = (int)((int64_t)g * N / G), p1 = (int)((int64_t)(g + 1) * N / G);
+  const int np = block_pairs(N, g, G);
   const uint4 none = make_uint4(0u, 0u, 0u, 0u);
-  int k = p0 + wid * 64 + lane;
-  uint4 next = k < p1 ? pairs[vb + k] : none;
+  auto fetch = [&](int i) {
+    const int k = pair_of(i, g, G);
+    return i < np && k < N ? pairs[vb + k] : none;
+  };
+  uint4 next = fetch((int)threadIdx.x);
   for (int c = (int)threadIdx.x; c < nc; c += kTlThreads) {
     s_hits[c] = 0ull;
     s_entries[c] = 0u;
   }
+  if (threadIdx.x == 0) s_large.n = 0u;
   __syncthreads();
-  for (int b = p0 + wid * 64; b < p1; b += kTlThreads) {
+  auto count = [&](int c, uint32_t tiles) {
+    atomicAdd(&s_entries[c], 1u);
+    // bit b of the tiles to bit 16 b
+    const uint32_t lo = (tiles & 1u) | (tiles & 2u) << 15, hi = ((tiles >> 2) & 1u) | (tiles & 8u) << 13;
+    atomicAdd((unsigned long long*)&s_hits[c], (unsigned long long)hi << 32 | lo);
+  };
+  auto count_large = [&](int i, int s0, int ds) {
+    const int pair = pair_of(i, g, G);
+    for_each_large_cell<false>(pairs[vb + pair], rec + (vb + pair) * 4, cells_x, s0, ds,
+                               [&](int c, uint32_t tiles, uint32_t) { count(c, tiles); });
+  };
+  for (int b = wid * 64; b < np; b += kTlThreads) {
     const uint4 q = next;
-    const float4* rp = rec + (vb + k) * 4;
-    k += kTlThreads;
-    next = k < p1 ? pairs[vb + k] : none;
-    for_each_cell<false>(q, rp, 0u, 0u, cells_x, s_own + wid * 64,
-                  [&](int c, uint32_t tiles, int, uint32_t, uint32_t, uint32_t) {
-                    atomicAdd(&s_entries[c], 1u);
-                    // bit b of the tiles to bit 16 b
-                    const uint32_t lo = (tiles & 1u) | (tiles & 2u) << 15, hi = ((tiles >> 2) & 1u) | (tiles & 8u) << 13;
-                    atomicAdd((unsigned long long*)&s_hits[c], (unsigned long long)hi << 32 | lo);
-                  });
+    next = fetch(b + lane + kTlThreads);
+    uint64_t larges = for_each_cell<false>(
+        q, 0u, 0u, cells_x, s_own + wid * 64,
+        [&](int c, uint32_t tiles, int, uint32_t, uint32_t, uint32_t) { count(c, tiles); });
+    if (larges) larges = keep_large(s_large, larges, b + lane);
+    for (; larges; larges &= larges - 1) count_large(b + __ffsll((long long)larges) - 1, 0, 1);
   }
+  __syncthreads();
+  const int nl = min((int)s_large.n, kLargeMost);
+  for (int i = 0; i < nl; ++i)
+    count_large(__builtin_amdgcn_readfirstlane((int)s_large.pair[i]), wid, kTlThreads / 64);
   __syncthreads();
   const size_t row = (size_t)cb.matrix[v] + (size_t)g * nc;
   for (int c = (int)threadIdx.x; c < nc; c += kTlThreads) {
@@ -484,6 +531,7 @@ k_cell_place(const float4* __restrict__ rec, const uint4* __restrict__ pairs, co
              uint64_t* __restrict__ entries, uint32_t* __restrict__ emit_g) {
   extern __shared__ uint32_t s_pos[];
   __shared__ uint8_t s_own[kTlThreads];
+  __shared__ LargeList s_large;
   if (render_dropped(va)) return;
   int g, G;
   const int v = view_of_block(cb, va.n, g, G);
@@ -491,40 +539,55 @@ k_cell_place(const float4* __restrict__ rec, const uint4* __restrict__ pairs, co
   const int nc = view_cells(V), cells_x = cells_of(V.tiles_x);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const size_t vb = (size_t)v * N;
-  const int p0 = (int)((int64_t)g * N / G), p1 = (int)((int64_t)(g + 1) * N / G);
-  int k = p0 + wid * 64 + lane;
+  const int np = block_pairs(N, g, G);
   uint4 nq;
   uint32_t nd, ne;
-  auto fetch = [&]() {
+  auto fetch = [&](int i) {
+    const int k = pair_of(i, g, G);
     nq = make_uint4(0u, 0u, 0u, 0u);
     nd = ne = 0u;
-    if (k < p1) {
+    if (i < np && k < N) {
       nq = pairs[vb + k];
       nd = dkey[vb + k];
       if (DET) ne = inst_off[vb + k];
     }
   };
-  fetch();
+  fetch((int)threadIdx.x);
   const uint32_t* row = ws.entries + cb.matrix[v] + (size_t)g * nc;
   for (int c = (int)threadIdx.x; c < nc; c += kTlThreads) s_pos[c] = row[c] + ws.start[cb.cell[v] + c];
+  if (threadIdx.x == 0) s_large.n = 0u;
   __syncthreads();
-  for (int b = p0 + wid * 64; b < p1; b += kTlThreads) {
+  auto place = [&](int c, uint32_t tiles, uint32_t id, uint32_t idx, uint32_t od, uint32_t oe) {
+    const uint32_t slot = atomicAdd(&s_pos[c], 1u);
+    if (DET) {
+      emit_g[oe + idx] = id;
+      id = oe + idx;
+    }
+    entries[slot] = (uint64_t)od << 32 | (id << kTlMaskBits) | tiles;
+  };
+  auto place_large = [&](int i, int s0, int ds) {
+    const int pair = pair_of(i, g, G);
+    const uint32_t od = dkey[vb + pair], oe = DET ? inst_off[vb + pair] : 0u;
+    for_each_large_cell<DET>(
+        pairs[vb + pair], rec + (vb + pair) * 4, cells_x, s0, ds,
+        [&](int c, uint32_t tiles, uint32_t idx) { place(c, tiles, (uint32_t)pair, idx, od, oe); });
+  };
+  for (int b = wid * 64; b < np; b += kTlThreads) {
     const uint4 q = nq;
     const uint32_t d = nd, e0 = ne;
-    const float4* rp = rec + (vb + k) * 4;
-    k += kTlThreads;
-    fetch();
-    for_each_cell<DET>(q, rp, d, e0, cells_x, s_own + wid * 64,
-                  [&](int c, uint32_t tiles, int own, uint32_t idx, uint32_t od, uint32_t oe) {
-                    const uint32_t slot = atomicAdd(&s_pos[c], 1u);
-                    uint32_t id = (uint32_t)(b + own);
-                    if (DET) {
-                      emit_g[oe + idx] = id;
-                      id = oe + idx;
-                    }
-                    entries[slot] = (uint64_t)od << 32 | (id << kTlMaskBits) | tiles;
-                  });
+    fetch(b + lane + kTlThreads);
+    uint64_t larges = for_each_cell<DET>(q, d, e0, cells_x, s_own + wid * 64,
+                                         [&](int c, uint32_t tiles, int own, uint32_t idx, uint32_t od, uint32_t oe) {
+                                           place(c, tiles, (uint32_t)pair_of(b + own, g, G), idx, od, oe);
+                                         });
+    if (larges) larges = keep_large(s_large, larges, b + lane);
+    for (; larges; larges &= larges - 1) place_large(b + __ffsll((long long)larges) - 1, 0, 1);
   }
+  __syncthreads();
+  // (a pair's hits in earlier cells are counted by the wave that walks it: whole pairs then)
+  const int nl = min((int)s_large.n, kLargeMost);
+  for (int i = DET ? wid : 0; i < nl; i += DET ? kTlThreads / 64 : 1)
+    place_large(__builtin_amdgcn_readfirstlane((int)s_large.pair[i]), DET ? 0 : wid, DET ? 1 : kTlThreads / 64);
 }
 
 // Orders n <= CAP entries of LDS: a bitonic network in the form whose comparators all point

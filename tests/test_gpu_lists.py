@@ -86,6 +86,20 @@ def test_lists_of_large_images(width, height, views, deterministic):
     _check_lists(params, 0, cams, deterministic)
 
 
+# Gaussians whose rectangles have more than 64 tiles, walked by all waves of a block: a run of
+# them among small ones, and more in a block than its list of them holds
+@pytest.mark.parametrize("n,first,large", [(900, 100, 40), (1500, 0, 1500)])
+@pytest.mark.parametrize("deterministic", [False, True])
+def test_lists_of_runs_of_large_gaussians(n, first, large, deterministic):
+    cams = [scenes.pinhole(333, 250, 250.0), scenes.pinhole(260, 205, 180.0)]
+    params = scenes.frustum_gaussians(n, 0, cams[0], seed=n + large)
+    params[first:first + large, 3:6] = 1.0  # several metres across
+    print(f"{large} large of {n} Gaussians, deterministic {deterministic}", flush=True)
+    m, _ = _check_lists(params, 0, cams, deterministic)
+    counts = m.debug_last_render()["counts"][0].cpu().numpy()
+    assert (counts[first:first + large] > 64).sum() > 0.6 * large
+
+
 def test_deterministic_gradients_do_not_depend_on_the_lists_path():
     """The per-instance records (emission indices) of the lists by counting and of the radix
     path sum to the same gradients: one view alone, and beside a large image that sends the
