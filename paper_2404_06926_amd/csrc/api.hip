@@ -86,7 +86,7 @@ struct gs_map {
   DevBuf rec, counts, offsets, scan_tmp, g2d, keys[2], vals[2], sort_tmp, ranges, pixT, pixN, loss_tmp;
   DevBuf dkey[2], dval[2];     // depth-sort keys / (view, Gaussian) ids, double-buffered
   DevBuf list_g, list_e;       // per instance in blend order: its Gaussian; its emission index (deterministic)
-  DevBuf tl_pairs, tl_space, tl_entries, tl_merged;  // tile lists by counting (tilelist.hip)
+  DevBuf tl_pairs, tl_space, tl_entries, tl_groups;  // tile lists by counting (tilelist.hip)
   DevBuf emit_g, inst_off;     // Gaussian of each emission index; first emission index per pair
   DevBuf block_start;           // instance-parallel binning: first pair per emission block
   DevBuf split_slot, split_extra, split_state;  // long lists cut into chunks (blend)
@@ -232,7 +232,7 @@ gs_status ensure_instances(gs_map* m, int64_t nc, bool sorted, int64_t vn, hipSt
   GS_TRY(ensure(m, m->list_g, (size_t)nc * 4, s));
   if (!sorted) {
     GS_TRY(ensure(m, m->tl_entries, (size_t)nc * 8, s));
-    GS_TRY(ensure(m, m->tl_merged, (size_t)nc * 8, s));
+    GS_TRY(ensure(m, m->tl_groups, (size_t)nc * 8, s));
   }
   if (m->deterministic) {
     GS_TRY(ensure(m, m->inst_grad, (size_t)nc * 12 * 4, s));
@@ -478,7 +478,7 @@ gs_status gs_destroy_map(gs_map* m) {
   DevBuf* bufs[] = {&m->rec, &m->counts, &m->offsets, &m->scan_tmp, &m->g2d, &m->keys[0], &m->keys[1],
                     &m->vals[0], &m->vals[1], &m->sort_tmp, &m->ranges, &m->pixT, &m->pixN, &m->loss_tmp,
                     &m->dkey[0], &m->dkey[1], &m->dval[0], &m->dval[1], &m->emit_g, &m->inst_off, &m->list_g, &m->list_e,
-                    &m->tl_pairs, &m->tl_space, &m->tl_entries, &m->tl_merged,
+                    &m->tl_pairs, &m->tl_space, &m->tl_entries, &m->tl_groups,
                     &m->block_start, &m->split_slot, &m->split_extra, &m->split_state,
                     &m->inst_grad, &m->exp_part, &m->dbg_t, &m->gr_rgb, &m->gr_T, &m->gr_flags,
                     &m->gr_off, &m->gr_tmp, &m->gr_d2, &m->ar_rgb, &m->ar_T, &m->ar_nc, &m->ar_dl,
@@ -725,7 +725,7 @@ gs_status gs_render(gs_map* m, int32_t nv, const gs_view* views, const gs_frame*
     StageTimer t(m, s, GS_STAGE_DUPLICATE);
     m->last_list_e = m->deterministic ? (const uint32_t*)m->list_e.ptr : nullptr;
     GS_HIP(tile_lists_build(rec, (const uint4*)m->tl_pairs.ptr, dkey[0], inst_off, N, va, m->tl_space.ptr, ranges,
-                            (uint64_t*)m->tl_entries.ptr, (uint64_t*)m->tl_merged.ptr, (uint32_t*)m->emit_g.ptr,
+                            (uint64_t*)m->tl_entries.ptr, (uint64_t*)m->tl_groups.ptr, (uint32_t*)m->emit_g.ptr,
                             (uint32_t*)m->list_g.ptr, m->deterministic ? (uint32_t*)m->list_e.ptr : nullptr, m->last_sp, s));
   } else {
     uint32_t* keys[2] = {(uint32_t*)m->keys[0].ptr, (uint32_t*)m->keys[1].ptr};

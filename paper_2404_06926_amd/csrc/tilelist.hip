@@ -13,7 +13,7 @@
 //                   in any order within the block;
 //   k_cell_sort     one block per cell orders its entries in LDS and deals them out to its
 //                   tiles' lists by ballots (two sizes of block); cells of more than kSortMost
-//                   entries are ordered in chunks, merged and dealt out by k_cell_merge.
+//                   entries are ordered in chunks, which k_cell_merge deals out.
 // (depth, Gaussian) is unique in a cell, so the lists do not depend on the order of arrival.
 //
 // Why cells: what bounds the placement is not its bytes but the scattered writes, which L2
@@ -62,7 +62,13 @@ static int max_cells(const ViewsArg& va) {
   return c;
 }
 
+// A map of far more Gaussians than the images have room for fills few cells with many chunks
+// each, whose merge costs more than the radix path: a render of 200k over 64x48 (50000 per
+// cell) took 357 us here and 381 there, 1M (250000) 494 and 354.
+constexpr int64_t kTlMostPerCell = 65536;
+
 bool tile_lists_fit(const ViewsArg& va, int64_t N, int64_t max_instances) {
+  if (va.n * N > kTlMostPerCell * cells_total(va)) return false;
   for (int v = 0; v < va.n; ++v)
     if ((int64_t)cells_of(va.v[v].tiles_x) * cells_of(va.v[v].tiles_y) > kTlMaxCells) return false;
   return N < kTlMaxId && max_instances < kTlMaxId;
@@ -77,18 +83,20 @@ struct CellBase {
   int64_t matrix[kMaxViews];
 };
 
-// Blocks: two of 512 lanes per CU with one view, four with several, shared out by the views'
-// cells (a view's entries grow with its size) plus an even part (its pairs do not); at least
-// 256 pairs each, since a block writes and reads a matrix row whatever its share. A view's
-// count is a multiple of eight (xcd_block).
+// Blocks of 512 lanes: about 1024 pairs each (512 to 4096 blocks), since blocks of more pairs
+// end unevenly and spread their writes (3M Gaussians, 1920x1200: count and place 180 and 305 us
+// with 512 blocks, 113 and 152 with 2929; 8 x 1M at 1280x720: 137 and 300 with 1024, 109 and
+// 222 with 4096), while a block of fewer writes and reads its matrix row for little. Shared out
+// by the views' cells (a view's entries grow with its size) plus an even part (its pairs do
+// not), at least 256 pairs each. A view's count is a multiple of eight (xcd_block).
 static CellBase cell_base(const ViewsArg& va, int32_t N) {
   CellBase b{};
-  const int64_t cells = cells_total(va, b.cell), grid = va.n > 1 ? 1024 : 512;
+  const int64_t cells = cells_total(va, b.cell), grid = std::clamp<int64_t>((int64_t)va.n * N / 1024, 512, 4096);
   const int64_t fewest = ((int64_t)N + kTlMaxPairs - 1) / kTlMaxPairs, most = std::max<int64_t>(1, ((int64_t)N + 255) / 256);
   int64_t words = 0;
   for (int v = 0; v < va.n; ++v) {
     const int64_t nc = (int64_t)cells_of(va.v[v].tiles_x) * cells_of(va.v[v].tiles_y);
-    const int64_t share = va.n > 1 ? grid * (nc * va.n + cells) / (2 * cells * va.n) : grid;
+    const int64_t share = grid * (nc * va.n + cells) / (2 * cells * va.n);
     int64_t G = std::min(std::max(share, fewest), most);
     if (va.n > 1) G = (G + 7) & ~int64_t(7);
     b.block[v + 1] = b.block[v] + (int32_t)G;
@@ -123,31 +131,37 @@ __device__ __forceinline__ int block_pairs(int N, int g, int G) {
   return g < runs ? ((runs - 1 - g) / G + 1) * kTlRun : 0;  // (the last may reach past N)
 }
 
-// Workspace: per cell and block the packed hits (8 B) and the entries (4 B), then per cell its
-// first entry (one more at the end), per tile its hits, and the sort's work items.
+// Workspace: per cell and block the packed hits (8 B) and the entries (4 B); per cell its
+// entries and its first one (one more at the end), per tile its hits; and the work items of
+// the larger sorting blocks.
 constexpr int kSortExtra = 1024;
-constexpr uint32_t kAlone = 0xFFFFFFFFu;
+enum { kItems, kExtra, kChunks, kTlCounts };  // TlSpace::count
 struct TlSpace {
   uint64_t* hits;
   uint32_t* entries;
+  uint32_t* sizes;
   uint32_t* start;
   uint32_t* totals;
-  uint2* extra;      // (cell, chunk >= 1) of cells ordered in chunks
-  uint32_t* count;   // extra items
-  uint32_t* alone;   // per chunked cell: kAlone where its first block orders every chunk, else
-                     // the merging blocks that have finished
+  uint4* items;      // (cell, chunk, first entry, entries) of the cells past the small size, in any order
+  uint32_t* lists;   // per cell, where its four tiles' lists start
+  uint4* chunks;     // those of the items that are chunks of a larger cell
+  uint32_t* count;   // items; chunks after a cell's first; chunks
+  uint32_t* alone;   // per cell of several chunks: whether its first block takes all of them
 };
 int64_t tile_space_bytes(const ViewsArg& va, int32_t N) {
   const int64_t c = cells_total(va), m = matrix_words(va, cell_base(va, N));
-  return 12 * m + 4 * (2 * c + 1 + va.total_tiles) + 8 * kSortExtra + 256;
+  return 12 * m + 16 * (2 * c + 3 * kSortExtra) + 4 * (3 * c + 1 + va.total_tiles + kTlCounts) + 256;
 }
 static TlSpace tl_space(void* ws, const ViewsArg& va, const CellBase& cb) {
   const int64_t c = cells_total(va), m = matrix_words(va, cb);
   TlSpace t;
-  t.hits = (uint64_t*)ws;
-  t.extra = (uint2*)(t.hits + m);
-  t.entries = (uint32_t*)(t.extra + kSortExtra);
-  t.start = t.entries + m;
+  t.items = (uint4*)ws;
+  t.chunks = t.items + c + kSortExtra;
+  t.lists = (uint32_t*)(t.chunks + 2 * kSortExtra);
+  t.hits = (uint64_t*)(t.lists + 4 * c);
+  t.entries = (uint32_t*)(t.hits + m);
+  t.sizes = t.entries + m;
+  t.start = t.sizes + c;
   t.totals = t.start + c + 1;
   t.alone = t.totals + va.total_tiles;
   t.count = t.alone + c;
@@ -296,7 +310,7 @@ __device__ __forceinline__ uint64_t keep_large(LargeList& L, uint64_t larges, in
 }
 
 // Each block's row of both matrices.
-__global__ void __launch_bounds__(kTlThreads)
+__global__ void __launch_bounds__(kTlThreads) __attribute__((amdgpu_waves_per_eu(8)))
 k_cell_count(const float4* __restrict__ rec, const uint4* __restrict__ pairs, int32_t N, ViewsArg va, CellBase cb,
              TlSpace ws) {
   extern __shared__ uint64_t s_cells[];
@@ -370,6 +384,7 @@ k_cell_colscan(ViewsArg va, CellBase cb, int n_cells, TlSpace ws) {
   __shared__ uint32_t s_sum[5][kTlSegs][kTlCols];
   const int lane = threadIdx.x % kTlCols, seg = threadIdx.x / kTlCols;
   const int cell = (int)blockIdx.x * kTlCols + lane;
+  if (blockIdx.x == 0 && threadIdx.x < kTlCounts) ws.count[threadIdx.x] = 0u;
   const bool ok = cell < n_cells;
   const int v = ok ? view_of_cell(cb, va.n, cell) : 0;
   const ViewDev& V = va.v[v];
@@ -400,7 +415,7 @@ k_cell_colscan(ViewsArg va, CellBase cb, int n_cells, TlSpace ws) {
   if (!ok) return;
   uint32_t run = 0;
   for (int k = 0; k < seg; ++k) run += s_sum[4][k][lane];
-  if (seg == kTlSegs - 1) ws.start[cell] = run + sum;
+  if (seg == kTlSegs - 1) ws.sizes[cell] = run + sum;
   for (int r = r0; r < r1; r += 8) {
     uint32_t x[8];
 #pragma unroll
@@ -445,87 +460,112 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t x, uint32_t* s_warp, uin
 // chunks do not fit is left to its first block).
 template <bool LARGE>
 struct SortShape {
-  static constexpr int lo = 0, cap = 4096, threads = 512;
+  static constexpr int cap = 4096, threads = 512;
 };
 template <>
 struct SortShape<true> {
-  static constexpr int lo = 4096, cap = 16384, threads = 1024;
+  static constexpr int cap = 16384, threads = 1024;
 };
-constexpr int kSortMost = SortShape<true>::cap;
+constexpr int kSortSmall = SortShape<false>::cap, kSortMost = SortShape<true>::cap;
 __device__ __forceinline__ int sort_chunks(uint32_t n) { return (int)((n + kSortMost - 1) / kSortMost); }
 
-// One block: exclusive scans of the tiles' hits to ranges (zero for empty tiles) and the
-// instance count, and of the cells' entries to their starts. With more than `cap` instances
-// the render is dropped (empty ranges and cells, overflow[0] |= 1). overflow[2] keeps the
-// largest need. Also the chunks of the largest cells.
+// Exclusive scans of the tiles' hits to ranges (zero for empty tiles) and the instance count,
+// and of the cells' entries to their starts; the work items of cells past the small size.
+// With more than `cap` instances the render is dropped (empty ranges and cells, overflow[0] |=
+// 1). overflow[2] keeps the largest need. Every block sums all tiles for the total and for what
+// lies before its own kTlOffPer x 1024 tiles and cells (one block alone took 32 us for the
+// 28800 tiles of eight 1280x720 views and 7 for one; now 15 and 6, with the cells' lists).
 constexpr int kTlOffThreads = 1024;
-constexpr int kTlOffPer = 8;
-__global__ void __launch_bounds__(kTlOffThreads)
-k_cell_offsets(int32_t n_tiles, int32_t n_cells, int64_t cap, uint2* __restrict__ ranges, uint32_t* __restrict__ n_inst,
-               uint32_t* __restrict__ overflow, uint32_t* __restrict__ split_counts, TlSpace ws) {
-  __shared__ uint32_t s_warp[kTlOffThreads / 64];
-  __shared__ uint32_t s_extra;
-  if (threadIdx.x == 0) s_extra = 0u;
-  uint32_t total = 0;
-  for (int b = 0; b < n_tiles; b += kTlOffThreads * kTlOffPer) {
-    const int t0 = b + (int)threadIdx.x * kTlOffPer;
-    uint32_t x[kTlOffPer], sum = 0;
+constexpr int kTlOffPer = 2;
+// This lane's sums of x[0 .. n) and of the first `before` of them.
+__device__ __forceinline__ void sum_before(const uint32_t* __restrict__ x, int n, int before, uint32_t& all,
+                                           uint32_t& pre) {
+  for (int i0 = (int)threadIdx.x; i0 < n; i0 += 8 * kTlOffThreads) {
+    uint32_t y[8];
 #pragma unroll
-    for (int k = 0; k < kTlOffPer; ++k) {
-      x[k] = t0 + k < n_tiles ? ws.totals[t0 + k] : 0u;
-      sum += x[k];
+    for (int k = 0; k < 8; ++k) {
+      const int i = i0 + k * kTlOffThreads;
+      y[k] = i < n ? x[i] : 0u;
     }
-    uint32_t run = block_scan<kTlOffThreads>(sum, s_warp, total) - sum;
 #pragma unroll
-    for (int k = 0; k < kTlOffPer; ++k) {
-      if (t0 + k < n_tiles) ranges[t0 + k] = x[k] ? make_uint2(run, run + x[k]) : make_uint2(0u, 0u);
-      run += x[k];
+    for (int k = 0; k < 8; ++k) {
+      all += y[k];
+      pre += i0 + k * kTlOffThreads < before ? y[k] : 0u;
     }
   }
+}
+__global__ void __launch_bounds__(kTlOffThreads)
+k_cell_offsets(ViewsArg va, CellBase cb, int32_t n_cells, int64_t cap, uint2* __restrict__ ranges,
+               uint32_t* __restrict__ n_inst, uint32_t* __restrict__ overflow, uint32_t* __restrict__ split_counts,
+               TlSpace ws) {
+  __shared__ uint32_t s_warp[kTlOffThreads / 64];
+  const int n_tiles = va.total_tiles;
+  const int first = (int)blockIdx.x * kTlOffThreads * kTlOffPer;
+  const int t0 = first + (int)threadIdx.x * kTlOffPer;
+  uint32_t all = 0, pre = 0, call = 0, cpre = 0;
+  uint32_t x[kTlOffPer], c[kTlOffPer], xs = 0, cs = 0;
+#pragma unroll
+  for (int k = 0; k < kTlOffPer; ++k) {
+    x[k] = t0 + k < n_tiles ? ws.totals[t0 + k] : 0u;
+    c[k] = t0 + k < n_cells ? ws.sizes[t0 + k] : 0u;
+    xs += x[k];
+    cs += c[k];
+  }
+  sum_before(ws.totals, n_tiles, first, all, pre);
+  sum_before(ws.sizes, min(n_cells, first), first, call, cpre);
+  // the sums over the block's lanes, then the lanes' places in the block's own run
+  uint32_t total = 0, at = 0, cell_at = 0;
+  block_scan<kTlOffThreads>(all, s_warp, total);
+  block_scan<kTlOffThreads>(pre, s_warp, at);
+  block_scan<kTlOffThreads>(cpre, s_warp, cell_at);
+  uint32_t run = block_scan<kTlOffThreads>(xs, s_warp, at) - xs;
+  uint32_t crun = block_scan<kTlOffThreads>(cs, s_warp, cell_at) - cs;
   const bool dropped = (int64_t)total > cap;
-  if (threadIdx.x == 0) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
     n_inst[0] = total;
     if (dropped) atomicOr(overflow, 1u);
     atomicMax(overflow + 2, total);
   }
-  uint32_t carry = 0;
-  for (int b = 0; b < n_cells; b += kTlOffThreads * kTlOffPer) {
-    const int t0 = b + (int)threadIdx.x * kTlOffPer;
-    uint32_t x[kTlOffPer], sum = 0;
+  if (blockIdx.x == 0 && threadIdx.x < 2 && split_counts)
+    split_counts[threadIdx.x] = 0u;  // (k_cell_sort takes the long lists)
 #pragma unroll
-    for (int k = 0; k < kTlOffPer; ++k) {
-      x[k] = t0 + k < n_cells && !dropped ? ws.start[t0 + k] : 0u;
-      sum += x[k];
+  for (int k = 0; k < kTlOffPer; ++k) {
+    const int i = t0 + k;
+    if (i < n_tiles) {
+      ranges[i] = x[k] && !dropped ? make_uint2(run, run + x[k]) : make_uint2(0u, 0u);
+      const int v = view_of_tile(va, i), lt = i - va.v[v].tile_base, tiles_x = va.v[v].tiles_x;
+      const int ty = lt / tiles_x, tx = lt - ty * tiles_x;
+      ws.lists[4 * (cb.cell[v] + (ty >> 1) * cells_of(tiles_x) + (tx >> 1)) + 2 * (ty & 1) + (tx & 1)] = run;
     }
-    uint32_t run = block_scan<kTlOffThreads>(sum, s_warp, carry) - sum;
-#pragma unroll
-    for (int k = 0; k < kTlOffPer; ++k) {
-      const int c = t0 + k;
-      if (c < n_cells) ws.start[c] = run;
-      run += x[k];
-      if (x[k] <= (uint32_t)kSortMost) continue;
-      const uint32_t more = (uint32_t)sort_chunks(x[k]) - 1u;
-      const uint32_t e0 = atomicAdd(&s_extra, more);
-      const bool fits = e0 + more <= (uint32_t)kSortExtra;
-      ws.alone[c] = fits ? 0u : kAlone;
-      // (items reserved but not used are marked empty)
-      for (uint32_t i = 0; i < more && e0 + i < (uint32_t)kSortExtra; ++i)
-        ws.extra[e0 + i] = fits ? make_uint2((uint32_t)c, i + 1u) : make_uint2(kNoSlot, 0u);
+    run += x[k];
+    if (i >= n_cells) continue;
+    if (dropped) crun = c[k] = 0u;
+    const uint32_t start = crun;
+    ws.start[i] = start;
+    crun += c[k];
+    if (i == n_cells - 1) ws.start[n_cells] = crun;
+    if (c[k] <= (uint32_t)kSortSmall) continue;
+    const uint32_t more = (uint32_t)sort_chunks(c[k]) - 1u;
+    bool fits = true;
+    if (more) {
+      const uint32_t e0 = atomicAdd(ws.count + kExtra, more);
+      fits = e0 + more <= (uint32_t)kSortExtra;
+      ws.alone[i] = fits ? 0u : 1u;
+    }
+    const uint32_t n = fits ? more + 1u : 1u, j0 = atomicAdd(ws.count + kItems, n);
+    const uint32_t c0 = n > 1u ? atomicAdd(ws.count + kChunks, n) : 0u;
+    for (uint32_t j = 0; j < n; ++j) {
+      ws.items[j0 + j] = make_uint4((uint32_t)i, j, start, c[k]);
+      if (n > 1u) ws.chunks[c0 + j] = ws.items[j0 + j];
     }
   }
-  if (threadIdx.x == 0) ws.start[n_cells] = carry;
-  if (dropped)
-    for (int t = (int)threadIdx.x; t < n_tiles; t += kTlOffThreads) ranges[t] = make_uint2(0u, 0u);
-  __syncthreads();
-  if (threadIdx.x == 0) ws.count[0] = min(s_extra, (uint32_t)kSortExtra);
-  if (threadIdx.x < 2 && split_counts) split_counts[threadIdx.x] = 0u;  // (k_cell_sort takes the long lists)
 }
 
 // DET: the entry carries, instead of the Gaussian, the emission index of its first hit (the
 // pair's first one plus the pair's hits in earlier cells), which grows with the Gaussian, and
 // emit_g tells the Gaussian of it.
 template <bool DET>
-__global__ void __launch_bounds__(kTlThreads)
+__global__ void __launch_bounds__(kTlThreads) __attribute__((amdgpu_waves_per_eu(8)))
 k_cell_place(const float4* __restrict__ rec, const uint4* __restrict__ pairs, const uint32_t* __restrict__ dkey,
              const uint32_t* __restrict__ inst_off, int32_t N, ViewsArg va, CellBase cb, TlSpace ws,
              uint64_t* __restrict__ entries, uint32_t* __restrict__ emit_g) {
@@ -628,6 +668,10 @@ __device__ __forceinline__ void bitonic_sort(uint64_t* s, int n) {
 // depths) a bitonic network orders the entries instead, whose time does not depend on the
 // values.
 constexpr int kBinMost = 256;
+// Up to this many entries are ranked by comparing each with all: two barriers where the bins
+// take a dozen (6435 cells of 60 entries on average: 57 us with bins alone, 45 with this; up to
+// 512 entries ranked: 49).
+constexpr int kRankMost = 128;
 // Two fine bins share a word (16 bits each: CAP < 2^16); four 4096-entry blocks fit a CU.
 template <int NT, int CAP>
 struct __align__(16) SortLds {
@@ -647,6 +691,20 @@ __device__ __forceinline__ void sort_run(SortLds<NT, CAP>& L, const uint64_t* __
   constexpr int PER = CAP / NT, WORDS = CAP / 4 / NT;
   static_assert(CAP % (4 * NT) == 0 && CAP < 65536, "whole words of bins per lane");
   const int tid = (int)threadIdx.x;
+  if (CAP <= kSortSmall && n <= kRankMost) {  // (the larger size has none so small)
+    const uint64_t e = tid < n ? src[tid] : ~0ull;
+    if (tid < kRankMost) L.e[tid] = e;  // (past n: larger than every entry)
+    __syncthreads();
+    int r = 0;
+    if (tid < n)
+      for (int j = 0; j < n; j += 8)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) r += L.e[j + u] < e ? 1 : 0;
+    __syncthreads();
+    if (tid < n) L.e[r] = e;
+    __syncthreads();
+    return;
+  }
   uint64_t e[PER];
   uint32_t lo = 0xffffffffu, hi = 0u;
 #pragma unroll
@@ -777,26 +835,6 @@ __device__ __forceinline__ void sort_run(SortLds<NT, CAP>& L, const uint64_t* __
   __syncthreads();
 }
 
-// Position in a chunked cell of entry e, which is entry i of chunk c: the entries before it in
-// its own chunk and in every other.
-__device__ __forceinline__ uint32_t merged_position(const uint64_t* __restrict__ list, int n, int nch, int c, int i,
-                                                    uint64_t e) {
-  uint32_t pos = (uint32_t)i;
-  for (int o = 0; o < nch; ++o) {
-    if (o == c) continue;
-    int a, b;
-    chunk_range(n, nch, o, a, b);
-    const int a0 = a;
-    while (a < b) {
-      const int mid = (a + b) >> 1;
-      if (list[mid] < e) a = mid + 1;
-      else b = mid;
-    }
-    pos += (uint32_t)(a - a0);
-  }
-  return pos;
-}
-
 // Where a cell's tiles' lists go.
 struct ListOut {
   uint32_t* list_g;
@@ -806,10 +844,10 @@ struct ListOut {
 
 // Deals the n ordered entries e of a cell out to its tiles' lists: each wave takes a run of
 // 64-entry groups, counts its run's hits per tile, and after a prefix over the waves places
-// them, a group at a time, by ballots. s_cnt: [waves][4].
+// them, a group at a time, by ballots. to: where the lists start. s_cnt: [waves][4].
 template <int NT>
-__device__ __forceinline__ void deal_cell(const uint64_t* e, int n, const ViewDev& V, int lc,
-                                          const uint2* __restrict__ ranges, uint32_t (*s_cnt)[4], const ListOut& o) {
+__device__ __forceinline__ void deal_cell(const uint64_t* e, int n, const uint4& to, uint32_t (*s_cnt)[4],
+                                          const ListOut& o) {
   constexpr int NW = NT / 64;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int groups = (n + 63) >> 6, per = (groups + NW - 1) / NW;
@@ -823,14 +861,10 @@ __device__ __forceinline__ void deal_cell(const uint64_t* e, int n, const ViewDe
   }
   if (lane < 4) s_cnt[wid][lane] = lane == 0 ? cnt[0] : lane == 1 ? cnt[1] : lane == 2 ? cnt[2] : cnt[3];
   __syncthreads();
-  const int cx = cells_of(V.tiles_x), tx = 2 * (lc % cx), ty = 2 * (lc / cx);
-  uint32_t at[4];
+  uint32_t at[4] = {to.x, to.y, to.z, to.w};
 #pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const int x = tx + (b & 1), y = ty + (b >> 1);
-    at[b] = x < V.tiles_x && y < V.tiles_y ? ranges[V.tile_base + y * V.tiles_x + x].x : 0u;
+  for (int b = 0; b < 4; ++b)
     for (int w = 0; w < wid; ++w) at[b] += s_cnt[w][b];
-  }
   const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
   for (int g = g0; g < g1; ++g) {
     const int i = g * 64 + lane;
@@ -850,45 +884,137 @@ __device__ __forceinline__ void deal_cell(const uint64_t* e, int n, const ViewDe
   }
 }
 
-// Entries first, first + step, ... of a chunked cell to their merged positions, chunk by chunk.
-__device__ __forceinline__ void merge_cell(const uint64_t* __restrict__ list, int n, int nch, int first, int step,
-                                           uint64_t* __restrict__ merged) {
-  for (int c = 0; c < nch; ++c) {
-    int a, b;
-    chunk_range(n, nch, c, a, b);
-    for (int i = a + first; i < b; i += step) {
-      const uint64_t e = list[i];
-      merged[merged_position(list, n, nch, c, i - a, e)] = e;
+// First entry of chunk c where the first `longer` chunks have len + 1 entries and the rest len.
+__device__ __forceinline__ int chunk_begin(int len, int longer, int c) { return c * len + min(c, longer); }
+
+// An ordered chunk, back to its place, and per 64 of its entries which of them reach each of
+// the cell's four tiles (a 64-bit mask per tile) and how many of the chunk's earlier ones do
+// (32 bits each): kGroupWords words per group, the chunk's totals after its last.
+constexpr int kGroupWords = 6;
+template <int NT>
+__device__ __forceinline__ void write_chunk(const uint64_t* e, int n, uint64_t* __restrict__ list,
+                                            uint64_t* __restrict__ groups, uint32_t (*s_cnt)[4]) {
+  constexpr int NW = NT / 64;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int ng = (n + 63) >> 6, per = (ng + NW - 1) / NW;
+  const int g0 = min(wid * per, ng), g1 = min(g0 + per, ng);
+  uint32_t at[4] = {0u, 0u, 0u, 0u};
+  for (int pass = 0; pass < 2; ++pass) {
+    for (int g = g0; g < g1; ++g) {
+      const int i = g * 64 + lane;
+      const uint64_t x = i < n ? e[i] : 0ull;
+      if (pass == 0 && i < n) list[i] = x;
+      uint64_t m[4];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) m[b] = __ballot((uint32_t)(x >> b) & 1u);
+      if (pass == 1 && lane < kGroupWords)
+        groups[g * kGroupWords + lane] = lane == 0   ? m[0]
+                                         : lane == 1 ? m[1]
+                                         : lane == 2 ? m[2]
+                                         : lane == 3 ? m[3]
+                                         : lane == 4 ? (uint64_t)at[1] << 32 | at[0]
+                                                     : (uint64_t)at[3] << 32 | at[2];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) at[b] += (uint32_t)__popcll(m[b]);
     }
+    if (pass == 0) {
+      if (lane < 4) s_cnt[wid][lane] = lane == 0 ? at[0] : lane == 1 ? at[1] : lane == 2 ? at[2] : at[3];
+      __syncthreads();
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        at[b] = 0u;
+        for (int w = 0; w < wid; ++w) at[b] += s_cnt[w][b];
+      }
+    } else if (g0 < g1 && g1 == ng && lane < kGroupWords) {
+      groups[ng * kGroupWords + lane] = lane < 4 ? 0ull : lane == 4 ? (uint64_t)at[1] << 32 | at[0] : (uint64_t)at[3] << 32 | at[2];
+    }
+  }
+  __syncthreads();  // s_cnt and the entries are reused
+}
+
+// Entries first, first + step, ... of chunk c of a cell to its tiles' lists: an entry's place in
+// a list is the number of entries before it that reach the tile, in its own chunk and, by a
+// binary search, in every other.
+__device__ __forceinline__ void merge_chunk(const uint64_t* list, const uint64_t* groups, int n, int nch, int c,
+                                            int first, int step, const uint4& to, const ListOut& o) {
+  const int len = n / nch, longer = n % nch;
+  const int a0 = chunk_begin(len, longer, c), b0 = chunk_begin(len, longer, c + 1);
+  for (int i = a0 + first; i < b0; i += step) {
+    const uint64_t e = list[i];
+    uint32_t at[4] = {to.x, to.y, to.z, to.w};
+    for (int k = 0; k < nch; ++k) {
+      const int a = chunk_begin(len, longer, k);
+      int lo = k == c ? i : a, hi = k == c ? i : chunk_begin(len, longer, k + 1);
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (list[mid] < e) lo = mid + 1;
+        else hi = mid;
+      }
+      const uint64_t* g = groups + a + ((lo - a) >> 6) * kGroupWords;
+      const uint64_t below = (1ull << ((lo - a) & 63)) - 1ull;
+      const uint64_t p0 = g[4], p1 = g[5];
+      at[0] += (uint32_t)__popcll(g[0] & below) + (uint32_t)p0;
+      at[1] += (uint32_t)__popcll(g[1] & below) + (uint32_t)(p0 >> 32);
+      at[2] += (uint32_t)__popcll(g[2] & below) + (uint32_t)p1;
+      at[3] += (uint32_t)__popcll(g[3] & below) + (uint32_t)(p1 >> 32);
+    }
+    const uint32_t tiles = (uint32_t)e & 15u, id = (uint32_t)e >> kTlMaskBits;
+    const uint32_t gid = o.list_e ? o.emit_g[id] : id;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      if ((tiles >> b) & 1u) {
+        o.list_g[at[b]] = gid;
+        if (o.list_e) o.list_e[at[b]] = id + (uint32_t)__popc(tiles & ((1u << b) - 1u));
+      }
   }
 }
 
-// Block c orders cell c's entries where their number is in the size's range; with the larger
-// size the blocks past the cells take the extra chunks. The smaller size (which every cell
-// passes) also marks the cell's long tile lists (split_tile).
+// Orders and deals out cell `cell`, or orders its chunk c (every chunk, and deals it out, where
+// its block is alone with it). groups: one word per entry, which the chunks' groups fit into.
 template <bool LARGE>
-__global__ void __launch_bounds__(SortShape<LARGE>::threads)
-k_cell_sort(ViewsArg va, CellBase cb, int32_t n_cells, const uint2* __restrict__ ranges, uint64_t* __restrict__ entries,
-            uint64_t* __restrict__ merged, TlSpace ws, ListOut o, SplitArg sp) {
-  using S = SortShape<LARGE>;
-  constexpr int NT = S::threads;
-  __shared__ SortLds<NT, S::cap> L;
-  __shared__ uint32_t s_cnt[NT / 64][4];
-  int cell = (int)blockIdx.x, c = 0;
-  if (LARGE && cell >= n_cells) {
-    const int x = cell - n_cells;
-    if (x >= (int)ws.count[0]) return;
-    const uint2 it = ws.extra[x];
-    if (it.x == kNoSlot) return;
-    cell = (int)it.x;
-    c = (int)it.y;
+__device__ __forceinline__ void sort_cell(SortLds<SortShape<LARGE>::threads, SortShape<LARGE>::cap>& L,
+                                          uint32_t (*s_cnt)[4], int cell, int c, uint32_t start, int n,
+                                          uint64_t* __restrict__ entries, uint64_t* __restrict__ groups,
+                                          const TlSpace& ws, const ListOut& o) {
+  constexpr int NT = SortShape<LARGE>::threads;
+  uint64_t* list = entries + start;
+  const uint4 to = ((const uint4*)ws.lists)[cell];
+  const int nch = LARGE ? sort_chunks((uint32_t)n) : 1;
+  if (nch == 1) {
+    sort_run(L, list, n);
+    deal_cell<NT>(L.e, n, to, s_cnt, o);
+    return;
   }
+  const bool alone = ws.alone[cell] != 0u;
+  const int c1 = alone ? nch : c + 1;
+  const int len = n / nch, longer = n % nch;
+  for (int k = c; k < c1; ++k) {
+    const int a = chunk_begin(len, longer, k), b = chunk_begin(len, longer, k + 1);
+    sort_run(L, list + a, b - a);
+    write_chunk<NT>(L.e, b - a, list + a, groups + start + a, s_cnt);
+  }
+  if (!alone) return;
+  __threadfence_block();
+  __syncthreads();
+  for (int k = 0; k < nch; ++k) merge_chunk(list, groups + start, n, nch, k, (int)threadIdx.x, NT, to, o);
+}
+
+// Block c orders cell c's entries where the small size holds them, and marks the cell's long
+// tile lists (split_tile).
+__global__ void __launch_bounds__(SortShape<false>::threads)
+k_cell_sort_small(ViewsArg va, CellBase cb, const uint2* __restrict__ ranges, uint64_t* __restrict__ entries, TlSpace ws,
+                  ListOut o, SplitArg sp) {
+  using S = SortShape<false>;
+  __shared__ SortLds<S::threads, S::cap> L;
+  __shared__ uint32_t s_cnt[S::threads / 64][4];
+  const int cell = (int)blockIdx.x;
   const uint32_t start = ws.start[cell];
   const int n = (int)(ws.start[cell + 1] - start);
-  const int v = view_of_cell(cb, va.n, cell);
-  const ViewDev& V = va.v[v];
-  if (!LARGE && sp.par > 0 && threadIdx.x < 4) {
-    const int lc = cell - cb.cell[v], cx = cells_of(V.tiles_x);
+  if (n > 0 && n <= S::cap) sort_cell<false>(L, s_cnt, cell, 0, start, n, entries, nullptr, ws, o);
+  if (sp.par > 0 && threadIdx.x < 4) {
+    const int v = view_of_cell(cb, va.n, cell), lc = cell - cb.cell[v];
+    const ViewDev& V = va.v[v];
+    const int cx = cells_of(V.tiles_x);
     const int tx = 2 * (lc % cx) + ((int)threadIdx.x & 1), ty = 2 * (lc / cx) + ((int)threadIdx.x >> 1);
     if (tx < V.tiles_x && ty < V.tiles_y) {
       const int t = V.tile_base + ty * V.tiles_x + tx;
@@ -896,64 +1022,34 @@ k_cell_sort(ViewsArg va, CellBase cb, int32_t n_cells, const uint2* __restrict__
       split_tile(sp, t, r.y - r.x, *sp.n_inst, va.total_tiles, sp.counts);
     }
   }
-  if (n <= S::lo || (!LARGE && n > S::cap)) return;
-  uint64_t* list = entries + start;
-  const int nch = LARGE ? sort_chunks((uint32_t)n) : 1;
-  if (nch == 1) {
-    sort_run(L, list, n);
-    deal_cell<NT>(L.e, n, V, cell - cb.cell[v], ranges, s_cnt, o);
-    return;
-  }
-  const bool alone = ws.alone[cell] == kAlone;
-  const int c1 = alone ? nch : c + 1;
-  for (int k = c; k < c1; ++k) {
-    int a, b;
-    chunk_range(n, nch, k, a, b);
-    sort_run(L, list + a, b - a);
-    for (int i = (int)threadIdx.x; i < b - a; i += NT) list[a + i] = L.e[i];
-    __syncthreads();
-  }
-  if (!alone) return;
-  __threadfence_block();
-  __syncthreads();
-  merge_cell(list, n, nch, (int)threadIdx.x, NT, merged + start);
-  __threadfence_block();
-  __syncthreads();
-  deal_cell<NT>(merged + start, n, V, cell - cb.cell[v], ranges, s_cnt, o);
 }
 
-// Cells ordered in chunks (none in most renders): the blocks of row y of the grid merge the
-// chunks of cells y, y + rows, ... of the extra items (each cell's first item stands for it);
-// the last of them to finish deals the cell out. The release and acquire around the arrival
-// count are what makes the merged entries visible across the XCDs' L2s, and cost nothing
-// where no cell has chunks.
-constexpr int kMergeRows = 16, kMergeThreads = 1024, kMergeCols = 16;
+// One item of the larger cells per block (the grid is the most that the instances allow: a
+// block per cell spent 15 us on 6435 cells without one such item).
+__global__ void __launch_bounds__(SortShape<true>::threads)
+k_cell_sort_large(uint64_t* __restrict__ entries, uint64_t* __restrict__ groups, TlSpace ws, ListOut o) {
+  using S = SortShape<true>;
+  __shared__ SortLds<S::threads, S::cap> L;
+  __shared__ uint32_t s_cnt[S::threads / 64][4];
+  const uint4 it = ws.items[blockIdx.x];  // (a grid of at most the items' places)
+  if (blockIdx.x >= ws.count[kItems]) return;
+  sort_cell<true>(L, s_cnt, (int)it.x, (int)it.y, it.z, (int)it.w, entries, groups, ws, o);
+}
+
+// Deals out the cells ordered in chunks (none in most renders): the blocks of row y of the grid
+// take chunks y, y + rows, ..., an entry per lane. What bounds it is the chain of an entry's
+// binary searches, 14 dependent loads per other chunk: 685k Gaussians over six cells (some 8
+// chunks each), 815 us when one block dealt out each merged cell, 98 now; 194k over six, 127
+// and 14.
+constexpr int kMergeRows = 32, kMergeThreads = 256, kMergeCols = kSortMost / kMergeThreads;
 __global__ void __launch_bounds__(kMergeThreads)
-k_cell_merge(ViewsArg va, CellBase cb, const uint2* __restrict__ ranges, const uint64_t* __restrict__ entries,
-             uint64_t* __restrict__ merged, TlSpace ws, ListOut o) {
-  __shared__ uint32_t s_cnt[kMergeThreads / 64][4];
-  __shared__ uint32_t s_last;
-  const uint32_t count = ws.count[0];
-  uint32_t turn = 0;
-  for (uint32_t x = 0; x < count; ++x) {
-    const uint2 it = ws.extra[x];
-    if (it.x == kNoSlot || it.y != 1u) continue;
-    if (turn++ % kMergeRows != blockIdx.y) continue;
-    const int cell = (int)it.x;
-    const uint32_t start = ws.start[cell];
-    const int n = (int)(ws.start[cell + 1] - start);
-    merge_cell(entries + start, n, sort_chunks((uint32_t)n), (int)(blockIdx.x * kMergeThreads + threadIdx.x),
-               kMergeCols * kMergeThreads, merged + start);
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) s_last = atomicAdd(&ws.alone[cell], 1u) == (uint32_t)kMergeCols - 1u ? 1u : 0u;
-    __syncthreads();
-    if (s_last) {
-      __threadfence();
-      const int v = view_of_cell(cb, va.n, cell);
-      deal_cell<kMergeThreads>(merged + start, n, va.v[v], cell - cb.cell[v], ranges, s_cnt, o);
-    }
-    __syncthreads();  // s_cnt and s_last are reused
+k_cell_merge(const uint64_t* __restrict__ entries, const uint64_t* __restrict__ groups, TlSpace ws, ListOut o) {
+  const uint32_t count = ws.count[kChunks];
+  for (uint32_t x = blockIdx.y; x < count; x += kMergeRows) {
+    const uint4 it = ws.chunks[x];
+    merge_chunk(entries + it.z, groups + it.z, (int)it.w, sort_chunks(it.w), (int)it.y,
+                (int)(blockIdx.x * kMergeThreads + threadIdx.x), kMergeCols * kMergeThreads,
+                ((const uint4*)ws.lists)[it.x], o);
   }
 }
 
@@ -983,14 +1079,16 @@ hipError_t tile_lists_plan(const float4* rec, const uint4* pairs, int32_t N, con
                      ws);
   hipLaunchKernelGGL(k_cell_colscan, dim3((unsigned)((nc + kTlCols - 1) / kTlCols)), dim3(kTlSegs * kTlCols), 0, s, va, cb,
                      nc, ws);
-  hipLaunchKernelGGL(k_cell_offsets, dim3(1), dim3(kTlOffThreads), 0, s, va.total_tiles, nc, cap, ranges, n_inst,
-                     overflow, split_counts, ws);
+  const int off_blocks = (va.total_tiles + kTlOffThreads * kTlOffPer - 1) / (kTlOffThreads * kTlOffPer);
+  hipLaunchKernelGGL(k_cell_offsets, dim3((unsigned)off_blocks), dim3(kTlOffThreads), 0, s, va, cb, nc, cap,
+                     ranges, n_inst, overflow, split_counts, ws);
   return hipGetLastError();
 }
 
 hipError_t tile_lists_build(const float4* rec, const uint4* pairs, const uint32_t* dkey, const uint32_t* inst_off,
                             int32_t N, const ViewsArg& va, void* space, const uint2* ranges, uint64_t* entries,
-                            uint64_t* merged, uint32_t* emit_g, uint32_t* list_g, uint32_t* list_e, const SplitArg& sp, hipStream_t s) {
+                            uint64_t* groups, uint32_t* emit_g, uint32_t* list_g, uint32_t* list_e,
+                            const SplitArg& sp, hipStream_t s) {
   const int nc = (int)cells_total(va);
   const CellBase cb = cell_base(va, N);
   const TlSpace ws = tl_space(space, va, cb);
@@ -1005,15 +1103,17 @@ hipError_t tile_lists_build(const float4* rec, const uint4* pairs, const uint32_
   else
     hipLaunchKernelGGL(k_cell_place<false>, grid, dim3(kTlThreads), lds, s, rec, pairs, dkey, inst_off, N, va, cb, ws,
                        entries, emit_g);
-  // a cell holds a Gaussian once: a small map has no cells for the larger blocks
-  hipLaunchKernelGGL(k_cell_sort<false>, dim3((unsigned)nc), dim3(SortShape<false>::threads), 0, s, va, cb, nc, ranges,
-                     entries, merged, ws, o, sp);
-  if (N > SortShape<false>::cap)
-    hipLaunchKernelGGL(k_cell_sort<true>, dim3((unsigned)(nc + (N > kSortMost ? kSortExtra : 0))),
-                       dim3(SortShape<true>::threads), 0, s, va, cb, nc, ranges, entries, merged, ws, o, sp);
+  hipLaunchKernelGGL(k_cell_sort_small, dim3((unsigned)nc), dim3(SortShape<false>::threads), 0, s, va, cb, ranges,
+                     entries, ws, o, sp);
+  // a cell holds a Gaussian once: a small map has no items for the larger blocks
+  if (N > kSortSmall) {
+    const int64_t most = std::min<int64_t>(nc, va.inst_cap / kSortSmall + 1),
+                  extra = N > kSortMost ? std::min<int64_t>(kSortExtra, va.inst_cap / kSortMost + 1) : 0;
+    hipLaunchKernelGGL(k_cell_sort_large, dim3((unsigned)(most + extra)), dim3(SortShape<true>::threads), 0, s,
+                       entries, groups, ws, o);
+  }
   if (N > kSortMost)
-    hipLaunchKernelGGL(k_cell_merge, dim3(kMergeCols, kMergeRows), dim3(kMergeThreads), 0, s, va, cb, ranges, entries,
-                       merged, ws, o);
+    hipLaunchKernelGGL(k_cell_merge, dim3(kMergeCols, kMergeRows), dim3(kMergeThreads), 0, s, entries, groups, ws, o);
   return hipGetLastError();
 }
 

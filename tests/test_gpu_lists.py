@@ -57,6 +57,17 @@ def test_lists_of_small_large_and_chunked_cells(n, over, most, deterministic):
     assert over < largest <= most
 
 
+# one cell: the most Gaussians that it takes in chunks, and past them (radix path); and a few
+# entries either side of what one wave-wide comparison ranks
+@pytest.mark.parametrize("n", [65_536, 65_600, 100, 128, 129, 260])
+@pytest.mark.parametrize("deterministic", [False, True])
+def test_lists_of_one_cell(n, deterministic):
+    cam = scenes.pinhole(24, 20, 20.0)
+    params = scenes.frustum_gaussians(n, 0, cam, seed=n)
+    print(f"{n} Gaussians over one cell, deterministic {deterministic}", flush=True)
+    _check_lists(params, 0, [cam], deterministic)
+
+
 # all depths equal (order by index alone), a few distinct depths, and a tight cluster with one
 # far outlier: more entries per bin than the bins take
 @pytest.mark.parametrize("shape", ["equal", "steps", "cluster"])
