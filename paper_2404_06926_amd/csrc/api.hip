@@ -595,7 +595,7 @@ gs_status gs_add_sky(gs_map* m, int64_t n, const float* xyz, float o_sky, void* 
   if (!(o_sky > 0.f && o_sky < 1.f)) return fail(GS_ERR_INVALID, "o_sky must be in (0, 1)");
   if (m->n + n > (int64_t)INT32_MAX) return fail(GS_ERR_CAPACITY, "more than 2^31-1 Gaussians");
   hipStream_t s = (hipStream_t)stream;
-  GS_TRY(ensure(m, m->gr_d2, (size_t)n * 4, s));
+  GS_TRY(ensure(m, m->gr_d2, (size_t)n * 4 * nn_segments(n), s));
   GS_TRY(grow_capacity(m, m->n + n, s));
   const float logit0 = std::log(o_sky / (1.0f - o_sky));
   GS_HIP(init_sky(m->buf, m->cap, m->F, m->K, m->n, n, xyz, (float*)m->gr_d2.ptr, logit0, m->vis, s));

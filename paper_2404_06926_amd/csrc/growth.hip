@@ -81,44 +81,74 @@ k_init_selected(float* __restrict__ buf, int64_t cap, int32_t F, int32_t K, int6
            rgb[3 * j + 1], rgb[3 * j + 2], vis);
 }
 
-// Squared distance from each point to its closest other point: every lane owns one point
-// and sweeps all points through LDS in tiles of 256.
-__global__ void __launch_bounds__(256) k_nn_dist2(const float* __restrict__ xyz, int64_t n, float* __restrict__ d2) {
-  __shared__ float s_p[3][256];
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  float x = 0.f, y = 0.f, z = 0.f;
-  if (j < n) {
-    x = xyz[3 * j];
-    y = xyz[3 * j + 1];
-    z = xyz[3 * j + 2];
-  }
-  float best = __builtin_huge_valf();
-  for (int64_t base = 0; base < n; base += 256) {
-    __syncthreads();
-    const int64_t k = base + threadIdx.x;
-    if (k < n) {
-      s_p[0][threadIdx.x] = xyz[3 * k];
-      s_p[1][threadIdx.x] = xyz[3 * k + 1];
-      s_p[2][threadIdx.x] = xyz[3 * k + 2];
-    }
-    __syncthreads();
-    const int cnt = (int)min((int64_t)256, n - base);
-    for (int t = 0; t < cnt; ++t) {
-      const float dx = s_p[0][t] - x, dy = s_p[1][t] - y, dz = s_p[2][t] - z;
-      const float e = dx * dx + dy * dy + dz * dz;
-      if (base + t != j) best = fminf(best, e);
+// Squared distance from each point to its closest other point: every lane owns kNnPer points
+// and sweeps its block's segment of all points through LDS in tiles of 256; part[s n + j] is
+// point j's least over segment s. Bound by VALU work (seven instructions per pair, of which
+// none but the minimum's order may change: a pair's distance rounds as it always did). With
+// one block per 256 points and no segments a sky of 20k ran on 79 of 256 CUs, 1389 us; with
+// enough segments for kNnBlocks blocks 97.
+constexpr int kNnThreads = 256, kNnPer = 2, kNnBlocks = 2048;
+__global__ void __launch_bounds__(kNnThreads)
+k_nn_dist2(const float* __restrict__ xyz, int64_t n, float* __restrict__ part) {
+  __shared__ float4 s_p[kNnThreads];
+  const int64_t j0 = (int64_t)blockIdx.x * (kNnThreads * kNnPer);
+  float x[kNnPer], y[kNnPer], z[kNnPer], best[kNnPer];
+#pragma unroll
+  for (int u = 0; u < kNnPer; ++u) {
+    const int64_t j = j0 + u * kNnThreads + threadIdx.x;
+    x[u] = y[u] = z[u] = 0.f;
+    best[u] = __builtin_huge_valf();
+    if (j < n) {
+      x[u] = xyz[3 * j];
+      y[u] = xyz[3 * j + 1];
+      z[u] = xyz[3 * j + 2];
     }
   }
-  if (j < n) d2[j] = best;
+  const int64_t tiles = (n + kNnThreads - 1) / kNnThreads;
+  const int64_t b0 = (int64_t)blockIdx.y * tiles / gridDim.y, b1 = (int64_t)(blockIdx.y + 1) * tiles / gridDim.y;
+  for (int64_t b = b0; b < b1; ++b) {
+    const int64_t base = b * kNnThreads, k = base + threadIdx.x;
+    __syncthreads();
+    // (past the end: infinitely far)
+    const float inf = __builtin_huge_valf();
+    s_p[threadIdx.x] = k < n ? make_float4(xyz[3 * k], xyz[3 * k + 1], xyz[3 * k + 2], 0.f) : make_float4(inf, inf, inf, 0.f);
+    __syncthreads();
+    const int64_t own = base - j0;
+    const bool meets = own >= 0 && own < kNnThreads * kNnPer;  // the tile holds points of this block
+#pragma unroll 8
+    for (int t = 0; t < kNnThreads; ++t) {
+      const float4 p = s_p[t];
+#pragma unroll
+      for (int u = 0; u < kNnPer; ++u) {
+        const float dx = p.x - x[u], dy = p.y - y[u], dz = p.z - z[u];
+        const float e = __fmaf_rn(dz, dz, __fmaf_rn(dx, dx, __fmul_rn(dy, dy)));
+        if (!meets || (int)own + t != u * kNnThreads + (int)threadIdx.x) best[u] = fminf(best[u], e);
+      }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kNnPer; ++u) {
+    const int64_t j = j0 + u * kNnThreads + threadIdx.x;
+    if (j < n) part[blockIdx.y * n + j] = best[u];
+  }
+}
+static int64_t nn_blocks(int64_t n) { return (n + kNnThreads * kNnPer - 1) / (kNnThreads * kNnPer); }
+int nn_segments(int64_t n) {
+  const int64_t tiles = (n + kNnThreads - 1) / kNnThreads;
+  return (int)std::max<int64_t>(1, std::min(tiles, kNnBlocks / nn_blocks(n)));
 }
 
 // Sky rows: white DC, opacity logit0, isotropic scale = nearest-neighbour distance.
 __global__ void __launch_bounds__(256)
 k_init_sky(float* __restrict__ buf, int64_t cap, int32_t F, int32_t K, int64_t n0, int64_t n,
-           const float* __restrict__ xyz, const float* __restrict__ d2, float logit0, uint8_t* __restrict__ vis) {
+           const float* __restrict__ xyz, const float* __restrict__ part, int segments, float logit0,
+           uint8_t* __restrict__ vis) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
-  init_row(buf, cap, F, K, n0 + j, xyz[3 * j], xyz[3 * j + 1], xyz[3 * j + 2], 0.5f * logf(d2[j]), logit0, 1.0f,
+  float d2 = part[j];
+#pragma unroll 8
+  for (int g = 1; g < segments; ++g) d2 = fminf(d2, part[g * n + j]);
+  init_row(buf, cap, F, K, n0 + j, xyz[3 * j], xyz[3 * j + 1], xyz[3 * j + 2], 0.5f * logf(d2), logit0, 1.0f,
            1.0f, 1.0f, vis);
 }
 
@@ -143,8 +173,9 @@ hipError_t init_selected(float* buf, int64_t cap, int32_t F, int32_t K, int64_t 
 hipError_t init_sky(float* buf, int64_t cap, int32_t F, int32_t K, int64_t n0, int64_t n, const float* xyz,
                     float* d2, float logit0, uint8_t* vis, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_nn_dist2, dim3(blocks(n)), dim3(256), 0, s, xyz, n, d2);
-  hipLaunchKernelGGL(k_init_sky, dim3(blocks(n)), dim3(256), 0, s, buf, cap, F, K, n0, n, xyz, d2, logit0, vis);
+  const int segments = nn_segments(n);
+  hipLaunchKernelGGL(k_nn_dist2, dim3((unsigned)nn_blocks(n), (unsigned)segments), dim3(kNnThreads), 0, s, xyz, n, d2);
+  hipLaunchKernelGGL(k_init_sky, dim3(blocks(n)), dim3(256), 0, s, buf, cap, F, K, n0, n, xyz, d2, segments, logit0, vis);
   return hipGetLastError();
 }
 

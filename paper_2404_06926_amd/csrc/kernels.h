@@ -197,12 +197,14 @@ hipError_t init_points(float* buf, int64_t cap, int32_t F, int32_t K, int64_t n0
                        const float* rgb, const ViewDev& V, float near_z, float logit0, uint8_t* vis,
                        hipStream_t s);
 // map growth (growth.hip): Eq. 8 selection of points by the opacity of their pixel, the
-// selected points' rows, and sky rows from nearest-neighbour distances (d2: n floats).
+// selected points' rows, and sky rows from nearest-neighbour distances.
 hipError_t expand_flags(const float* xyz, int64_t n, const ViewDev& V, const float* T, float tau, float near_z,
                         uint32_t* flags, hipStream_t s);
 hipError_t init_selected(float* buf, int64_t cap, int32_t F, int32_t K, int64_t n0, int64_t n, const float* xyz,
                          const float* rgb, const uint32_t* flags, const uint32_t* offsets, const ViewDev& V,
                          float near_z, float logit0, uint8_t* vis, hipStream_t s);
+// d2 (init_sky): workspace of nn_segments(n) words per point.
+int nn_segments(int64_t n);
 hipError_t init_sky(float* buf, int64_t cap, int32_t F, int32_t K, int64_t n0, int64_t n, const float* xyz,
                     float* d2, float logit0, uint8_t* vis, hipStream_t s);
 hipError_t copy_planes(const float* src, int64_t cap0, float* dst, int64_t cap1, int64_t n, int nplanes,

@@ -99,6 +99,29 @@ def test_sky_rows_match_oracle():
     np.testing.assert_allclose(got[:, 6:], ref[:, 6:], rtol=1e-6, atol=1e-6)
 
 
+# edges of the sweep's tiles (256 points) and of a block's points (512), fewer tiles than
+# segments and more; pairs of equal points, whose distance is zero
+@pytest.mark.parametrize("n", [2, 3, 256, 257, 511, 513, 1025, 40_000])
+def test_sky_scales_at_the_sweeps_edges(n):
+    torch = torch_mod()
+    r = np.random.default_rng(n)
+    xyz = r.standard_normal((n, 3)).astype(np.float32) * 500.0
+    if n > 256:
+        xyz[n - 1] = xyz[0]
+    print(f"sky of {n} points", flush=True)
+    m = gpu_map(np.zeros((0, 11 + 3), np.float32), 0, cap=64)
+    m.add_sky(torch.tensor(xyz).cuda(), o_sky=0.7)
+    torch.cuda.synchronize()
+    got = m.params().cpu().numpy()[3].astype(np.float64)
+    d = oracle.nearest_neighbour_distance(xyz.astype(np.float64))
+    same = d == 0
+    assert same.sum() == (2 if n > 256 else 0) and np.isneginf(got[same]).all()
+    # differences, products and their sum: six roundings of the squared distance, half of that
+    # and the logarithm's own two ulp in its logarithm
+    ref = np.log(d[~same])
+    np.testing.assert_allclose(got[~same], ref, atol=4 * 2.0 ** -24, rtol=4 * 2.0 ** -24)
+
+
 def test_keyframe_job_expands_by_the_mask():
     # gs_submit_keyframe appends what gs_expand would append on the same map state.
     torch = torch_mod()
