@@ -182,6 +182,12 @@ k_project_fwd(const float* __restrict__ P, int64_t cap, int32_t N, ViewsArg va, 
 //
 // The SH gradients of a single-view batch (MULTI = false) are emitted as soon as they are
 // formed; with several views they are summed in per-lane LDS slots first.
+//
+// With several views a lane's chain of 2D-gradient reads, one per view and phase, bounds the
+// kernel (3.3 TB/s of traffic at 1M rows of degree 0 and eight views, 309 us). The next view's
+// gradients are therefore read while one's are used, and degree 0, whose colours do not
+// depend on the direction, takes them along in the geometry's pass: 225 us; degree 3, 200k
+// rows and eight views of 640x512: 213 -> 202 us.
 __device__ __forceinline__ void pair_grad(size_t vi, const uint32_t* __restrict__ counts,
                                           const float4* __restrict__ g2d, const float4* __restrict__ inst_grad,
                                           const uint32_t* __restrict__ inst_off, float4& ga, float4& gb,
@@ -261,7 +267,7 @@ k_project_bwd(float* P, float* __restrict__ Gp, int64_t cap, int32_t N, ViewsArg
               const uint32_t* __restrict__ counts, float4* __restrict__ g2d, const float4* __restrict__ inst_grad,
               const uint32_t* __restrict__ inst_off, uint8_t* __restrict__ vis, AdamArg ad, LossFinish lf) {
   constexpr int K = (DEG + 1) * (DEG + 1);
-  __shared__ float s_gsh[MULTI ? 3 * K : 1][MULTI ? 256 : 1];
+  __shared__ float s_gsh[MULTI && DEG > 0 ? 3 * K : 1][MULTI && DEG > 0 ? 256 : 1];
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (FUSED && lf.part && blockIdx.x == 0) {
     // the step's losses (Eq. 9) from the loss kernel's per-tile sums, in place of a launch
@@ -307,23 +313,32 @@ k_project_bwd(float* P, float* __restrict__ Gp, int64_t cap, int32_t N, ViewsArg
   float lr_sh[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) lr_sh[k] = ad.lr.lr[k == 0 ? 11 : 14];
-  bool any = false;
-  for (int v = 0; v < va.n; ++v) any |= counts[(size_t)v * N + i] > 0;
-  if (!any && !(FUSED && vis[i])) return;
+  uint32_t seen = 0;  // bit v: the row has tiles in view v
+#pragma unroll
+  for (int v = 0; v < (MULTI ? kMaxViews : 1); ++v)
+    if (v < va.n && counts[(size_t)v * N + i] > 0) seen |= 1u << v;
+  if (!seen && !(FUSED && vis[i])) return;
+  // the 2D gradients of the views in turn, the next view's in flight while one's are used
+  float4 na, nb, nc;
+  auto fetch = [&](int v) {
+    if (v < va.n && ((seen >> v) & 1u)) pair_grad((size_t)v * N + i, counts, g2d, inst_grad, inst_off, na, nb, nc);
+  };
 
   const float mu0 = ldp(0), mu1 = ldp(1), mu2 = ldp(2);
   float gmu[3] = {0.f, 0.f, 0.f};
 
   // ---- phase 1: colour = max(0, sum_k sh_k Y_k(dir) + 0.5), dir = normalised (mu - campos)
-  if (MULTI)
+  // (degree 0 with several views: nothing depends on the direction, and phase 2 takes it along)
+  constexpr bool ALONG = MULTI && DEG == 0;
+  if (MULTI && !ALONG)
     for (int f = 0; f < 3 * K; ++f) s_gsh[f][threadIdx.x] = 0.0f;
   bool sh_done = false;  // single view: SH planes already emitted
-  for (int v = 0; v < va.n; ++v) {
-    const size_t vi = (size_t)v * N + i;
-    if (counts[vi] == 0) continue;
+  if (!ALONG) fetch(0);
+  for (int v = 0; v < (ALONG ? 0 : va.n); ++v) {
+    const float4 gb = nb, gc = nc;
+    fetch(v + 1);
+    if (!((seen >> v) & 1u)) continue;
     const ViewDev& V = va.v[v];
-    float4 ga, gb, gc;
-    pair_grad(vi, counts, g2d, inst_grad, inst_off, ga, gb, gc);
     const float g_col[3] = {gb.z, gb.w, gc.x};
     const float dv0 = mu0 - V.campos[0], dv1 = mu1 - V.campos[1], dv2 = mu2 - V.campos[2];
     const float inv = rsqrtf(dv0 * dv0 + dv1 * dv1 + dv2 * dv2);
@@ -369,7 +384,7 @@ k_project_bwd(float* P, float* __restrict__ Gp, int64_t cap, int32_t N, ViewsArg
       gmu[2] += (gdz - dot * d2) * inv;
     }
   }
-  if (MULTI || !sh_done) {
+  if (!ALONG && (MULTI || !sh_done)) {
     // several views: the summed SH gradients; a single view without a tile in this batch
     // (fused path, row marked by an earlier backward): zero local part
 #pragma unroll 1
@@ -416,12 +431,28 @@ k_project_bwd(float* P, float* __restrict__ Gp, int64_t cap, int32_t N, ViewsArg
   float gM[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
   float glogit = 0.0f;
 
+  float dc[3] = {0.f, 0.f, 0.f}, gdc[3] = {0.f, 0.f, 0.f}, Y0[1] = {0.f};
+  bool lit[3] = {true, true, true};  // channels above the clamp
+  if (ALONG) {
+    sh_basis<0>(0.f, 0.f, 1.f, Y0);
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) {
+      dc[ch] = ldp(11 + ch);
+      lit[ch] = !(__fmaf_rn(dc[ch], Y0[0], 0.5f) < 0.0f);
+    }
+  }
+  fetch(0);
   for (int v = 0; v < va.n; ++v) {
     const size_t vi = (size_t)v * N + i;
-    if (counts[vi] == 0) continue;
+    const float4 ga = na, gb = nb, gc = nc;
+    fetch(v + 1);
+    if (!((seen >> v) & 1u)) continue;
     const ViewDev& V = va.v[v];
-    float4 ga, gb, gc;
-    pair_grad(vi, counts, g2d, inst_grad, inst_off, ga, gb, gc);
+    if (ALONG) {
+      const float g_col[3] = {gb.z, gb.w, gc.x};
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) gdc[ch] = __fadd_rn(gdc[ch], __fmul_rn(lit[ch] ? g_col[ch] : 0.0f, Y0[0]));
+    }
     if (!inst_grad) {
       const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
       g2d[vi * 3 + 0] = zero;
@@ -533,6 +564,15 @@ k_project_bwd(float* P, float* __restrict__ Gp, int64_t cap, int32_t N, ViewsArg
   const float gg[11] = {gmu[0], gmu[1], gmu[2], gls[0], gls[1], gls[2], (gq[0] - qd * unit[0]) * iqn,
                         (gq[1] - qd * unit[1]) * iqn, (gq[2] - qd * unit[2]) * iqn, (gq[3] - qd * unit[3]) * iqn,
                         glogit};
+  if (ALONG) {
+    if (FUSED) {
+      const float lr_dc[3] = {lr_sh[0], lr_sh[0], lr_sh[0]};
+      adam_rows<3>(P, Mp, Vp, Gp, cap, lo, 11, 1, dc, gdc, lr_dc, ad, bc1, bc2);
+    } else {
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) emit(11 + ch, gdc[ch]);
+    }
+  }
   if (FUSED) {
     const float pg[11] = {mu0, mu1, mu2, ls0, ls1, ls2, q0, q1, q2, q3, logit};
     float lr_geo[11];
