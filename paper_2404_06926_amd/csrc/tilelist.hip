@@ -6,28 +6,30 @@
 //   k_cell_count    each block counts its pairs' entries per cell, and the hits of the cell's
 //                   four tiles, in LDS -> its row of the view's matrices;
 //   k_cell_colscan  exclusive prefix of every cell's entries over the rows, and the totals;
-//   k_cell_offsets  exclusive scans of the totals (one block): tile ranges, cell starts, the
-//                   instance count, overflow, and the chunks of long lists;
+//   k_cell_offsets  exclusive scans of the totals: tile ranges, cell starts, the instance
+//                   count, overflow, and the work items of cells past the small block size;
 //   k_cell_place    each block walks its pairs again and writes one entry (depth, Gaussian,
 //                   which of the four tiles) per cell it reaches at the cell's next position,
 //                   in any order within the block;
-//   k_cell_sort     one block per cell orders its entries in LDS and deals them out to its
+//   k_cell_sort_small, k_cell_sort_large
+//                   one block per cell orders its entries in LDS and deals them out to its
 //                   tiles' lists by ballots (two sizes of block); cells of more than kSortMost
 //                   entries are ordered in chunks, which k_cell_merge deals out.
 // (depth, Gaussian) is unique in a cell, so the lists do not depend on the order of arrival.
 //
 // Why cells: what bounds the placement is not its bytes but the scattered writes, which L2
 // writes back as partial lines (one 8-B entry per hit: 272 MB written for 55 MB of entries at
-// 6.9 M hits, 97 us; one per cell: 114 MB, 44 us), and a Gaussian reaches two to three times
+// 6.9 M hits, 97 us; one per cell: 114 MB, 44 us then), and a Gaussian reaches two to three times
 // fewer cells than tiles, which the sort gains as well.
 //
 // Measured against the path it replaced where it applies (a depth sort of the pairs by four
 // radix passes, a scan of the counts in that order, an emission, two radix passes by tile id,
-// the ranges), in us: 1M Gaussians at 1280x720 (6.9 M instances) 257 -> 142; eight views of 1M
-// (41.6 M) 1416 -> 735; 3M at 1920x1200 (35.9 M) 917 -> 550; a street map of 520k with a long
-// horizon (0.7 M) 149 -> 106; 10k at 256x192 (17.8 k) 99 -> 34, of which most were launches
-// (20 -> 6). At 1M the counting takes 27, the column and total scans 16, the placement 44 and
-// the sort 40. Counting and placing issue VALU work for about half of their time.
+// the ranges), in us: 1M Gaussians at 1280x720 (6.9 M instances) 257 -> 126; eight views of 1M
+// (41.6 M) 1416 -> 623; 3M at 1920x1200 (35.9 M) 917 -> 541; a street map of 520k with a long
+// horizon (0.7 M) 149 -> 89; 10k at 256x192 (17.8 k) 99 -> 29, of which most were launches
+// (20 -> 6). At 1M the counting takes 27, the column and total scans 18, the placement 33 and
+// the sort 39. Counting and placing issue VALU work for more than half of their time; the sort
+// of a cell is a chain of LDS steps and barriers.
 //
 // The LDS counters bound the cells of a view (tile_lists_fit); larger images take the radix
 // path (binning.hip).
@@ -86,12 +88,16 @@ struct CellBase {
 // Blocks of 512 lanes: about 1024 pairs each (512 to 4096 blocks), since blocks of more pairs
 // end unevenly and spread their writes (3M Gaussians, 1920x1200: count and place 180 and 305 us
 // with 512 blocks, 113 and 152 with 2929; 8 x 1M at 1280x720: 137 and 300 with 1024, 109 and
-// 222 with 4096), while a block of fewer writes and reads its matrix row for little. Shared out
-// by the views' cells (a view's entries grow with its size) plus an even part (its pairs do
-// not), at least 256 pairs each. A view's count is a multiple of eight (xcd_block).
+// 222 with 4096), while a block of fewer writes and reads its matrix row for little; but no
+// more than make kTlMatrix matrix entries (3M at 3840x2160: a render of 4211 us without this
+// bound, 3526 with it). Shared out by the views' cells (a view's entries grow with its size)
+// plus an even part (its pairs do not), at least 256 pairs each. A view's count is a multiple
+// of eight (xcd_block).
+constexpr int64_t kTlMatrix = int64_t(8) << 20;
 static CellBase cell_base(const ViewsArg& va, int32_t N) {
   CellBase b{};
-  const int64_t cells = cells_total(va, b.cell), grid = std::clamp<int64_t>((int64_t)va.n * N / 1024, 512, 4096);
+  const int64_t cells = cells_total(va, b.cell), most_rows = kTlMatrix * va.n / cells,
+                grid = std::clamp<int64_t>((int64_t)va.n * N / 1024, 512, std::clamp<int64_t>(most_rows, 512, 4096));
   const int64_t fewest = ((int64_t)N + kTlMaxPairs - 1) / kTlMaxPairs, most = std::max<int64_t>(1, ((int64_t)N + 255) / 256);
   int64_t words = 0;
   for (int v = 0; v < va.n; ++v) {
@@ -527,7 +533,7 @@ k_cell_offsets(ViewsArg va, CellBase cb, int32_t n_cells, int64_t cap, uint2* __
     atomicMax(overflow + 2, total);
   }
   if (blockIdx.x == 0 && threadIdx.x < 2 && split_counts)
-    split_counts[threadIdx.x] = 0u;  // (k_cell_sort takes the long lists)
+    split_counts[threadIdx.x] = 0u;  // (k_cell_sort_small takes the long lists)
 #pragma unroll
   for (int k = 0; k < kTlOffPer; ++k) {
     const int i = t0 + k;
