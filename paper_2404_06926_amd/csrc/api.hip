@@ -229,6 +229,7 @@ gs_status grow_capacity(gs_map* m, int64_t need, hipStream_t s) {
 // Buffers for nc instances: those of the lists by counting, or (sorted) of the tile sort, whose
 // temporary the depth sort of vn pairs shares.
 gs_status ensure_instances(gs_map* m, int64_t nc, bool sorted, int64_t vn, hipStream_t s) {
+  nc = std::min(nc, kMostInstances);
   GS_TRY(ensure(m, m->list_g, (size_t)nc * 4, s));
   if (!sorted) {
     GS_TRY(ensure(m, m->tl_entries, (size_t)nc * 8, s));
@@ -713,7 +714,8 @@ gs_status gs_render(gs_map* m, int32_t nv, const gs_view* views, const gs_frame*
     GS_HIP(hipMemcpyAsync(m->h_pinned, m->d_ninst, 4, hipMemcpyDeviceToHost, s));
     GS_HIP(hipStreamSynchronize(s));
     const int64_t need = m->h_pinned[0];
-    const int64_t cap = need > m->inst_cap ? std::max<int64_t>(need + need / 4, 1 << 16) : m->inst_cap;
+    if (need > kMostInstances) return fail(GS_ERR_CAPACITY, "the render needs 2^32 instances or more");
+    const int64_t cap = need > m->inst_cap ? planned_capacity(need) : m->inst_cap;
     GS_TRY(ensure_instances(m, cap, sorted, vn, s));
     // a deterministic render of more instances than an entry's id holds takes the tile sort
     if (!sorted && !tile_lists_fit(va, N, m->deterministic ? need : 0)) return gs_render(m, nv, views, frames, stream);

@@ -15,8 +15,8 @@
 // Stability makes the result identical to sorting the 64-bit keys tile << 32 | depth bits
 // with ties in emission order, at about a fifth of the bytes.
 // Kernels that depend on the instance count read it from device memory, so the sequence
-// has host-known launch shapes (graph-capturable). Instances beyond the buffer capacity
-// are dropped and flagged; the render is then empty.
+// has host-known launch shapes (graph-capturable). A render of more instances than the
+// buffers hold drops them all and is flagged; it is then empty.
 #include "gs_common.h"
 #include "kernels.h"
 
@@ -81,12 +81,12 @@ __device__ __forceinline__ void scan_share(int64_t n, int G, int64_t& t0, int64_
 // the end read the last element (clamped, so they need no branch) and count as zero.
 template <bool GATHER>
 __global__ void __launch_bounds__(kScanBlock)
-k_scan_up(const uint32_t* __restrict__ in, const uint32_t* __restrict__ idx, int64_t n, uint32_t* __restrict__ sums,
+k_scan_up(const uint32_t* __restrict__ in, const uint32_t* __restrict__ idx, int64_t n, uint64_t* __restrict__ sums,
           int G, uint32_t* __restrict__ gathered) {
-  __shared__ uint32_t s_warp[kScanBlock / 64];
+  __shared__ uint64_t s_sum[kScanBlock / 64];
   int64_t t0, t1;
   scan_share(n, G, t0, t1);
-  uint32_t tsum = 0;
+  uint64_t tsum = 0;
   for (int64_t t = t0; t < t1; ++t) {
     const int64_t base = t * kScanTile + (int64_t)threadIdx.x;
     uint32_t ix[kScanItems], v[kScanItems];
@@ -108,27 +108,28 @@ k_scan_up(const uint32_t* __restrict__ in, const uint32_t* __restrict__ idx, int
       tsum += v[k];
     }
   }
-  uint32_t total;
-  block_exclusive_scan(tsum, s_warp, total);
-  if (threadIdx.x == 0) sums[blockIdx.x] = total;
+  tsum = block_sum64<kScanBlock>(tsum, s_sum);
+  if (threadIdx.x == 0) sums[blockIdx.x] = tsum;
 }
 
-// total (optional): the sum of all elements, written by the last block. block_start
+// total (optional): the sum of all elements as an instance count (instance_word), written by
+// the last block; the scan itself is modulo 2^32. block_start
 // (optional): the emission blocks' first pairs, for instances below bs_cap.
 __global__ void __launch_bounds__(kScanBlock)
 k_scan_down(const uint32_t* __restrict__ in, const uint32_t* __restrict__ idx, uint32_t* __restrict__ out, int64_t n,
-            const uint32_t* __restrict__ sums, int G, uint32_t* __restrict__ total_out,
+            const uint64_t* __restrict__ sums, int G, uint32_t* __restrict__ total_out,
             uint32_t* __restrict__ block_start, int64_t bs_cap) {
   __shared__ uint32_t s_warp[kScanBlock / 64];
+  __shared__ uint64_t s_sum[kScanBlock / 64];
   // start of this block's run: the sums of the blocks before it (G <= 4096: 16 per thread)
-  uint32_t before = 0;
+  uint64_t before = 0;
 #pragma unroll
   for (int k = 0; k < kScanGrid / kScanBlock; ++k) {
     const int b = (int)threadIdx.x + k * kScanBlock;
     if (b < (int)blockIdx.x) before += sums[b];
   }
-  uint32_t carry;
-  block_exclusive_scan(before, s_warp, carry);
+  before = block_sum64<kScanBlock>(before, s_sum);
+  uint32_t carry = (uint32_t)before;
   int64_t t0, t1;
   scan_share(n, G, t0, t1);
   for (int64_t t = t0; t < t1; ++t) {
@@ -173,22 +174,24 @@ k_scan_down(const uint32_t* __restrict__ in, const uint32_t* __restrict__ idx, u
     }
     carry += tile_total;
   }
-  if (total_out && blockIdx.x == (unsigned)(G - 1) && threadIdx.x == 0) total_out[0] = carry;
+  if (total_out && blockIdx.x == (unsigned)(G - 1) && threadIdx.x == 0)
+    total_out[0] = instance_word(before + sums[G - 1]);
 }
 
-// block sums, then room for n gathered values
-int64_t scan_temp_elems(int64_t n) { return kScanGrid + n + 1; }
+// block sums (8 B each), then room for n gathered values
+int64_t scan_temp_elems(int64_t n) { return 2 * kScanGrid + n + 1; }
 
 static hipError_t scan_impl(const uint32_t* in, const uint32_t* idx, uint32_t* out, int64_t n, uint32_t* temp,
                             uint32_t* total, uint32_t* block_start, int64_t bs_cap, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int G = scan_grid(n);
-  uint32_t* gathered = temp + kScanGrid;
+  uint64_t* sums = (uint64_t*)temp;
+  uint32_t* gathered = temp + 2 * kScanGrid;
   if (idx)
-    hipLaunchKernelGGL(k_scan_up<true>, dim3(G), dim3(kScanBlock), 0, s, in, idx, n, temp, G, gathered);
+    hipLaunchKernelGGL(k_scan_up<true>, dim3(G), dim3(kScanBlock), 0, s, in, idx, n, sums, G, gathered);
   else
-    hipLaunchKernelGGL(k_scan_up<false>, dim3(G), dim3(kScanBlock), 0, s, in, idx, n, temp, G, gathered);
-  hipLaunchKernelGGL(k_scan_down, dim3(G), dim3(kScanBlock), 0, s, idx ? gathered : in, nullptr, out, n, temp, G, total,
+    hipLaunchKernelGGL(k_scan_up<false>, dim3(G), dim3(kScanBlock), 0, s, in, idx, n, sums, G, gathered);
+  hipLaunchKernelGGL(k_scan_down, dim3(G), dim3(kScanBlock), 0, s, idx ? gathered : in, nullptr, out, n, sums, G, total,
                      bs_cap > 0 ? block_start : nullptr, bs_cap);
   return hipGetLastError();
 }
@@ -481,8 +484,9 @@ hipError_t radix_sort_u32(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* 
 // rectangle). A pair whose rectangle has more than 64 tiles (no mask) is emitted whole by
 // the block where its instances start: after the block's own slots, one wave per such pair
 // evaluates the tile predicate over the rectangle and places the hits with a ballot prefix
-// sum (the blocks its instances reach further on skip them). Instances past the capacity
-// are not written; the overflow flag is raised and the render is emptied downstream.
+// sum (the blocks its instances reach further on skip them). With more instances
+// than the capacity none is written; the overflow flag is raised and the render is emptied
+// downstream.
 constexpr int kLbGroups = kLb / 64;            // 64-slot mark groups per block
 
 // block_start[b] = the pair that owns instance kLb b (as the scan of the counts marks them).
@@ -513,9 +517,11 @@ k_dup_lb(const float4* __restrict__ rec, const uint32_t* __restrict__ order, con
   const int64_t total = n_dev[0];
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     if (total > capacity) atomicOr(overflow, 1u);
-    atomicMax(overflow + 2, (uint32_t)total);  // the largest need since the last check
+    // the largest need since the last check
+    if (total != (int64_t)kTooManyInstances) atomicMax(overflow + 2, (uint32_t)total);
   }
-  const int64_t lim = min(total, capacity);
+  // a dropped render emits nothing (past 2^32 instances the offsets and marks wrapped around)
+  const int64_t lim = total > capacity ? 0 : total;
   const int64_t slot0 = (int64_t)blockIdx.x * kLb;
   if (slot0 >= lim) return;
   const int64_t k0 = block_start[blockIdx.x];
@@ -604,8 +610,6 @@ k_dup_lb(const float4* __restrict__ rec, const uint32_t* __restrict__ order, con
     emit_g[slot] = gid;
   }
   // the pairs with more than 64 candidate tiles that start in this block, one wave each
-  // (none when the instances overflow: the render is dropped)
-  if (total > capacity) return;
   const int nbig = s_nbig;
   const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;  // lanes under this one
   for (int q = wid; q < nbig; q += kLbThreads / 64) {
@@ -667,18 +671,20 @@ hipError_t duplicate_keys(const float4* rec, const uint32_t* counts, const uint3
   return hipGetLastError();
 }
 
-// Gaussian index of every instance in blend order (for inspection).
+// Gaussian index of every instance in blend order.
 __global__ void __launch_bounds__(256)
 k_gather_g(const uint32_t* __restrict__ vals, const uint32_t* __restrict__ emit_g, const uint32_t* __restrict__ n_dev,
            int64_t cap, uint32_t* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < sort_count(n_dev, cap)) out[i] = emit_g[vals[i]];
+  const int64_t n = sort_count(n_dev, cap), step = (int64_t)gridDim.x * 256;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += step) out[i] = emit_g[vals[i]];
 }
 
 hipError_t gather_gaussians(const uint32_t* vals, const uint32_t* emit_g, const uint32_t* n_dev, int64_t cap,
                             uint32_t* out, hipStream_t s) {
   if (cap <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_g, dim3((unsigned)((cap + 255) / 256)), dim3(256), 0, s, vals, emit_g, n_dev, cap, out);
+  // (a launch holds less than 2^32 lanes)
+  const int64_t blocks = std::min<int64_t>((cap + 255) / 256, int64_t(1) << 23);
+  hipLaunchKernelGGL(k_gather_g, dim3((unsigned)blocks), dim3(256), 0, s, vals, emit_g, n_dev, cap, out);
   return hipGetLastError();
 }
 

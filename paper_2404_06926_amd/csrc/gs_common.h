@@ -46,6 +46,20 @@ struct ViewDev {
   const float* dl_dopac;    // H x W (backward, may be nullptr)
 };
 
+// Instance counts are 32-bit words. A render that needs 2^32 - 1 instances or more holds
+// kTooManyInstances there, which is above every capacity: a count that wrapped around would
+// look as if it fitted while the lists are laid out for the true one.
+constexpr uint32_t kTooManyInstances = 0xffffffffu;
+constexpr int64_t kMostInstances = (int64_t)kTooManyInstances - 1;  // largest capacity
+__host__ __device__ constexpr uint32_t instance_word(uint64_t total) {
+  return total < kTooManyInstances ? (uint32_t)total : kTooManyInstances;
+}
+// Capacity that a planned render of `need` instances grows to: a quarter to spare.
+constexpr int64_t planned_capacity(int64_t need) {
+  const int64_t c = need + need / 4, least = int64_t(1) << 16;
+  return c < least ? least : c < kMostInstances ? c : kMostInstances;
+}
+
 struct ViewsArg {
   int32_t n;
   int32_t total_tiles;
@@ -118,6 +132,19 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Sum over a block of NT lanes, in every lane.
+template <int NT>
+__device__ __forceinline__ uint64_t block_sum64(uint64_t x, uint64_t* s_wave) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x += (uint64_t)__shfl_xor((unsigned long long)x, o, 64);
+  if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x >> 6] = x;
+  __syncthreads();
+  x = 0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) x += s_wave[w];
+  return x;
 }
 
 // position of the r-th set bit (r counted from 0) of a 32-bit word that has more than r

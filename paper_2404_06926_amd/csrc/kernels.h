@@ -56,15 +56,15 @@ hipError_t project_backward(int deg, float* P, float* G, int64_t cap, int32_t N,
 // binning (binning.hip)
 int64_t scan_temp_elems(int64_t n);
 hipError_t exclusive_scan(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* temp, hipStream_t s);
-// offsets[k] = sum of counts[order[j]] for j < k; total = sum of all. With capacity > 0 it
+// offsets[k] = sum of counts[order[j]] for j < k; total = sum of all (instance_word). With capacity > 0 it
 // also writes block_start (block_start_elems(capacity) words) for duplicate_keys, as for
 // that capacity.
 hipError_t scan_counts(const uint32_t* counts, const uint32_t* order, uint32_t* offsets, int64_t n,
                        uint32_t* temp, uint32_t* total, uint32_t* block_start, int64_t capacity, hipStream_t s);
 // Instances in depth order, one lane per instance (block_start: block_start_elems(capacity)
 // words); a pair with more than 64 candidate tiles is emitted by one wave.
-// overflow[0] |= 1 when the instances exceed the capacity; overflow[2] = max(overflow[2],
-// instance count).
+// overflow[0] |= 1 when the instances exceed the capacity (none is written then);
+// overflow[2] = max(overflow[2], instance count), unless that is kTooManyInstances.
 // With all_off, inst_off receives every pair's first emission index (the deterministic
 // backward reads it). starts_marked: scan_counts wrote block_start for this capacity;
 // otherwise a launch of its own writes it.
@@ -89,7 +89,7 @@ struct SplitArg;
 // pairs: the projection's pair words. space: tile_space_bytes (16-B aligned).
 bool tile_lists_fit(const ViewsArg& va, int64_t N, int64_t max_instances);
 int64_t tile_space_bytes(const ViewsArg& va, int32_t N);
-// Tile ranges and *n_inst; overflow as in duplicate_keys, the ranges being empty when more
+// Tile ranges and *n_inst (instance_word of the sum); overflow as in duplicate_keys, the ranges being empty when more
 // than cap instances are needed. split_counts: the split's counters (or nullptr), cleared.
 hipError_t tile_lists_plan(const float4* rec, const uint4* pairs, int32_t N, const ViewsArg& va, void* space,
                            int64_t cap, uint2* ranges, uint32_t* n_inst, uint32_t* overflow, uint32_t* split_counts,

@@ -478,13 +478,14 @@ __device__ __forceinline__ int sort_chunks(uint32_t n) { return (int)((n + kSort
 // Exclusive scans of the tiles' hits to ranges (zero for empty tiles) and the instance count,
 // and of the cells' entries to their starts; the work items of cells past the small size.
 // With more than `cap` instances the render is dropped (empty ranges and cells, overflow[0] |=
-// 1). overflow[2] keeps the largest need. Every block sums all tiles for the total and for what
+// 1); the total is formed in 64 bits, since a wrapped one could fit. overflow[2] keeps the
+// largest need that a count holds. Every block sums all tiles for the total and for what
 // lies before its own kTlOffPer x 1024 tiles and cells (one block alone took 32 us for the
 // 28800 tiles of eight 1280x720 views and 7 for one; now 15 and 6, with the cells' lists).
 constexpr int kTlOffThreads = 1024;
 constexpr int kTlOffPer = 2;
-// This lane's sums of x[0 .. n) and of the first `before` of them.
-__device__ __forceinline__ void sum_before(const uint32_t* __restrict__ x, int n, int before, uint32_t& all,
+// This lane's sums of x[0 .. n), and of the first `before` of them.
+__device__ __forceinline__ void sum_before(const uint32_t* __restrict__ x, int n, int before, uint64_t& all,
                                            uint32_t& pre) {
   for (int i0 = (int)threadIdx.x; i0 < n; i0 += 8 * kTlOffThreads) {
     uint32_t y[8];
@@ -505,10 +506,12 @@ k_cell_offsets(ViewsArg va, CellBase cb, int32_t n_cells, int64_t cap, uint2* __
                uint32_t* __restrict__ n_inst, uint32_t* __restrict__ overflow, uint32_t* __restrict__ split_counts,
                TlSpace ws) {
   __shared__ uint32_t s_warp[kTlOffThreads / 64];
+  __shared__ uint64_t s_sum[kTlOffThreads / 64];
   const int n_tiles = va.total_tiles;
   const int first = (int)blockIdx.x * kTlOffThreads * kTlOffPer;
   const int t0 = first + (int)threadIdx.x * kTlOffPer;
-  uint32_t all = 0, pre = 0, call = 0, cpre = 0;
+  uint64_t all = 0, call = 0;
+  uint32_t pre = 0, cpre = 0;
   uint32_t x[kTlOffPer], c[kTlOffPer], xs = 0, cs = 0;
 #pragma unroll
   for (int k = 0; k < kTlOffPer; ++k) {
@@ -520,17 +523,18 @@ k_cell_offsets(ViewsArg va, CellBase cb, int32_t n_cells, int64_t cap, uint2* __
   sum_before(ws.totals, n_tiles, first, all, pre);
   sum_before(ws.sizes, min(n_cells, first), first, call, cpre);
   // the sums over the block's lanes, then the lanes' places in the block's own run
-  uint32_t total = 0, at = 0, cell_at = 0;
-  block_scan<kTlOffThreads>(all, s_warp, total);
+  const uint64_t total = block_sum64<kTlOffThreads>(all, s_sum);
+  uint32_t at = 0, cell_at = 0;
   block_scan<kTlOffThreads>(pre, s_warp, at);
   block_scan<kTlOffThreads>(cpre, s_warp, cell_at);
   uint32_t run = block_scan<kTlOffThreads>(xs, s_warp, at) - xs;
   uint32_t crun = block_scan<kTlOffThreads>(cs, s_warp, cell_at) - cs;
-  const bool dropped = (int64_t)total > cap;
+  const uint32_t count = instance_word(total);
+  const bool dropped = (int64_t)total > cap || count == kTooManyInstances;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    n_inst[0] = total;
-    if (dropped) atomicOr(overflow, 1u);
-    atomicMax(overflow + 2, total);
+    n_inst[0] = count;
+    if ((int64_t)total > cap) atomicOr(overflow, 1u);
+    if (count != kTooManyInstances) atomicMax(overflow + 2, count);
   }
   if (blockIdx.x == 0 && threadIdx.x < 2 && split_counts)
     split_counts[threadIdx.x] = 0u;  // (k_cell_sort_small takes the long lists)
