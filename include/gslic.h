@@ -341,7 +341,8 @@ gs_status gs_debug_last_render(gs_map* map, void* stream, const uint32_t** tiles
  * whose render dropped instances is skipped: the parameters, their Adam moments, the
  * exposures and the Adam step count are left as they were (its loss value is not
  * meaningful). Counts are 32-bit: a render of 2^32 - 1 instances or more is dropped at every
- * capacity, and with sync_plan = 1 it returns GS_ERR_CAPACITY. */
+ * capacity, and with sync_plan = 1 it returns GS_ERR_CAPACITY. A capacity above the held one
+ * replaces the buffers: the last render has no backward any more. */
 gs_status gs_set_instance_policy(gs_map* map, int32_t sync_plan, int64_t capacity);
 
 /* Synchronise `stream` and report whether any render since the last check dropped

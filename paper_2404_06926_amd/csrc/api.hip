@@ -113,7 +113,7 @@ struct gs_map {
   bool have_render = false;
   ViewsArg last_va{};
   int32_t last_N = 0;
-  const uint32_t* last_list_e = nullptr;  // emission index per instance (deterministic renders)
+  const DevBuf* last_e = nullptr;  // emission index per instance (deterministic renders)
   bool last_det = false;       // the last render wrote what the deterministic backward reads
   // keyframe window
   std::vector<KeyframeSlot> kf;
@@ -226,10 +226,7 @@ gs_status grow_capacity(gs_map* m, int64_t need, hipStream_t s) {
   return GS_OK;
 }
 
-// Buffers for nc instances: those of the lists by counting, or (sorted) of the tile sort, whose
-// temporary the depth sort of vn pairs shares.
-gs_status ensure_instances(gs_map* m, int64_t nc, bool sorted, int64_t vn, hipStream_t s) {
-  nc = std::min(nc, kMostInstances);
+gs_status instance_buffers(gs_map* m, int64_t nc, bool sorted, int64_t vn, hipStream_t s) {
   GS_TRY(ensure(m, m->list_g, (size_t)nc * 4, s));
   if (!sorted) {
     GS_TRY(ensure(m, m->tl_entries, (size_t)nc * 8, s));
@@ -251,8 +248,19 @@ gs_status ensure_instances(gs_map* m, int64_t nc, bool sorted, int64_t vn, hipSt
     GS_TRY(ensure(m, m->block_start, (size_t)block_start_elems(nc) * 4, s));
     GS_TRY(ensure(m, m->sort_tmp, (size_t)sort_temp_elems(std::max<int64_t>(nc, vn)) * 4, s));
   }
-  if (nc > m->inst_cap) m->inst_cap = nc;
   return GS_OK;
+}
+
+// Buffers for nc instances: those of the lists by counting, or (sorted) of the tile sort, whose
+// temporary the depth sort of vn pairs shares.
+gs_status ensure_instances(gs_map* m, int64_t nc, bool sorted, int64_t vn, hipStream_t s) {
+  nc = std::min(nc, kMostInstances);
+  const uint64_t epoch = m->epoch;
+  const gs_status st = instance_buffers(m, nc, sorted, vn, s);
+  // the lists of the last render went with a buffer that was replaced
+  if (m->epoch != epoch) m->have_render = false;
+  if (st == GS_OK && nc > m->inst_cap) m->inst_cap = nc;
+  return st;
 }
 
 SplitArg split_arg(gs_map* m, int64_t tiles) {
@@ -725,7 +733,7 @@ gs_status gs_render(gs_map* m, int32_t nv, const gs_view* views, const gs_frame*
   va.inst_cap = m->inst_cap;
   if (!sorted) {
     StageTimer t(m, s, GS_STAGE_DUPLICATE);
-    m->last_list_e = m->deterministic ? (const uint32_t*)m->list_e.ptr : nullptr;
+    m->last_e = &m->list_e;
     GS_HIP(tile_lists_build(rec, (const uint4*)m->tl_pairs.ptr, dkey[0], inst_off, N, va, m->tl_space.ptr, ranges,
                             (uint64_t*)m->tl_entries.ptr, (uint64_t*)m->tl_groups.ptr, (uint32_t*)m->emit_g.ptr,
                             (uint32_t*)m->list_g.ptr, m->deterministic ? (uint32_t*)m->list_e.ptr : nullptr, m->last_sp, s));
@@ -744,7 +752,7 @@ gs_status gs_render(gs_map* m, int32_t nv, const gs_view* views, const gs_frame*
       StageTimer t(m, s, GS_STAGE_SORT);
       GS_HIP(radix_sort_u32(keys, vals, m->d_ninst, m->inst_cap, bits_for(tiles + 1), (uint32_t*)m->sort_tmp.ptr,
                             &which, s, true));
-      m->last_list_e = vals[which];
+      m->last_e = &m->vals[which];
       GS_HIP(gather_gaussians(vals[which], (const uint32_t*)m->emit_g.ptr, m->d_ninst, m->inst_cap,
                               (uint32_t*)m->list_g.ptr, s));
     }
@@ -803,12 +811,13 @@ static gs_status backward_impl(gs_map* m, int32_t nv, const float* const* dL_drg
     StageTimer t(m, s, GS_STAGE_BLEND_BACKWARD);
     // deterministic when the render was (it wrote every pair's first emission index)
     float* ig = m->last_det ? (float*)m->inst_grad.ptr : nullptr;
+    const uint32_t* list_e = m->last_det ? (const uint32_t*)m->last_e->ptr : nullptr;
     if (m->bwd_mode == 1 && !maps)
-      GS_HIP(blend_backward_per_gaussian(va, rec, N, (const uint32_t*)m->list_g.ptr, m->last_list_e,
+      GS_HIP(blend_backward_per_gaussian(va, rec, N, (const uint32_t*)m->list_g.ptr, list_e,
                                          (const uint2*)m->ranges.ptr, g2d, ig,
                                          (float*)m->exp_part.ptr, m->last_sp, s));
     else
-      GS_HIP(blend_backward(va, rec, N, (const uint32_t*)m->list_g.ptr, m->last_list_e,
+      GS_HIP(blend_backward(va, rec, N, (const uint32_t*)m->list_g.ptr, list_e,
                             (const uint2*)m->ranges.ptr, g2d, ig, (float*)m->exp_part.ptr, m->last_sp,
                             m->bwd_px, s));
   }
