@@ -634,37 +634,44 @@ gs_status gs_render(gs_map* m, int32_t nv, const gs_view* views, const gs_frame*
   va.total_tiles = (int32_t)tiles;
   const int32_t N = (int32_t)m->n;
   const int64_t vn = (int64_t)nv * N;
-  // workspace
-  GS_TRY(ensure(m, m->rec, (size_t)std::max<int64_t>(vn, 1) * kRecFloats * 4, s));
-  GS_TRY(ensure(m, m->counts, (size_t)std::max<int64_t>(vn, 1) * 4, s));
+  // workspace; from the first of its buffers that is replaced on, and from the first launch on,
+  // the render before this one is gone
+  const uint64_t epoch = m->epoch;
+  auto sized = [&](DevBuf& b, size_t bytes, bool zero = false) {
+    const gs_status st = ensure(m, b, bytes, s, zero);
+    if (m->epoch != epoch) m->have_render = false;
+    return st;
+  };
+  GS_TRY(sized(m->rec, (size_t)std::max<int64_t>(vn, 1) * kRecFloats * 4));
+  GS_TRY(sized(m->counts, (size_t)std::max<int64_t>(vn, 1) * 4));
   // the lists by counting, or by sorting where a view has more tiles than they take
   const bool sorted = !tile_lists_fit(va, N, m->deterministic ? std::max<int64_t>(m->inst_cap, vn) : 0);
   if (sorted) {
-    GS_TRY(ensure(m, m->offsets, (size_t)std::max<int64_t>(vn, 1) * 4, s));
-    GS_TRY(ensure(m, m->dkey[1], (size_t)std::max<int64_t>(vn, 1) * 4, s));
-    for (int b = 0; b < 2; ++b) GS_TRY(ensure(m, m->dval[b], (size_t)std::max<int64_t>(vn, 1) * 4, s));
-    GS_TRY(ensure(m, m->sort_tmp,
-                  (size_t)sort_temp_elems(std::max<int64_t>(std::max<int64_t>(vn, m->inst_cap), 1)) * 4, s));
+    GS_TRY(sized(m->offsets, (size_t)std::max<int64_t>(vn, 1) * 4));
+    GS_TRY(sized(m->dkey[1], (size_t)std::max<int64_t>(vn, 1) * 4));
+    for (int b = 0; b < 2; ++b) GS_TRY(sized(m->dval[b], (size_t)std::max<int64_t>(vn, 1) * 4));
+    GS_TRY(sized(m->sort_tmp,
+                 (size_t)sort_temp_elems(std::max<int64_t>(std::max<int64_t>(vn, m->inst_cap), 1)) * 4));
   } else {
-    GS_TRY(ensure(m, m->tl_pairs, (size_t)std::max<int64_t>(vn, 1) * 16, s));
-    GS_TRY(ensure(m, m->tl_space, (size_t)tile_space_bytes(va, N), s));
+    GS_TRY(sized(m->tl_pairs, (size_t)std::max<int64_t>(vn, 1) * 16));
+    GS_TRY(sized(m->tl_space, (size_t)tile_space_bytes(va, N)));
   }
   if (sorted || m->deterministic) {
-    GS_TRY(ensure(m, m->scan_tmp, (size_t)scan_temp_elems(std::max<int64_t>(vn, 1)) * 4, s));
-    GS_TRY(ensure(m, m->inst_off, (size_t)std::max<int64_t>(vn, 1) * 4, s));
+    GS_TRY(sized(m->scan_tmp, (size_t)scan_temp_elems(std::max<int64_t>(vn, 1)) * 4));
+    GS_TRY(sized(m->inst_off, (size_t)std::max<int64_t>(vn, 1) * 4));
   }
-  GS_TRY(ensure(m, m->g2d, (size_t)std::max<int64_t>(vn, 1) * kGradFloats * 4, s, true));
-  GS_TRY(ensure(m, m->dkey[0], (size_t)std::max<int64_t>(vn, 1) * 4, s));
-  GS_TRY(ensure(m, m->exp_part, (size_t)std::max<int64_t>(tiles, 1) * 12 * 4, s));
-  GS_TRY(ensure(m, m->ranges, (size_t)tiles * 8 + 16, s));  // + the split counters
+  GS_TRY(sized(m->g2d, (size_t)std::max<int64_t>(vn, 1) * kGradFloats * 4, true));
+  GS_TRY(sized(m->dkey[0], (size_t)std::max<int64_t>(vn, 1) * 4));
+  GS_TRY(sized(m->exp_part, (size_t)std::max<int64_t>(tiles, 1) * 12 * 4));
+  GS_TRY(sized(m->ranges, (size_t)tiles * 8 + 16));  // + the split counters
   if (m->split_par > 0) {
     const size_t par = (size_t)m->split_par;
-    GS_TRY(ensure(m, m->split_slot, (size_t)std::max<int64_t>(tiles, 1) * 4, s));
-    GS_TRY(ensure(m, m->split_extra, par * 8, s));
-    GS_TRY(ensure(m, m->split_state, 2 * par * kSplitFields * kTile * kTile * 4, s));
+    GS_TRY(sized(m->split_slot, (size_t)std::max<int64_t>(tiles, 1) * 4));
+    GS_TRY(sized(m->split_extra, par * 8));
+    GS_TRY(sized(m->split_state, 2 * par * kSplitFields * kTile * kTile * 4));
   }
-  GS_TRY(ensure(m, m->pixT, (size_t)pix * 4, s));
-  GS_TRY(ensure(m, m->pixN, (size_t)pix * 4, s));
+  GS_TRY(sized(m->pixT, (size_t)pix * 4));
+  GS_TRY(sized(m->pixN, (size_t)pix * 4));
   for (int v = 0; v < nv; ++v) {
     ViewDev& d = va.v[v];
     d.out_rgb = frames[v].rgb;
@@ -673,6 +680,7 @@ gs_status gs_render(gs_map* m, int32_t nv, const gs_view* views, const gs_frame*
     d.out_depth = frames[v].depth;
     d.out_opac = frames[v].opacity;
   }
+  if (!m->capturing) m->have_render = false;
   float4* rec = (float4*)m->rec.ptr;
   uint32_t* counts = (uint32_t*)m->counts.ptr;
   uint32_t* offsets = (uint32_t*)m->offsets.ptr;

@@ -47,3 +47,45 @@ def test_growing_the_instance_buffers_ends_the_render(width, deterministic):
     torch.cuda.synchronize()
     if deterministic:
         assert torch.equal(m.grads(), want)
+
+
+# A render that fails for memory: with its first buffer, which leaves the render before it as
+# it was, and after some were replaced (a larger view, on a map of one small render)
+@pytest.mark.parametrize("granted", [0, 1, 3])
+@pytest.mark.parametrize("deterministic", [False, True])
+def test_a_render_that_fails_for_memory_ends_the_one_before(granted, deterministic, monkeypatch):
+    torch = torch_mod()
+    left = [1 << 30]
+    alloc = gslic.TorchAllocator._do_alloc
+
+    def rationed(self, nbytes, stream, ctx):
+        left[0] -= 1
+        return alloc(self, nbytes, stream, ctx) if left[0] >= 0 else None
+
+    monkeypatch.setattr(gslic.TorchAllocator, "_do_alloc", rationed)
+    cam, params = _scene()
+    views = [cam, scenes.pinhole(320, 240, 260.0), scenes.pinhole(300, 200, 260.0)]
+    m = gpu_map(params, 1)
+    m.set_deterministic(deterministic)
+    g = [torch.ones(3, cam.height, cam.width, device="cuda")]
+    m.render([cam])
+    m.render_backward(g)
+    torch.cuda.synchronize()
+    want = m.grads().clone()
+    m.adam_step()
+    torch.cuda.synchronize()
+    m = gpu_map(params, 1)
+    m.set_deterministic(deterministic)
+    m.render([cam])
+    left[0] = granted
+    print(f"{granted} buffers granted, deterministic {deterministic}", flush=True)
+    _refused(lambda: m.render(views), gslic.GS_ERR_OOM)
+    left[0] = 1 << 30
+    if granted:
+        _refused(lambda: m.render_backward(g))
+        _refused(m.debug_last_render)
+        m.render([cam])
+    m.render_backward(g)
+    torch.cuda.synchronize()
+    if deterministic:
+        assert torch.equal(m.grads(), want)
