@@ -83,12 +83,19 @@ struct gs_map {
   int64_t h_step = 0;
   int64_t resident = 0;
   // workspace
-  DevBuf rec, counts, offsets, scan_tmp, g2d, keys[2], vals[2], sort_tmp, ranges, pixT, pixN, loss_tmp;
+  DevBuf rec, counts, offsets, scan_tmp, g2d, sort_tmp, ranges, pixT, pixN, loss_tmp;
   DevBuf dkey[2], dval[2];     // depth-sort keys / (view, Gaussian) ids, double-buffered
-  DevBuf list_g, list_e;       // per instance in blend order: its Gaussian; its emission index (deterministic)
-  DevBuf tl_pairs, tl_space, tl_entries, tl_groups;  // tile lists by counting (tilelist.hip)
-  DevBuf emit_g, inst_off;     // Gaussian of each emission index; first emission index per pair
-  DevBuf block_start;           // instance-parallel binning: first pair per emission block
+  // per instance, shared by the two ways to the tile lists (20 B, whichever a render takes):
+  //               by counting (tilelist.hip)       by sorting (binning.hip)
+  //   inst_a      entries                          tile keys, two halves (sorted_half)
+  //   inst_b      chunks' groups                   emission indices, two halves
+  //   inst_c      Gaussians in blend order         Gaussian of each emission index
+  // (by sorting, the Gaussians in blend order are put where the other half's keys were)
+  DevBuf inst_a, inst_b, inst_c;
+  DevBuf list_e, emit_g;       // deterministic, by counting: emission index of each instance; its Gaussian
+  DevBuf inst_off;             // first emission index per pair
+  DevBuf tl_pairs, tl_space;   // tile lists by counting: pair words; counting matrices
+  DevBuf block_start;          // instance-parallel binning: first pair per emission block
   DevBuf split_slot, split_extra, split_state;  // long lists cut into chunks (blend)
   DevBuf inst_grad, exp_part;  // deterministic backward: per-instance gradients, per-tile exposure sums
   DevBuf dbg_t;                // tile of each instance in blend order (inspection only)
@@ -113,7 +120,7 @@ struct gs_map {
   bool have_render = false;
   ViewsArg last_va{};
   int32_t last_N = 0;
-  const DevBuf* last_e = nullptr;  // emission index per instance (deterministic renders)
+  int last_half = -1;          // half of inst_a and inst_b with its sorted instances; -1: lists by counting
   bool last_det = false;       // the last render wrote what the deterministic backward reads
   // keyframe window
   std::vector<KeyframeSlot> kf;
@@ -226,39 +233,41 @@ gs_status grow_capacity(gs_map* m, int64_t need, hipStream_t s) {
   return GS_OK;
 }
 
-gs_status instance_buffers(gs_map* m, int64_t nc, bool sorted, int64_t vn, hipStream_t s) {
-  GS_TRY(ensure(m, m->list_g, (size_t)nc * 4, s));
-  if (!sorted) {
-    GS_TRY(ensure(m, m->tl_entries, (size_t)nc * 8, s));
-    GS_TRY(ensure(m, m->tl_groups, (size_t)nc * 8, s));
-  }
+size_t half_bytes(int64_t nc) { return ((size_t)nc * 4 + 255) & ~size_t(255); }
+// Half `h` of a buffer of two words per instance.
+uint32_t* sorted_half(const gs_map* m, const DevBuf& b, int h) {
+  return (uint32_t*)((char*)b.ptr + h * half_bytes(m->inst_cap));
+}
+// The last render's Gaussians in blend order, and their emission indices (deterministic).
+uint32_t* last_list_g(const gs_map* m) {
+  return m->last_half < 0 ? (uint32_t*)m->inst_c.ptr : sorted_half(m, m->inst_a, m->last_half ^ 1);
+}
+uint32_t* last_list_e(const gs_map* m) {
+  return m->last_half < 0 ? (uint32_t*)m->list_e.ptr : sorted_half(m, m->inst_b, m->last_half);
+}
+
+gs_status instance_buffers(gs_map* m, int64_t nc, hipStream_t s) {
+  GS_TRY(ensure(m, m->inst_a, 2 * half_bytes(nc), s));
+  GS_TRY(ensure(m, m->inst_b, 2 * half_bytes(nc), s));
+  GS_TRY(ensure(m, m->inst_c, (size_t)nc * 4, s));
+  GS_TRY(ensure(m, m->block_start, (size_t)block_start_elems(nc) * 4, s));
+  GS_TRY(ensure(m, m->sort_tmp, (size_t)sort_temp_elems(nc) * 4, s));
   if (m->deterministic) {
     GS_TRY(ensure(m, m->inst_grad, (size_t)nc * 12 * 4, s));
-    if (!sorted) {
-      GS_TRY(ensure(m, m->list_e, (size_t)nc * 4, s));
-      GS_TRY(ensure(m, m->emit_g, (size_t)nc * 4, s));
-    }
-  }
-  if (sorted) {
-    for (int b = 0; b < 2; ++b) {
-      GS_TRY(ensure(m, m->keys[b], (size_t)nc * 4, s));
-      GS_TRY(ensure(m, m->vals[b], (size_t)nc * 4, s));
-    }
+    GS_TRY(ensure(m, m->list_e, (size_t)nc * 4, s));
     GS_TRY(ensure(m, m->emit_g, (size_t)nc * 4, s));
-    GS_TRY(ensure(m, m->block_start, (size_t)block_start_elems(nc) * 4, s));
-    GS_TRY(ensure(m, m->sort_tmp, (size_t)sort_temp_elems(std::max<int64_t>(nc, vn)) * 4, s));
   }
   return GS_OK;
 }
 
-// Buffers for nc instances: those of the lists by counting, or (sorted) of the tile sort, whose
-// temporary the depth sort of vn pairs shares.
-gs_status ensure_instances(gs_map* m, int64_t nc, bool sorted, int64_t vn, hipStream_t s) {
+// Buffers for nc instances, for either way to the lists: a capacity that is set before a render
+// or a capture holds for both.
+gs_status ensure_instances(gs_map* m, int64_t nc, hipStream_t s) {
   nc = std::min(nc, kMostInstances);
   const uint64_t epoch = m->epoch;
-  const gs_status st = instance_buffers(m, nc, sorted, vn, s);
-  // the lists of the last render went with a buffer that was replaced
-  if (m->epoch != epoch) m->have_render = false;
+  const gs_status st = instance_buffers(m, nc, s);
+  // the lists of the last render went with a buffer that was replaced, or lie in its halves
+  if (m->epoch != epoch || nc > m->inst_cap) m->have_render = false;
   if (st == GS_OK && nc > m->inst_cap) m->inst_cap = nc;
   return st;
 }
@@ -484,10 +493,10 @@ gs_status gs_destroy_map(gs_map* m) {
   dev_free(m, m->d_overflow, 64, s);
   dev_free(m, m->d_loss, 256, s);
   dev_free(m, m->d_nvn, 64, s);
-  DevBuf* bufs[] = {&m->rec, &m->counts, &m->offsets, &m->scan_tmp, &m->g2d, &m->keys[0], &m->keys[1],
-                    &m->vals[0], &m->vals[1], &m->sort_tmp, &m->ranges, &m->pixT, &m->pixN, &m->loss_tmp,
-                    &m->dkey[0], &m->dkey[1], &m->dval[0], &m->dval[1], &m->emit_g, &m->inst_off, &m->list_g, &m->list_e,
-                    &m->tl_pairs, &m->tl_space, &m->tl_entries, &m->tl_groups,
+  DevBuf* bufs[] = {&m->rec, &m->counts, &m->offsets, &m->scan_tmp, &m->g2d, &m->inst_a, &m->inst_b,
+                    &m->inst_c, &m->sort_tmp, &m->ranges, &m->pixT, &m->pixN, &m->loss_tmp,
+                    &m->dkey[0], &m->dkey[1], &m->dval[0], &m->dval[1], &m->emit_g, &m->inst_off, &m->list_e,
+                    &m->tl_pairs, &m->tl_space,
                     &m->block_start, &m->split_slot, &m->split_extra, &m->split_state,
                     &m->inst_grad, &m->exp_part, &m->dbg_t, &m->gr_rgb, &m->gr_T, &m->gr_flags,
                     &m->gr_off, &m->gr_tmp, &m->gr_d2, &m->ar_rgb, &m->ar_T, &m->ar_nc, &m->ar_dl,
@@ -706,7 +715,7 @@ gs_status gs_render(gs_map* m, int32_t nv, const gs_view* views, const gs_frame*
   if (!m->sync_plan && m->inst_cap == 0)
     return fail(GS_ERR_STATE, "sync_plan = 0 needs an instance capacity (gs_set_instance_policy)");
   // the instance buffers of the current capacity
-  if (m->inst_cap > 0) GS_TRY(ensure_instances(m, m->inst_cap, sorted, vn, s));
+  if (m->inst_cap > 0) GS_TRY(ensure_instances(m, m->inst_cap, s));
   const int64_t marked_cap = m->inst_cap;
   uint2* ranges = (uint2*)m->ranges.ptr;
   uint32_t* inst_off = (uint32_t*)m->inst_off.ptr;
@@ -732,7 +741,7 @@ gs_status gs_render(gs_map* m, int32_t nv, const gs_view* views, const gs_frame*
     const int64_t need = m->h_pinned[0];
     if (need > kMostInstances) return fail(GS_ERR_CAPACITY, "the render needs 2^32 instances or more");
     const int64_t cap = need > m->inst_cap ? planned_capacity(need) : m->inst_cap;
-    GS_TRY(ensure_instances(m, cap, sorted, vn, s));
+    GS_TRY(ensure_instances(m, cap, s));
     // a deterministic render of more instances than an entry's id holds takes the tile sort
     if (!sorted && !tile_lists_fit(va, N, m->deterministic ? need : 0)) return gs_render(m, nv, views, frames, stream);
   }
@@ -741,16 +750,17 @@ gs_status gs_render(gs_map* m, int32_t nv, const gs_view* views, const gs_frame*
   va.inst_cap = m->inst_cap;
   if (!sorted) {
     StageTimer t(m, s, GS_STAGE_DUPLICATE);
-    m->last_e = &m->list_e;
+    m->last_half = -1;
     GS_HIP(tile_lists_build(rec, (const uint4*)m->tl_pairs.ptr, dkey[0], inst_off, N, va, m->tl_space.ptr, ranges,
-                            (uint64_t*)m->tl_entries.ptr, (uint64_t*)m->tl_groups.ptr, (uint32_t*)m->emit_g.ptr,
-                            (uint32_t*)m->list_g.ptr, m->deterministic ? (uint32_t*)m->list_e.ptr : nullptr, m->last_sp, s));
+                            (uint64_t*)m->inst_a.ptr, (uint64_t*)m->inst_b.ptr, (uint32_t*)m->emit_g.ptr,
+                            last_list_g(m), m->deterministic ? last_list_e(m) : nullptr, m->last_sp, s));
   } else {
-    uint32_t* keys[2] = {(uint32_t*)m->keys[0].ptr, (uint32_t*)m->keys[1].ptr};
-    uint32_t* vals[2] = {(uint32_t*)m->vals[0].ptr, (uint32_t*)m->vals[1].ptr};
+    uint32_t* keys[2] = {sorted_half(m, m->inst_a, 0), sorted_half(m, m->inst_a, 1)};
+    uint32_t* vals[2] = {sorted_half(m, m->inst_b, 0), sorted_half(m, m->inst_b, 1)};
+    uint32_t* emit_g = (uint32_t*)m->inst_c.ptr;
     {
       StageTimer t(m, s, GS_STAGE_DUPLICATE);
-      GS_HIP(duplicate_keys(rec, counts, order, offsets, m->d_ninst, N, va, keys[0], (uint32_t*)m->emit_g.ptr,
+      GS_HIP(duplicate_keys(rec, counts, order, offsets, m->d_ninst, N, va, keys[0], emit_g,
                             inst_off, m->deterministic, (uint32_t*)m->block_start.ptr,
                             marked_cap > 0 && marked_cap == m->inst_cap, m->inst_cap, m->d_overflow, s));
     }
@@ -760,9 +770,8 @@ gs_status gs_render(gs_map* m, int32_t nv, const gs_view* views, const gs_frame*
       StageTimer t(m, s, GS_STAGE_SORT);
       GS_HIP(radix_sort_u32(keys, vals, m->d_ninst, m->inst_cap, bits_for(tiles + 1), (uint32_t*)m->sort_tmp.ptr,
                             &which, s, true));
-      m->last_e = &m->vals[which];
-      GS_HIP(gather_gaussians(vals[which], (const uint32_t*)m->emit_g.ptr, m->d_ninst, m->inst_cap,
-                              (uint32_t*)m->list_g.ptr, s));
+      m->last_half = which;
+      GS_HIP(gather_gaussians(vals[which], emit_g, m->d_ninst, m->inst_cap, last_list_g(m), s));
     }
     StageTimer t(m, s, GS_STAGE_RANGES);
     GS_HIP(tile_ranges(keys[which], m->d_ninst, m->inst_cap, ranges, tiles, s));
@@ -770,7 +779,7 @@ gs_status gs_render(gs_map* m, int32_t nv, const gs_view* views, const gs_frame*
   }
   {
     StageTimer t(m, s, GS_STAGE_BLEND);
-    GS_HIP(blend_forward(va, rec, N, (const uint32_t*)m->list_g.ptr, ranges, m->last_sp, m->fwd_px, s));
+    GS_HIP(blend_forward(va, rec, N, last_list_g(m), ranges, m->last_sp, m->fwd_px, s));
   }
   m->have_render = true;
   m->last_va = va;
@@ -819,13 +828,13 @@ static gs_status backward_impl(gs_map* m, int32_t nv, const float* const* dL_drg
     StageTimer t(m, s, GS_STAGE_BLEND_BACKWARD);
     // deterministic when the render was (it wrote every pair's first emission index)
     float* ig = m->last_det ? (float*)m->inst_grad.ptr : nullptr;
-    const uint32_t* list_e = m->last_det ? (const uint32_t*)m->last_e->ptr : nullptr;
+    const uint32_t *list_g = last_list_g(m), *list_e = m->last_det ? last_list_e(m) : nullptr;
     if (m->bwd_mode == 1 && !maps)
-      GS_HIP(blend_backward_per_gaussian(va, rec, N, (const uint32_t*)m->list_g.ptr, list_e,
+      GS_HIP(blend_backward_per_gaussian(va, rec, N, list_g, list_e,
                                          (const uint2*)m->ranges.ptr, g2d, ig,
                                          (float*)m->exp_part.ptr, m->last_sp, s));
     else
-      GS_HIP(blend_backward(va, rec, N, (const uint32_t*)m->list_g.ptr, list_e,
+      GS_HIP(blend_backward(va, rec, N, list_g, list_e,
                             (const uint2*)m->ranges.ptr, g2d, ig, (float*)m->exp_part.ptr, m->last_sp,
                             m->bwd_px, s));
   }
@@ -1065,7 +1074,7 @@ gs_status gs_submit_keyframe(gs_map* m, const gs_view* view, const float* image,
           const int64_t scaled = m->serve_peak * nk / m->serve_views;
           est = std::max<int64_t>(est, scaled + scaled / 4 + (1 << 16));
         }
-        gs_status st = ensure_instances(m, est, false, 0, s);
+        gs_status st = ensure_instances(m, est, s);
         if (st != GS_OK) return restore(st);
         m->sync_plan = false;
         for (; it < iters; ++it) {
@@ -1424,7 +1433,7 @@ gs_status gs_debug_last_render(gs_map* m, void* stream, const uint32_t** keys, c
     GS_HIP(hipStreamSynchronize(s));
     *keys = (const uint32_t*)m->dbg_t.ptr;
   }
-  if (vals) *vals = (const uint32_t*)m->list_g.ptr;
+  if (vals) *vals = last_list_g(m);
   if (n_inst) *n_inst = m->h_pinned[0];
   if (ranges) *ranges = (const uint32_t*)m->ranges.ptr;
   if (n_tiles) *n_tiles = m->last_va.total_tiles;
@@ -1438,7 +1447,7 @@ gs_status gs_set_instance_policy(gs_map* m, int32_t sync_plan, int64_t capacity)
   if (capacity < 0 || capacity > (int64_t)UINT32_MAX) return fail(GS_ERR_INVALID, "capacity out of range");
   if (capacity > m->inst_cap) {
     hipStream_t s = nullptr;
-    GS_TRY(ensure_instances(m, capacity, false, 0, s));
+    GS_TRY(ensure_instances(m, capacity, s));
     GS_HIP(hipStreamSynchronize(s));
   }
   m->sync_plan = sync_plan != 0;

@@ -89,3 +89,64 @@ def test_a_render_that_fails_for_memory_ends_the_one_before(granted, determinist
     torch.cuda.synchronize()
     if deterministic:
         assert torch.equal(m.grads(), want)
+
+
+def _step_buffers(cam):
+    torch = torch_mod()
+    h, w = cam.height, cam.width
+    fr = [gslic.Frame(torch.empty(3, h, w, device="cuda"), torch.empty(h, w, device="cuda"),
+                      torch.empty(h, w, device="cuda", dtype=torch.int32))]
+    target = torch.from_numpy(scenes.smooth_image(7, h, w)).float().cuda()
+    return fr, [target], [gslic.identity_exposure_state()], [torch.empty(3, h, w, device="cuda")], torch.empty(
+        1, device="cuda")
+
+
+# An eager step, a larger capacity, a capture: by counting, and by sorting (more Gaussians than
+# the counting lists take for so few cells). The replays give what eager steps give.
+@pytest.mark.parametrize("n", [5000, 70_000])
+@pytest.mark.parametrize("deterministic", [False, True])
+def test_a_capacity_set_before_a_capture_holds_for_both_lists(n, deterministic):
+    torch = torch_mod()
+    cam = scenes.pinhole(30, 28, 25.0)
+    params = scenes.frustum_gaussians(n, 0, cam, seed=n)
+    out = []
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        for captured in (False, True):
+            m = gpu_map(params, 0)
+            m.set_deterministic(deterministic)
+            b = _step_buffers(cam)
+            m.step([cam], *b)
+            m.set_instance_policy(False, 4 * m.debug_last_render()["n_inst"])
+            print(f"{n} Gaussians, deterministic {deterministic}, captured {captured}", flush=True)
+            if captured:
+                g = m.capture_step([cam], *b)
+                for _ in range(3):
+                    g.launch()
+                    stream.synchronize()
+                g.close()
+            else:
+                for _ in range(3):
+                    m.step([cam], *b)
+            stream.synchronize()
+            assert not m.check_overflow()
+            out.append((b[0][0].rgb.clone(), m.params().clone()))
+    if deterministic:
+        assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    else:
+        # atomic sums of another order: an ulp of a gradient is at most a few ulps of an Adam step
+        assert torch.allclose(out[0][0], out[1][0], rtol=0, atol=1e-3)
+
+
+@pytest.mark.parametrize("n", [5000, 70_000])  # by counting, by sorting
+def test_instance_buffers_are_shared_by_both_lists(n):
+    cam = scenes.pinhole(30, 28, 25.0)
+    m = gpu_map(scenes.frustum_gaussians(n, 0, cam, seed=n), 0)
+    m.render([cam])
+    held = []
+    for capacity in (1 << 22, 1 << 23):
+        m.set_instance_policy(True, capacity)
+        m.render([cam])
+        held.append(m.info()[2])
+    # 20 B per instance and a word per 512 of them
+    assert held[1] - held[0] <= (20 + 0.01) * (1 << 22)
