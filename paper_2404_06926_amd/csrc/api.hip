@@ -94,7 +94,7 @@ struct gs_map {
   DevBuf inst_a, inst_b, inst_c;
   DevBuf list_e, emit_g;       // deterministic, by counting: emission index of each instance; its Gaussian
   DevBuf inst_off;             // first emission index per pair
-  DevBuf tl_pairs, tl_space;   // tile lists by counting: pair words; counting matrices
+  DevBuf tl_pairs, tl_space, tl_extra;  // tile lists by counting: pair words; matrices; work items
   DevBuf block_start;          // instance-parallel binning: first pair per emission block
   DevBuf split_slot, split_extra, split_state;  // long lists cut into chunks (blend)
   DevBuf inst_grad, exp_part;  // deterministic backward: per-instance gradients, per-tile exposure sums
@@ -250,6 +250,7 @@ gs_status instance_buffers(gs_map* m, int64_t nc, hipStream_t s) {
   GS_TRY(ensure(m, m->inst_a, 2 * half_bytes(nc), s));
   GS_TRY(ensure(m, m->inst_b, 2 * half_bytes(nc), s));
   GS_TRY(ensure(m, m->inst_c, (size_t)nc * 4, s));
+  GS_TRY(ensure(m, m->tl_extra, (size_t)tile_extra_bytes(nc), s));
   GS_TRY(ensure(m, m->block_start, (size_t)block_start_elems(nc) * 4, s));
   GS_TRY(ensure(m, m->sort_tmp, (size_t)sort_temp_elems(nc) * 4, s));
   if (m->deterministic) {
@@ -496,7 +497,7 @@ gs_status gs_destroy_map(gs_map* m) {
   DevBuf* bufs[] = {&m->rec, &m->counts, &m->offsets, &m->scan_tmp, &m->g2d, &m->inst_a, &m->inst_b,
                     &m->inst_c, &m->sort_tmp, &m->ranges, &m->pixT, &m->pixN, &m->loss_tmp,
                     &m->dkey[0], &m->dkey[1], &m->dval[0], &m->dval[1], &m->emit_g, &m->inst_off, &m->list_e,
-                    &m->tl_pairs, &m->tl_space,
+                    &m->tl_pairs, &m->tl_space, &m->tl_extra,
                     &m->block_start, &m->split_slot, &m->split_extra, &m->split_state,
                     &m->inst_grad, &m->exp_part, &m->dbg_t, &m->gr_rgb, &m->gr_T, &m->gr_flags,
                     &m->gr_off, &m->gr_tmp, &m->gr_d2, &m->ar_rgb, &m->ar_T, &m->ar_nc, &m->ar_dl,
@@ -752,7 +753,7 @@ gs_status gs_render(gs_map* m, int32_t nv, const gs_view* views, const gs_frame*
     StageTimer t(m, s, GS_STAGE_DUPLICATE);
     m->last_half = -1;
     GS_HIP(tile_lists_build(rec, (const uint4*)m->tl_pairs.ptr, dkey[0], inst_off, N, va, m->tl_space.ptr, ranges,
-                            (uint64_t*)m->inst_a.ptr, (uint64_t*)m->inst_b.ptr, (uint32_t*)m->emit_g.ptr,
+                            (uint64_t*)m->inst_a.ptr, (uint64_t*)m->inst_b.ptr, m->tl_extra.ptr, (uint32_t*)m->emit_g.ptr,
                             last_list_g(m), m->deterministic ? last_list_e(m) : nullptr, m->last_sp, s));
   } else {
     uint32_t* keys[2] = {sorted_half(m, m->inst_a, 0), sorted_half(m, m->inst_a, 1)};

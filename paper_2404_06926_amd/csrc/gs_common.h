@@ -134,12 +134,24 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Sum over a block of NT lanes, in every lane.
+// Inclusive sum over the wave with DPP row operations.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+// Sum over a block of NT lanes, in every lane (in three parts that 64 lanes cannot overflow: the
+// DPP scans are shorter than 64-bit shuffles through the LDS unit).
 template <int NT>
 __device__ __forceinline__ uint64_t block_sum64(uint64_t x, uint64_t* s_wave) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += (uint64_t)__shfl_xor((unsigned long long)x, o, 64);
-  if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x >> 6] = x;
+  const uint32_t a = (uint32_t)wave_scan((int)(x & 0xffffffu)), b = (uint32_t)wave_scan((int)((x >> 24) & 0xffffffu)),
+                 c = (uint32_t)wave_scan((int)(x >> 48));
+  if ((threadIdx.x & 63) == 63) s_wave[threadIdx.x >> 6] = a + ((uint64_t)b << 24) + ((uint64_t)c << 48);
   __syncthreads();
   x = 0;
 #pragma unroll

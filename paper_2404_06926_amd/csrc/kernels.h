@@ -89,6 +89,7 @@ struct SplitArg;
 // pairs: the projection's pair words. space: tile_space_bytes (16-B aligned).
 bool tile_lists_fit(const ViewsArg& va, int64_t N, int64_t max_instances);
 int64_t tile_space_bytes(const ViewsArg& va, int32_t N);
+int64_t tile_extra_bytes(int64_t instances);
 // Tile ranges and *n_inst (instance_word of the sum); overflow as in duplicate_keys, the ranges being empty when more
 // than cap instances are needed. split_counts: the split's counters (or nullptr), cleared.
 hipError_t tile_lists_plan(const float4* rec, const uint4* pairs, int32_t N, const ViewsArg& va, void* space,
@@ -96,11 +97,11 @@ hipError_t tile_lists_plan(const float4* rec, const uint4* pairs, int32_t N, con
                            hipStream_t s);
 // list_g: Gaussian of every instance. list_e: nullptr, or its emission index, from inst_off,
 // the first emission index of every pair (emit_g: workspace of one word per instance then).
-// entries, groups: 8 B per instance. va.n_inst and va.inst_cap are set. Also the work items of
+// entries, groups: 8 B per instance; extra: tile_extra_bytes(va.inst_cap). va.n_inst and va.inst_cap are set. Also the work items of
 // long lists (sp).
 hipError_t tile_lists_build(const float4* rec, const uint4* pairs, const uint32_t* dkey, const uint32_t* inst_off,
                             int32_t N, const ViewsArg& va, void* space, const uint2* ranges, uint64_t* entries,
-                            uint64_t* groups, uint32_t* emit_g, uint32_t* list_g, uint32_t* list_e,
+                            uint64_t* groups, void* extra, uint32_t* emit_g, uint32_t* list_g, uint32_t* list_e,
                             const SplitArg& sp, hipStream_t s);
 hipError_t list_tiles(const uint2* ranges, int64_t n_tiles, int64_t cap, uint32_t* tiles, hipStream_t s);
 

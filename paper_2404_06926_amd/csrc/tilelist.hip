@@ -7,14 +7,14 @@
 //                   four tiles, in LDS -> its row of the view's matrices;
 //   k_cell_colscan  exclusive prefix of every cell's entries over the rows, and the totals;
 //   k_cell_offsets  exclusive scans of the totals: tile ranges, cell starts, the instance
-//                   count, overflow, and the work items of cells past the small block size;
+//                   count, overflow, and the cells past the small block size;
 //   k_cell_place    each block walks its pairs again and writes one entry (depth, Gaussian,
 //                   which of the four tiles) per cell it reaches at the cell's next position,
 //                   in any order within the block;
 //   k_cell_sort_small, k_cell_sort_large
 //                   one block per cell orders its entries in LDS and deals them out to its
 //                   tiles' lists by ballots (two sizes of block); cells of more than kSortMost
-//                   entries are ordered in chunks, which k_cell_merge deals out.
+//                   entries are ordered in chunks, which k_cell_merge merges and deals out.
 // (depth, Gaussian) is unique in a cell, so the lists do not depend on the order of arrival.
 //
 // Why cells: what bounds the placement is not its bytes but the scattered writes, which L2
@@ -45,6 +45,23 @@ constexpr int kTlMaxPairs = 32768;       // of one block: its hits per tile are 
 constexpr int kTlMaskBits = 4;           // entry: depth bits << 32 | Gaussian << 4 | tiles
 constexpr int64_t kTlMaxId = int64_t(1) << (32 - kTlMaskBits);
 
+// Cells are ordered by blocks of two sizes: up to 4096 and 16384 entries (four and one of them
+// fit a CU's LDS). Larger cells are ordered in chunks of at most the larger size; the merge
+// holds a cell's chunks one per lane of a block, which bounds the Gaussians of a map (a cell
+// holds each once): larger maps take the radix path.
+template <bool LARGE>
+struct SortShape {
+  static constexpr int cap = 4096, threads = 512;
+};
+template <>
+struct SortShape<true> {
+  static constexpr int cap = 16384, threads = 1024;
+};
+constexpr int kSortSmall = SortShape<false>::cap, kSortMost = SortShape<true>::cap;
+constexpr int kMostChunks = 1024;
+constexpr int64_t kTlMostGaussians = (int64_t)kMostChunks * kSortMost;
+__device__ __forceinline__ int sort_chunks(uint32_t n) { return (int)((n + kSortMost - 1) / kSortMost); }
+
 __host__ __device__ __forceinline__ int cells_of(int tiles) { return (tiles + 1) >> 1; }
 __device__ __forceinline__ int view_cells(const ViewDev& V) { return cells_of(V.tiles_x) * cells_of(V.tiles_y); }
 
@@ -65,15 +82,17 @@ static int max_cells(const ViewsArg& va) {
 }
 
 // A map of far more Gaussians than the images have room for fills few cells with many chunks
-// each, whose merge costs more than the radix path: a render of 200k over 64x48 (50000 per
-// cell) took 357 us here and 381 there, 1M (250000) 494 and 354.
+// each; the radix path's time does not depend on the cells. The binning of a render over 64x48
+// (four cells), here and there, in us: 50000 per cell 97 and 113, 125000 138 and 123, 250000
+// 151 and 150, 1M 395 and 358. Below the line, but with all of them in one cell of 1280x720:
+// 200k 138 and 150, 1M 216 and 220, 2M 298 and 309, 4M 567 and 473.
 constexpr int64_t kTlMostPerCell = 65536;
 
 bool tile_lists_fit(const ViewsArg& va, int64_t N, int64_t max_instances) {
   if (va.n * N > kTlMostPerCell * cells_total(va)) return false;
   for (int v = 0; v < va.n; ++v)
     if ((int64_t)cells_of(va.v[v].tiles_x) * cells_of(va.v[v].tiles_y) > kTlMaxCells) return false;
-  return N < kTlMaxId && max_instances < kTlMaxId;
+  return N <= kTlMostGaussians && max_instances < kTlMaxId;
 }
 
 // How the views' pairs fall to the blocks: view v's are shared by blocks [block[v],
@@ -139,38 +158,38 @@ __device__ __forceinline__ int block_pairs(int N, int g, int G) {
 
 // Workspace: per cell and block the packed hits (8 B) and the entries (4 B); per cell its
 // entries and its first one (one more at the end), per tile its hits; and the work items of
-// the larger sorting blocks.
-constexpr int kSortExtra = 1024;
-enum { kItems, kExtra, kChunks, kTlCounts };  // TlSpace::count
+// the larger sorting blocks: every cell past the small size with its first chunk (or whole),
+// and, by the instance capacity, the chunks after a cell's first.
+enum { kItems, kExtra, kTlCounts };  // TlSpace::count
 struct TlSpace {
   uint64_t* hits;
   uint32_t* entries;
   uint32_t* sizes;
   uint32_t* start;
   uint32_t* totals;
-  uint4* items;      // (cell, chunk, first entry, entries) of the cells past the small size, in any order
+  uint4* items;      // (cell, chunk, the cell's first entry, its entries), in any order
   uint32_t* lists;   // per cell, where its four tiles' lists start
-  uint4* chunks;     // those of the items that are chunks of a larger cell
-  uint32_t* count;   // items; chunks after a cell's first; chunks
-  uint32_t* alone;   // per cell of several chunks: whether its first block takes all of them
+  uint32_t* count;   // items; chunks after a cell's first
 };
 int64_t tile_space_bytes(const ViewsArg& va, int32_t N) {
   const int64_t c = cells_total(va), m = matrix_words(va, cell_base(va, N));
-  return 12 * m + 16 * (2 * c + 3 * kSortExtra) + 4 * (3 * c + 1 + va.total_tiles + kTlCounts) + 256;
+  return 12 * m + 16 * (2 * c) + 4 * (2 * c + 1 + va.total_tiles + kTlCounts) + 256;
 }
+// Chunks after a cell's first: n entries of a cell have less than n / kSortMost, and the
+// entries of all cells are at most the instances.
+static int64_t most_extra(int64_t instances) { return instances / kSortMost + 1; }
+int64_t tile_extra_bytes(int64_t instances) { return 16 * most_extra(instances); }
 static TlSpace tl_space(void* ws, const ViewsArg& va, const CellBase& cb) {
   const int64_t c = cells_total(va), m = matrix_words(va, cb);
   TlSpace t;
   t.items = (uint4*)ws;
-  t.chunks = t.items + c + kSortExtra;
-  t.lists = (uint32_t*)(t.chunks + 2 * kSortExtra);
+  t.lists = (uint32_t*)(t.items + c);
   t.hits = (uint64_t*)(t.lists + 4 * c);
   t.entries = (uint32_t*)(t.hits + m);
   t.sizes = t.entries + m;
   t.start = t.sizes + c;
   t.totals = t.start + c + 1;
-  t.alone = t.totals + va.total_tiles;
-  t.count = t.alone + c;
+  t.count = t.totals + va.total_tiles;
   return t;
 }
 
@@ -185,17 +204,6 @@ __device__ __forceinline__ PairRect pair_rect(uint32_t a, uint32_t b) {
   r.rw = (int)(b & 0xffffu) - r.x0 + 1;
   r.rh = (int)(b >> 16) - r.y0 + 1;
   return r;
-}
-
-// Inclusive sum over the wave with DPP row operations.
-__device__ __forceinline__ int wave_scan(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
-  return x;
 }
 
 // Calls entry(cell, tiles, lane of the pair, hits of the pair in its earlier cells, the pair's
@@ -460,21 +468,6 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t x, uint32_t* s_warp, uin
   return r;
 }
 
-// Cells are ordered by blocks of two sizes: up to 4096 and 16384 entries (four and one of them
-// fit a CU's LDS). Larger cells are ordered in chunks of at most the larger size. The chunks
-// after a cell's first are work items of their own, up to kSortExtra of them (a cell whose
-// chunks do not fit is left to its first block).
-template <bool LARGE>
-struct SortShape {
-  static constexpr int cap = 4096, threads = 512;
-};
-template <>
-struct SortShape<true> {
-  static constexpr int cap = 16384, threads = 1024;
-};
-constexpr int kSortSmall = SortShape<false>::cap, kSortMost = SortShape<true>::cap;
-__device__ __forceinline__ int sort_chunks(uint32_t n) { return (int)((n + kSortMost - 1) / kSortMost); }
-
 // Exclusive scans of the tiles' hits to ranges (zero for empty tiles) and the instance count,
 // and of the cells' entries to their starts; the work items of cells past the small size.
 // With more than `cap` instances the render is dropped (empty ranges and cells, overflow[0] |=
@@ -506,7 +499,8 @@ k_cell_offsets(ViewsArg va, CellBase cb, int32_t n_cells, int64_t cap, uint2* __
                uint32_t* __restrict__ n_inst, uint32_t* __restrict__ overflow, uint32_t* __restrict__ split_counts,
                TlSpace ws) {
   __shared__ uint32_t s_warp[kTlOffThreads / 64];
-  __shared__ uint64_t s_sum[kTlOffThreads / 64];
+  __shared__ uint64_t s_sum[2][kTlOffThreads / 64];
+  __shared__ uint32_t s_items;
   const int n_tiles = va.total_tiles;
   const int first = (int)blockIdx.x * kTlOffThreads * kTlOffPer;
   const int t0 = first + (int)threadIdx.x * kTlOffPer;
@@ -522,15 +516,32 @@ k_cell_offsets(ViewsArg va, CellBase cb, int32_t n_cells, int64_t cap, uint2* __
   }
   sum_before(ws.totals, n_tiles, first, all, pre);
   sum_before(ws.sizes, min(n_cells, first), first, call, cpre);
-  // the sums over the block's lanes, then the lanes' places in the block's own run
-  const uint64_t total = block_sum64<kTlOffThreads>(all, s_sum);
-  uint32_t at = 0, cell_at = 0;
-  block_scan<kTlOffThreads>(pre, s_warp, at);
-  block_scan<kTlOffThreads>(cpre, s_warp, cell_at);
+  uint32_t large = 0;  // the lane's cells past the small size
+#pragma unroll
+  for (int k = 0; k < kTlOffPer; ++k) large += c[k] > (uint32_t)kSortSmall ? 1u : 0u;
+  // the sums over the block's lanes, then the lanes' places in the block's own run. (The hits
+  // of 2^20 tiles by 2^24 Gaussians leave the block's large cells 20 bits; the sums of earlier
+  // tiles and cells fit 32 each where they are used.)
+  const uint64_t both = block_sum64<kTlOffThreads>((uint64_t)large << 44 | all, s_sum[0]);
+  const uint64_t before = block_sum64<kTlOffThreads>((uint64_t)cpre << 32 | pre, s_sum[1]);
+  const uint64_t total = both & ((1ull << 44) - 1ull);
+  const uint32_t n_large = (uint32_t)(both >> 44);
+  uint32_t at = (uint32_t)before, cell_at = (uint32_t)(before >> 32);
   uint32_t run = block_scan<kTlOffThreads>(xs, s_warp, at) - xs;
   uint32_t crun = block_scan<kTlOffThreads>(cs, s_warp, cell_at) - cs;
   const uint32_t count = instance_word(total);
   const bool dropped = (int64_t)total > cap || count == kTooManyInstances;
+  // the places of the cells past the small size among the items, with one atomic per block (one
+  // per cell took 6 us more for 2280 of them, and 23 where the cells' sorting blocks did it);
+  // before the stores below, which a barrier would wait for
+  uint32_t item = 0;
+  if (n_large > 0 && !dropped) {
+    uint32_t carry = 0;
+    item = block_scan<kTlOffThreads>(large, s_warp, carry) - large;
+    if (threadIdx.x == 0) s_items = atomicAdd(ws.count + kItems, n_large);
+    __syncthreads();
+    item += s_items;
+  }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     n_inst[0] = count;
     if ((int64_t)total > cap) atomicOr(overflow, 1u);
@@ -550,24 +561,10 @@ k_cell_offsets(ViewsArg va, CellBase cb, int32_t n_cells, int64_t cap, uint2* __
     run += x[k];
     if (i >= n_cells) continue;
     if (dropped) crun = c[k] = 0u;
-    const uint32_t start = crun;
-    ws.start[i] = start;
+    ws.start[i] = crun;
+    if (c[k] > (uint32_t)kSortSmall) ws.items[item++] = make_uint4((uint32_t)i, 0u, crun, c[k]);
     crun += c[k];
     if (i == n_cells - 1) ws.start[n_cells] = crun;
-    if (c[k] <= (uint32_t)kSortSmall) continue;
-    const uint32_t more = (uint32_t)sort_chunks(c[k]) - 1u;
-    bool fits = true;
-    if (more) {
-      const uint32_t e0 = atomicAdd(ws.count + kExtra, more);
-      fits = e0 + more <= (uint32_t)kSortExtra;
-      ws.alone[i] = fits ? 0u : 1u;
-    }
-    const uint32_t n = fits ? more + 1u : 1u, j0 = atomicAdd(ws.count + kItems, n);
-    const uint32_t c0 = n > 1u ? atomicAdd(ws.count + kChunks, n) : 0u;
-    for (uint32_t j = 0; j < n; ++j) {
-      ws.items[j0 + j] = make_uint4((uint32_t)i, j, start, c[k]);
-      if (n > 1u) ws.chunks[c0 + j] = ws.items[j0 + j];
-    }
   }
 }
 
@@ -695,14 +692,15 @@ __device__ __forceinline__ uint32_t bin_value(const uint32_t* bins, uint32_t b) 
   return (bins[b >> 1] >> (16 * (b & 1u))) & 0xffffu;
 }
 
-// Leaves the n entries of src in order in L.e (after a barrier).
-template <int NT, int CAP>
-__device__ __forceinline__ void sort_run(SortLds<NT, CAP>& L, const uint64_t* __restrict__ src, int n) {
+// Leaves n entries, src(i) for i < n, in order in L.e (after a barrier). (Of more than kRankMost
+// all are read before L.e is written.)
+template <int NT, int CAP, typename SRC>
+__device__ __forceinline__ void sort_run(SortLds<NT, CAP>& L, int n, SRC src) {
   constexpr int PER = CAP / NT, WORDS = CAP / 4 / NT;
   static_assert(CAP % (4 * NT) == 0 && CAP < 65536, "whole words of bins per lane");
   const int tid = (int)threadIdx.x;
   if (CAP <= kSortSmall && n <= kRankMost) {  // (the larger size has none so small)
-    const uint64_t e = tid < n ? src[tid] : ~0ull;
+    const uint64_t e = tid < n ? src(tid) : ~0ull;
     if (tid < kRankMost) L.e[tid] = e;  // (past n: larger than every entry)
     __syncthreads();
     int r = 0;
@@ -720,7 +718,7 @@ __device__ __forceinline__ void sort_run(SortLds<NT, CAP>& L, const uint64_t* __
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int i = tid + k * NT;
-    e[k] = i < n ? src[i] : ~0ull;
+    e[k] = i < n ? src(i) : ~0ull;
     if (i < n) {
       lo = min(lo, (uint32_t)(e[k] >> 32));
       hi = max(hi, (uint32_t)(e[k] >> 32));
@@ -979,48 +977,47 @@ __device__ __forceinline__ void merge_chunk(const uint64_t* list, const uint64_t
   }
 }
 
-// Orders and deals out cell `cell`, or orders its chunk c (every chunk, and deals it out, where
-// its block is alone with it). groups: one word per entry, which the chunks' groups fit into.
+// Orders and deals out cell `cell`, or orders its chunk c where it has several. groups: one word
+// per entry, which the chunks' groups fit into.
 template <bool LARGE>
 __device__ __forceinline__ void sort_cell(SortLds<SortShape<LARGE>::threads, SortShape<LARGE>::cap>& L,
                                           uint32_t (*s_cnt)[4], int cell, int c, uint32_t start, int n,
                                           uint64_t* __restrict__ entries, uint64_t* __restrict__ groups,
-                                          const TlSpace& ws, const ListOut& o) {
+                                          const uint32_t* __restrict__ lists, const ListOut& o) {
   constexpr int NT = SortShape<LARGE>::threads;
   uint64_t* list = entries + start;
-  const uint4 to = ((const uint4*)ws.lists)[cell];
+  const uint4 to = ((const uint4*)lists)[cell];  // (in flight while the entries are ordered)
   const int nch = LARGE ? sort_chunks((uint32_t)n) : 1;
   if (nch == 1) {
-    sort_run(L, list, n);
+    sort_run(L, n, [&](int i) { return list[i]; });
     deal_cell<NT>(L.e, n, to, s_cnt, o);
     return;
   }
-  const bool alone = ws.alone[cell] != 0u;
-  const int c1 = alone ? nch : c + 1;
   const int len = n / nch, longer = n % nch;
-  for (int k = c; k < c1; ++k) {
-    const int a = chunk_begin(len, longer, k), b = chunk_begin(len, longer, k + 1);
-    sort_run(L, list + a, b - a);
-    write_chunk<NT>(L.e, b - a, list + a, groups + start + a, s_cnt);
-  }
-  if (!alone) return;
-  __threadfence_block();
-  __syncthreads();
-  for (int k = 0; k < nch; ++k) merge_chunk(list, groups + start, n, nch, k, (int)threadIdx.x, NT, to, o);
+  const int a = chunk_begin(len, longer, c), b = chunk_begin(len, longer, c + 1);
+  sort_run(L, b - a, [&](int i) { return list[a + i]; });
+  write_chunk<NT>(L.e, b - a, list + a, groups + start + a, s_cnt);
 }
 
-// Block c orders cell c's entries where the small size holds them, and marks the cell's long
-// tile lists (split_tile).
+// Block c orders cell c's entries where the small size holds them, lists the chunks after the
+// first of a cell of several, and marks the cell's long tile lists (split_tile).
 __global__ void __launch_bounds__(SortShape<false>::threads)
 k_cell_sort_small(ViewsArg va, CellBase cb, const uint2* __restrict__ ranges, uint64_t* __restrict__ entries, TlSpace ws,
-                  ListOut o, SplitArg sp) {
+                  uint4* __restrict__ extra, ListOut o, SplitArg sp) {
   using S = SortShape<false>;
   __shared__ SortLds<S::threads, S::cap> L;
   __shared__ uint32_t s_cnt[S::threads / 64][4];
   const int cell = (int)blockIdx.x;
   const uint32_t start = ws.start[cell];
   const int n = (int)(ws.start[cell + 1] - start);
-  if (n > 0 && n <= S::cap) sort_cell<false>(L, s_cnt, cell, 0, start, n, entries, nullptr, ws, o);
+  if (n > 0 && n <= S::cap) sort_cell<false>(L, s_cnt, cell, 0, start, n, entries, nullptr, ws.lists, o);
+  if (n > kSortMost) {
+    const uint32_t more = (uint32_t)sort_chunks((uint32_t)n) - 1u;
+    if (threadIdx.x == 0) s_cnt[0][0] = atomicAdd(ws.count + kExtra, more);
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < more; j += S::threads)
+      extra[s_cnt[0][0] + j] = make_uint4((uint32_t)cell, j + 1u, start, (uint32_t)n);
+  }
   if (sp.par > 0 && threadIdx.x < 4) {
     const int v = view_of_cell(cb, va.n, cell), lc = cell - cb.cell[v];
     const ViewDev& V = va.v[v];
@@ -1034,32 +1031,219 @@ k_cell_sort_small(ViewsArg va, CellBase cb, const uint2* __restrict__ ranges, ui
   }
 }
 
-// One item of the larger cells per block (the grid is the most that the instances allow: a
-// block per cell spent 15 us on 6435 cells without one such item).
+// Blocks [0, n_items) take one item of the larger cells each (the grid is the most that the
+// instances allow: a block per cell spent 15 us on 6435 cells without one such item), the
+// others a chunk after a cell's first.
 __global__ void __launch_bounds__(SortShape<true>::threads)
-k_cell_sort_large(uint64_t* __restrict__ entries, uint64_t* __restrict__ groups, TlSpace ws, ListOut o) {
+k_cell_sort_large(uint64_t* __restrict__ entries, uint64_t* __restrict__ groups, const uint4* __restrict__ items,
+                  const uint4* __restrict__ extra, const uint32_t* __restrict__ counts,
+                  const uint32_t* __restrict__ lists, int n_items, ListOut o) {
   using S = SortShape<true>;
   __shared__ SortLds<S::threads, S::cap> L;
   __shared__ uint32_t s_cnt[S::threads / 64][4];
-  const uint4 it = ws.items[blockIdx.x];  // (a grid of at most the items' places)
-  if (blockIdx.x >= ws.count[kItems]) return;
-  sort_cell<true>(L, s_cnt, (int)it.x, (int)it.y, it.z, (int)it.w, entries, groups, ws, o);
+  const bool first = (int)blockIdx.x < n_items;
+  const uint32_t x = first ? blockIdx.x : blockIdx.x - (uint32_t)n_items;
+  const uint4 it = (first ? items : extra)[x];  // (a grid of at most the items' places)
+  if (x >= counts[first ? kItems : kExtra]) return;
+  sort_cell<true>(L, s_cnt, (int)it.x, (int)it.y, it.z, (int)it.w, entries, groups, lists, o);
 }
 
-// Deals out the cells ordered in chunks (none in most renders): the blocks of row y of the grid
-// take chunks y, y + rows, ..., an entry per lane. What bounds it is the chain of an entry's
-// binary searches, 14 dependent loads per other chunk: 685k Gaussians over six cells (some 8
-// chunks each), 815 us when one block dealt out each merged cell, 98 now; 194k over six, 127
-// and 14.
-constexpr int kMergeRows = 32, kMergeThreads = 256, kMergeCols = kSortMost / kMergeThreads;
+// Cells of more than kRankChunks chunks are merged in segments of the whole order, three per
+// chunk, whose ends are found in all chunks at once: the cost per entry grows with the
+// logarithm of the chunks, where an entry's rank takes a search in every other chunk.
+constexpr int kRankChunks = 8;
+constexpr int kMergeThreads = 1024, kSegMost = 8192, kSegsPerChunk = 3;
+// A segment ends within kSegSlack entries of its even share: the largest even share, one such
+// distance at either end.
+constexpr int kSegSlack = (kSegMost - (kSortMost + kSegsPerChunk - 1) / kSegsPerChunk) / 2;
+static_assert(kSortMost * kRankChunks / (kRankChunks + 1) / kSegsPerChunk > 2 * kSegSlack, "ends in order");
+constexpr int kMostPlaces = kMergeThreads / 16;  // (more than kRankChunks chunks: 16 lanes each or more)
+static_assert(kRankChunks >= 8, "kMostPlaces");
+union MergeLds {
+  SortLds<kMergeThreads, kSegMost> sort;
+  struct {                               // (where sort.e comes later)
+    uint16_t lo[2][kMostChunks], hi[2][kMostChunks];
+    uint16_t from[kMostChunks];          // where a chunk's piece of the segment starts in it
+    uint16_t at[kMostChunks + 1];        // and in the segment
+    uint32_t below[2][kMostPlaces];
+    uint32_t places[2];
+    uint64_t first, last;
+  } find;
+};
+static_assert(sizeof(MergeLds::find) <= sizeof(MergeLds::sort.e), "read while the bins are cleared");
+
+// The places in a cell's nch ordered chunks of two values with about r[0] and r[1] of its n
+// entries below them: left in F.lo. A round tries kMergeThreads / nch places at once, each of
+// which counts the entries below it by a binary search in every chunk, until a place is within
+// kSegSlack of the rank: what is found depends on the cell and the rank alone, so neighbouring
+// segments agree on their common end. The first round's places are entries of the first chunk
+// about its own share of the rank (kSpread: two standard deviations of it where the chunk is a
+// fair sample); the later ones bisect the range of values that is left, and the chunks' own
+// ranges shrink with it. (depth, id) is unique in a cell: 64 halvings reach the rank itself.
+constexpr int kSpread = 128;
+template <typename FIND>
+__device__ __forceinline__ void find_ends(FIND& F, const uint64_t* __restrict__ list, int n, int nch, const int (&r)[2]) {
+  constexpr int lanes = 31 - __builtin_clz(kMergeThreads);
+  const int tid = (int)threadIdx.x;
+  const int lg = 32 - __builtin_clz(nch - 1), K = kMergeThreads >> lg;  // places
+  const int k = tid >> lg, c = tid & ((1 << lg) - 1);
+  const bool mine = c < nch;
+  const int len = n / nch, longer = n % nch;
+  const int a = chunk_begin(len, longer, min(c, nch - 1)), held = chunk_begin(len, longer, min(c, nch - 1) + 1) - a;
+  if (tid == 0) {
+    F.first = ~0ull;
+    F.last = 0ull;
+  }
+  __syncthreads();
+  if (tid < nch) {
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      F.lo[w][c] = (uint16_t)(r[w] == n ? held : 0);
+      F.hi[w][c] = (uint16_t)(r[w] == 0 ? 0 : held);
+    }
+    atomicMin((unsigned long long*)&F.first, (unsigned long long)list[a]);
+    atomicMax((unsigned long long*)&F.last, (unsigned long long)list[a + held - 1]);
+  }
+  __syncthreads();
+  // below L[w] lie less than r[w] entries, below H[w] more
+  uint64_t L[2] = {F.first, F.first}, H[2] = {F.last + 1ull, F.last + 1ull};
+  bool done[2] = {r[0] == 0 || r[0] == n, r[1] == 0 || r[1] == n};
+  for (int round = 0; round < 64 && !(done[0] && done[1]); ++round) {  // (uniform)
+    if (tid < 2 * K) F.below[tid >= K][tid & (K - 1)] = 0u;
+    if (tid < 2) F.places[tid] = 0u;
+    __syncthreads();
+    auto place = [&](int w, int i) {
+      if (round == 0) {
+        const int at = (int)((int64_t)r[w] * len / n) + (2 * i + 1 - K) * kSpread / K;
+        return list[min(max(at, 0), len - 1)];
+      }
+      const uint64_t half = (H[w] - L[w]) >> (lanes - lg + 1);
+      return half ? L[w] + (2u * (uint32_t)i + 1u) * half : min(L[w] + (uint64_t)i + 1u, H[w]);
+    };
+    int lo[2] = {0, 0}, hi[2] = {0, 0};
+    if (mine) {
+      uint64_t v[2];
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        v[w] = place(w, k);
+        lo[w] = F.lo[w][c];
+        hi[w] = done[w] ? lo[w] : F.hi[w][c];
+      }
+      while (lo[0] < hi[0] || lo[1] < hi[1]) {
+        // (a search that has ended reads the entry at its place, or the last, again)
+        const int m0 = (lo[0] + hi[0]) >> 1, m1 = (lo[1] + hi[1]) >> 1;
+        const uint64_t x0 = list[a + min(m0, held - 1)], x1 = list[a + min(m1, held - 1)];
+        if (lo[0] < hi[0]) {
+          if (x0 < v[0]) lo[0] = m0 + 1;
+          else hi[0] = m0;
+        }
+        if (lo[1] < hi[1]) {
+          if (x1 < v[1]) lo[1] = m1 + 1;
+          else hi[1] = m1;
+        }
+      }
+#pragma unroll
+      for (int w = 0; w < 2; ++w)
+        if (lo[w] > 0) atomicAdd(&F.below[w][k], (uint32_t)lo[w]);
+    }
+    __syncthreads();
+    if (tid < 2 * K) {
+      const int w = tid >= K, i = tid & (K - 1);
+      if (F.below[w][i] <= (uint32_t)r[w]) atomicMax(&F.places[w], (uint32_t)i + 1u);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      if (done[w]) continue;
+      const int at = (int)F.places[w];  // places with r entries below or less
+      int end = -1;
+      if (at > 0 && r[w] - (int)F.below[w][at - 1] <= kSegSlack) end = at - 1;
+      else if (at < K && (int)F.below[w][at] - r[w] <= kSegSlack) end = at;
+      if (mine && k == (end >= 0 ? end : at - 1)) F.lo[w][c] = (uint16_t)lo[w];
+      if (mine && k == at) F.hi[w][c] = (uint16_t)lo[w];
+      done[w] = end >= 0;
+      const uint64_t l = at > 0 ? place(w, at - 1) : L[w];
+      if (at < K) H[w] = place(w, at);
+      L[w] = l;
+    }
+    __syncthreads();
+  }
+}
+
+// Segment s of a cell's order to its tiles' lists: its pieces of the chunks are read, ordered
+// and dealt out; the lists' places follow from the hits before the pieces.
+__device__ __forceinline__ void merge_segment(MergeLds& L, uint32_t (*s_cnt)[4], uint32_t* s_warp, uint32_t* s_to,
+                                              const uint64_t* __restrict__ list, const uint64_t* __restrict__ groups,
+                                              int n, int nch, int s, const uint4& to, const ListOut& o) {
+  const int tid = (int)threadIdx.x, lane = tid & 63;
+  const int len = n / nch, longer = n % nch, segs = kSegsPerChunk * nch;
+  const int r[2] = {(int)((int64_t)s * n / segs), (int)((int64_t)(s + 1) * n / segs)};
+  if (tid < 4) s_to[tid] = tid == 0 ? to.x : tid == 1 ? to.y : tid == 2 ? to.z : to.w;
+  find_ends(L.find, list, n, nch, r);
+  int p0 = 0, size = 0;
+  if (tid < nch) {
+    p0 = L.find.lo[0][tid];
+    size = L.find.lo[1][tid] - p0;
+  }
+  uint32_t total = 0;
+  const uint32_t end = block_scan<kMergeThreads>((uint32_t)size, s_warp, total);
+  uint32_t hits[4] = {0u, 0u, 0u, 0u};
+  if (tid < nch) {
+    L.find.from[tid] = (uint16_t)p0;
+    L.find.at[tid] = (uint16_t)(end - (uint32_t)size);
+    const uint64_t* g = groups + chunk_begin(len, longer, tid) + (p0 >> 6) * kGroupWords;
+    const uint64_t below = (1ull << (p0 & 63)) - 1ull;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      hits[b] = (uint32_t)__popcll(g[b] & below) + (uint32_t)(g[4 + (b >> 1)] >> (32 * (b & 1)));
+  }
+  if (tid == 0) L.find.at[nch] = (uint16_t)total;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const int x = wave_scan((int)hits[b]);
+    if (lane == 63 && x) atomicAdd(&s_to[b], (uint32_t)x);
+  }
+  __syncthreads();
+  const int m = min((int)total, kSegMost);
+  sort_run(L.sort, m, [&](int i) {
+    int k = 0, past = nch;  // the last piece that starts at or before i (empty ones start where the next does)
+    while (past - k > 1) {
+      const int mid = (k + past) >> 1;
+      if ((int)L.find.at[mid] <= i) k = mid;
+      else past = mid;
+    }
+    return list[chunk_begin(len, longer, k) + L.find.from[k] + (i - L.find.at[k])];
+  });
+  deal_cell<kMergeThreads>(L.sort.e, m, make_uint4(s_to[0], s_to[1], s_to[2], s_to[3]), s_cnt, o);
+  __syncthreads();
+}
+
+// Deals out the cells ordered in chunks (none in most renders): the blocks take the parts of
+// every chunk after a cell's first in turn, and those of the first where theirs is the second.
+// Of up to kRankChunks chunks an entry per lane is ranked; what bounds that is the chain of an
+// entry's binary searches, 14 dependent loads per other chunk: 31 us for 7 chunks. More are
+// merged in segments: 34 us for a cell of 200k (13 chunks), 88 for 1M (62) and 138 for 2M (123),
+// where the ranks took some 500 and 2000; what bounds that is the first round's loads, 64 cold
+// lines per wave and step.
+constexpr int kMergeBlocks = 512, kMergeParts = kSortMost / kMergeThreads;
 __global__ void __launch_bounds__(kMergeThreads)
-k_cell_merge(const uint64_t* __restrict__ entries, const uint64_t* __restrict__ groups, TlSpace ws, ListOut o) {
-  const uint32_t count = ws.count[kChunks];
-  for (uint32_t x = blockIdx.y; x < count; x += kMergeRows) {
-    const uint4 it = ws.chunks[x];
-    merge_chunk(entries + it.z, groups + it.z, (int)it.w, sort_chunks(it.w), (int)it.y,
-                (int)(blockIdx.x * kMergeThreads + threadIdx.x), kMergeCols * kMergeThreads,
-                ((const uint4*)ws.lists)[it.x], o);
+k_cell_merge(const uint64_t* __restrict__ entries, const uint64_t* __restrict__ groups,
+             const uint4* __restrict__ extra, const uint32_t* __restrict__ counts, const uint32_t* __restrict__ lists,
+             ListOut o) {
+  __shared__ MergeLds L;
+  __shared__ uint32_t s_cnt[kMergeThreads / 64][4], s_warp[kMergeThreads / 64], s_to[4];
+  const uint32_t count = counts[kExtra];
+  for (uint32_t u = blockIdx.x; u < 2u * kMergeParts * count; u += kMergeBlocks) {
+    const int part = (int)(u / count) % kMergeParts;
+    const bool first = u / count >= (uint32_t)kMergeParts;
+    const uint4 it = extra[u % count];
+    if (first && it.y != 1u) continue;
+    const int c = first ? 0 : (int)it.y, n = (int)it.w, nch = sort_chunks(it.w);
+    const uint4 to = ((const uint4*)lists)[it.x];
+    if (nch <= kRankChunks)
+      merge_chunk(entries + it.z, groups + it.z, n, nch, c, part * kMergeThreads + (int)threadIdx.x, kSortMost, to, o);
+    else if (part < kSegsPerChunk)
+      merge_segment(L, s_cnt, s_warp, s_to, entries + it.z, groups + it.z, n, nch, kSegsPerChunk * c + part, to, o);
   }
 }
 
@@ -1097,7 +1281,7 @@ hipError_t tile_lists_plan(const float4* rec, const uint4* pairs, int32_t N, con
 
 hipError_t tile_lists_build(const float4* rec, const uint4* pairs, const uint32_t* dkey, const uint32_t* inst_off,
                             int32_t N, const ViewsArg& va, void* space, const uint2* ranges, uint64_t* entries,
-                            uint64_t* groups, uint32_t* emit_g, uint32_t* list_g, uint32_t* list_e,
+                            uint64_t* groups, void* extra, uint32_t* emit_g, uint32_t* list_g, uint32_t* list_e,
                             const SplitArg& sp, hipStream_t s) {
   const int nc = (int)cells_total(va);
   const CellBase cb = cell_base(va, N);
@@ -1114,16 +1298,17 @@ hipError_t tile_lists_build(const float4* rec, const uint4* pairs, const uint32_
     hipLaunchKernelGGL(k_cell_place<false>, grid, dim3(kTlThreads), lds, s, rec, pairs, dkey, inst_off, N, va, cb, ws,
                        entries, emit_g);
   hipLaunchKernelGGL(k_cell_sort_small, dim3((unsigned)nc), dim3(SortShape<false>::threads), 0, s, va, cb, ranges,
-                     entries, ws, o, sp);
+                     entries, ws, (uint4*)extra, o, sp);
   // a cell holds a Gaussian once: a small map has no items for the larger blocks
   if (N > kSortSmall) {
-    const int64_t most = std::min<int64_t>(nc, va.inst_cap / kSortSmall + 1),
-                  extra = N > kSortMost ? std::min<int64_t>(kSortExtra, va.inst_cap / kSortMost + 1) : 0;
-    hipLaunchKernelGGL(k_cell_sort_large, dim3((unsigned)(most + extra)), dim3(SortShape<true>::threads), 0, s,
-                       entries, groups, ws, o);
+    const int64_t items = std::min<int64_t>(nc, va.inst_cap / kSortSmall + 1),
+                  more = N > kSortMost ? most_extra(va.inst_cap) : 0;
+    hipLaunchKernelGGL(k_cell_sort_large, dim3((unsigned)(items + more)), dim3(SortShape<true>::threads), 0, s, entries,
+                       groups, ws.items, (const uint4*)extra, ws.count, ws.lists, (int)items, o);
   }
   if (N > kSortMost)
-    hipLaunchKernelGGL(k_cell_merge, dim3(kMergeCols, kMergeRows), dim3(kMergeThreads), 0, s, entries, groups, ws, o);
+    hipLaunchKernelGGL(k_cell_merge, dim3(kMergeBlocks), dim3(kMergeThreads), 0, s, entries, groups,
+                       (const uint4*)extra, ws.count, ws.lists, o);
   return hipGetLastError();
 }
 

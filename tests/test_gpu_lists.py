@@ -132,3 +132,78 @@ def test_deterministic_gradients_do_not_depend_on_the_lists_path():
     # most ~50 terms, 50 x 2^-24 of the column's largest entry
     scale = np.abs(out[0]).max(axis=1, keepdims=True)
     assert (np.abs(out[0] - out[1]) <= 3e-6 * scale + 3e-6 * np.abs(out[0])).all()
+
+
+def _one_cell(n, depths, seed):
+    """n small Gaussians of the given depths, all inside one cell of 2x2 tiles of the view."""
+    cam = scenes.pinhole(320, 240, 400.0)
+    params = scenes.frustum_gaussians(n, 0, cam, seed=seed)
+    r = np.random.default_rng(seed)
+    z = np.asarray(depths, np.float32)
+    params[:, 0] = (128 + 10 + 12 * r.random(n) - cam.cx) / cam.fx * z
+    params[:, 1] = (96 + 10 + 12 * r.random(n) - cam.cy) / cam.fy * z
+    params[:, 2] = z
+    params[:, 3:6] = np.log(2e-4 * z)[:, None]
+    return cam, params
+
+
+# 8 chunks, which are ranked, and 9 and more, which are merged in segments; depths at random, in
+# order of the map (no chunk is a sample of the others), equal, and in a tight cluster
+@pytest.mark.parametrize("n,depths,deterministic", [
+    (131_072, "random", False), (131_073, "random", True), (131_073, "ordered", False), (200_000, "equal", False),
+    (300_000, "random", False), (300_000, "ordered", True), (300_000, "cluster", False), (300_000, "equal", True)])
+def test_lists_of_a_cell_of_many_chunks(n, depths, deterministic):
+    r = np.random.default_rng(n)
+    z = {"random": 5.0 + 20.0 * r.random(n), "ordered": 5.0 + 20.0 * np.arange(n) / n, "equal": np.full(n, 5.0),
+         "cluster": np.where(np.arange(n) == n // 3, 400.0, 5.0 + 1e-6 * r.random(n))}[depths]
+    cam, params = _one_cell(n, z, n)
+    print(f"{n} Gaussians in one cell, depths {depths}, deterministic {deterministic}", flush=True)
+    _, bins = _check_lists(params, 0, [cam], deterministic)
+    assert _cell_sizes(bins, [cam]).max() == n
+
+
+def test_time_of_a_crowded_cell_grows_with_its_entries():
+    # a far view puts a map into one cell: four times the Gaussians may take four times as long
+    # (about 2 measured; 10 with a search in every other chunk per entry)
+    torch = torch_mod()
+    times = []
+    for n in (500_000, 2_000_000):
+        cam, params = _one_cell(n, 5.0 + 20.0 * np.random.default_rng(n).random(n), n)
+        m = gpu_map(params, 0)
+        m.render([cam])
+        m.set_stage_timing(True)
+        best = np.inf
+        for _ in range(5):
+            m.stage_times()
+            m.render([cam])
+            torch.cuda.synchronize()
+            best = min(best, m.stage_times()["duplicate"][0])
+        times.append(best)
+        print(f"{n} in one cell: lists {1e3 * best:.0f} us", flush=True)
+        m.close()
+    assert times[1] < 6 * times[0]
+
+
+@pytest.mark.parametrize("n", [4_300_000, 8_500_000])  # chunks past a quarter, and a half, of a merge block's lanes
+def test_lists_of_a_cell_of_hundreds_of_chunks(n):
+    # checked without the oracle: each tile's list is in strict order of (depth, index), and each
+    # Gaussian is listed once per tile that it reaches
+    torch = torch_mod()
+    cam, rows = _one_cell(1000, 5.0 + 20.0 * np.random.default_rng(1).random(1000), 1)
+    params = torch.from_numpy(rows).cuda().repeat(n // 1000, 1)
+    scale = 1.0 + 0.2 * torch.rand(n, 1, device="cuda", generator=torch.Generator("cuda").manual_seed(n))
+    params[:, 0:3] *= scale  # along the rays of the thousand
+    from paper_2404_06926_amd import gslic
+    m = gslic.GaussianMap(sh_degree=0, capacity=n)
+    m.add_gaussians(params)
+    print(f"{n} Gaussians in one cell", flush=True)
+    m.render([cam])
+    torch.cuda.synchronize()
+    dbg = m.debug_last_render()
+    counts, vals, tiles = dbg["counts"][0].long(), dbg["vals"].long(), dbg["tiles"].long()
+    assert dbg["n_inst"] == int(counts.sum()) > n
+    assert torch.equal(torch.bincount(vals, minlength=n), counts)
+    assert (tiles[1:] >= tiles[:-1]).all() and torch.unique(tiles).numel() <= 4
+    depth = dbg["proj"][0, :, 9].contiguous().view(torch.int32).long()[vals]
+    key = depth << 32 | vals
+    assert ((key[1:] > key[:-1]) | (tiles[1:] > tiles[:-1])).all()
