@@ -1254,9 +1254,15 @@ k_list_tiles(const uint2* __restrict__ ranges, int64_t cap, uint32_t* __restrict
   for (int64_t i = (int64_t)r.x + threadIdx.x; i < r.y && i < cap; i += 256) tiles[i] = blockIdx.x;
 }
 
-template <typename K>
-static hipError_t allow_lds(K kernel, size_t bytes) {
-  return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+// Dynamic LDS past the 64 KiB that every launch may have is allowed to the kernel by the most
+// that any render takes, not by what this one takes: the limit is the kernel's, and renders of
+// other maps on other threads set and use it at the same time.
+constexpr int kCountLds = 12, kPlaceLds = 4;  // bytes per cell
+static_assert(kTlMaxCells * kPlaceLds + 1024 <= 64 * 1024, "k_cell_place needs no allowance");
+static hipError_t allow_count_lds(size_t bytes) {
+  if (bytes + 1024 <= 64 * 1024) return hipSuccess;
+  return hipFuncSetAttribute((const void*)k_cell_count, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             kTlMaxCells * kCountLds);
 }
 
 hipError_t tile_lists_plan(const float4* rec, const uint4* pairs, int32_t N, const ViewsArg& va, void* space,
@@ -1266,8 +1272,8 @@ hipError_t tile_lists_plan(const float4* rec, const uint4* pairs, int32_t N, con
   const CellBase cb = cell_base(va, N);
   const TlSpace ws = tl_space(space, va, cb);
   const dim3 grid((unsigned)cb.block[va.n]);
-  const size_t lds = (size_t)max_cells(va) * 12;
-  hipError_t e = allow_lds(k_cell_count, lds);
+  const size_t lds = (size_t)max_cells(va) * kCountLds;
+  const hipError_t e = allow_count_lds(lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_cell_count, grid, dim3(kTlThreads), lds, s, rec, pairs, N, va, cb,
                      ws);
@@ -1288,9 +1294,7 @@ hipError_t tile_lists_build(const float4* rec, const uint4* pairs, const uint32_
   const TlSpace ws = tl_space(space, va, cb);
   const dim3 grid((unsigned)cb.block[va.n]);
   const ListOut o{list_g, list_e, emit_g};
-  const size_t lds = (size_t)max_cells(va) * 4;
-  hipError_t e = list_e ? allow_lds(k_cell_place<true>, lds) : allow_lds(k_cell_place<false>, lds);
-  if (e != hipSuccess) return e;
+  const size_t lds = (size_t)max_cells(va) * kPlaceLds;
   if (list_e)
     hipLaunchKernelGGL(k_cell_place<true>, grid, dim3(kTlThreads), lds, s, rec, pairs, dkey, inst_off, N, va, cb, ws,
                        entries, emit_g);

@@ -207,3 +207,25 @@ def test_lists_of_a_cell_of_hundreds_of_chunks(n):
     depth = dbg["proj"][0, :, 9].contiguous().view(torch.int32).long()[vals]
     key = depth << 32 | vals
     assert ((key[1:] > key[:-1]) | (tiles[1:] > tiles[:-1])).all()
+
+
+def test_renders_of_other_sizes_on_other_threads():
+    # maps on different host threads are independent: an image whose counters take most of a
+    # CU's LDS beside one whose counters take little, each equal to its render alone
+    from concurrent.futures import ThreadPoolExecutor
+    torch = torch_mod()
+    cams = [scenes.pinhole(4160, 3200, 3000.0), scenes.pinhole(64, 48, 50.0)]
+    maps = [gpu_map(scenes.frustum_gaussians(3000, 0, c, seed=k, log_scale_mean=-2.5), 0) for k, c in enumerate(cams)]
+    alone = [m.render([c])[0].rgb.clone() for m, c in zip(maps, cams)]
+    torch.cuda.synchronize()
+
+    def renders(k):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            out = [maps[k].render([cams[k]])[0].rgb for _ in range(10 if k == 0 else 100)]
+            stream.synchronize()
+        return out
+
+    with ThreadPoolExecutor(2) as ex:
+        for k, out in enumerate(ex.map(renders, range(2))):
+            assert all(torch.equal(o, alone[k]) for o in out)
