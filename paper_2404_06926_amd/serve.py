@@ -350,13 +350,24 @@ class Scheduler:
 
 
 def estimate_bytes(n_final: int, sh_degree: int, window: int, width: int, height: int) -> int:
-    """HBM a session holds: parameters, gradients and Adam moments (16 F bytes per
-    Gaussian), per (view, Gaussian) records of a batch (2 x 64 B + 28 B), instances
-    (~8 per visible pair, 20 B each), keyframe buffers (8 floats per pixel) and loss
-    scratch."""
+    """HBM a session of a full window holds: parameters, gradients and Adam moments (16 F
+    bytes per Gaussian, a quarter to spare for growth); per (view, Gaussian) pair the
+    projection's record and its gradients (64 and 48 B), count, depth, tile word or sort
+    buffers, up to 144 B, and about 8 instances at 20 B with a quarter to spare; per pixel of
+    the window the keyframe's image, render and gradient and the render's own transmittance
+    and count (13 words), and once the expansion's render; the counting matrices of the tile
+    lists (12 B per block and cell of 2x2 tiles); and the state of split tile lists with the
+    sort's counters."""
     F = 11 + 3 * (sh_degree + 1) ** 2
     P = width * height
-    return int(16 * F * n_final * 1.25 + window * n_final * (156 + 160) + window * P * 40 + P * 40)
+    pairs = window * n_final
+    cells = -(-width // 32) * -(-height // 32)
+    # blocks of the counting: about 1024 pairs each, between bounds, and rounded up per view
+    most = min(max((8 << 20) // cells, 512), 4096)
+    blocks = max(min(max(pairs // 1024, 512), most), window * -(-n_final // 32768)) + 8 * window
+    split_state = 2 * 4096 * 7 * 1024
+    return int(16 * F * n_final * 1.25 + pairs * (144 + 200) + window * P * 52 + P * 16 +
+               12 * blocks * cells + split_state + (2 << 20))
 
 
 def poisson_arrivals(rng: np.random.Generator, rate_hz: float, duration_s: float, start: float = 0.0):

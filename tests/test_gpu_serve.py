@@ -76,3 +76,24 @@ def test_keyframe_job_reruns_the_steps_whose_render_overflowed():
         assert not m.check_overflow()
     assert m.n == 2000 + 100 + 60000
     assert torch.isfinite(m.params()[:, : m.n]).all()
+
+
+@pytest.mark.parametrize("n,deg,window,W,H", [(2000, 1, 3, 128, 96), (100_000, 1, 8, 640, 480), (400_000, 0, 8, 1280, 720),
+                                              (50_000, 1, 2, 1600, 1200)])
+def test_estimate_covers_what_a_session_holds(n, deg, window, W, H):
+    # at about the instances per pair that the estimate assumes (8), or fewer
+    import torch
+    from paper_2404_06926_amd import gslic
+    cam = scenes.pinhole(W, H, 0.8 * W)
+    m = gslic.GaussianMap(sh_degree=deg, capacity=n)
+    m.add_gaussians(torch.from_numpy(scenes.frustum_gaussians(n, deg, cam, seed=n)).cuda())
+    img = torch.tensor(scenes.smooth_image(5, H, W), dtype=torch.float32, device="cuda")
+    for k in range(window + 1):
+        cam.t = np.array([0.02 * k, 0.0, 0.0], np.float32)
+        m.submit_keyframe(cam, img, iters=2, window=window)
+    m.render([cam])
+    torch.cuda.synchronize()
+    per_pair = m.debug_last_render()["n_inst"] / n
+    held, est = m.info()[2], serve.estimate_bytes(n, deg, window, W, H)
+    print(f"{per_pair:.2f} instances per pair, holds {held / 1e6:.1f} MB of {est / 1e6:.1f} estimated", flush=True)
+    assert held <= est
