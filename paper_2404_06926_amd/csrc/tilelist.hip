@@ -226,7 +226,7 @@ __device__ __forceinline__ uint64_t for_each_cell(uint4 q, uint32_t d, uint32_t 
   const bool large = r.rw * r.rh > 64;
   const int hits = large ? 0 : __popc(q.z) + __popc(q.w);
   const int ncw = ((r.x0 + r.rw - 1) >> 1) - (r.x0 >> 1) + 1, nch = ((r.y0 + r.rh - 1) >> 1) - (r.y0 >> 1) + 1;
-  const int a = hits ? ncw * nch : 0;  // at most 33 x 1, 25 for 8 x 8
+  const int a = hits ? ncw * nch : 0;  // at most 34 (17 x 2: 32 x 2 tiles off both edges of a cell), 33 wide
   const int end = wave_scan(a);
   const int beg = end - a;
   const int hbeg = HITS ? wave_scan(hits) - hits : 0;
