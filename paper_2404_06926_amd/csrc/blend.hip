@@ -184,16 +184,18 @@ __device__ __forceinline__ int term_of_lane(int lane) {
 // four entries are collected the wave turns: lane l takes entry l / 16 at the four pixels 4 (l
 // mod 16) .. + 3, which lie side by side in a row of the quadrant, forms the partial sums of
 // all terms over them, and the 16 lanes of an entry add up. The pixels' dL/d(colour) stay in
-// the lane's registers for the whole tile; the position moments need only the sums of g, i g
-// and i^2 g over the four pixels i = 0 .. 3 and the offsets of the first from the mean. Per
-// entry this takes 15 VALU instructions where products and a reduction of every entry by
-// itself take 34.
+// the lane's registers for the whole tile; the row's offset dy is one for its four pixels. Per
+// entry this takes 17 VALU instructions where products and a reduction of every entry by
+// itself take 34. (The offsets dx are each pixel's own: moments about the first of the four,
+// shifted by its offset, would take two less, but they cancel where the weight lies on a pixel
+// near the mean: the second moment's rounding error is ten times as large in general, and
+// 2^-16 pixels from the mean not one digit was right.)
 //
 // The backward is bound by its waves' instruction issue and latency: with these sums, the
 // entries' masks in scalar registers and batches of 128 entries (64 in the deterministic
 // form, whose partial sums take more LDS) at eight waves per SIMD it went from 9.4e7 to
-// 6.6e7 VALU instructions and from 176 to 151 us per launch at 1M Gaussians and 1280x720,
-// from 1058 to 878 us for eight views, 85 to 69 us with the maps' gradients (160k, 641x511).
+// 6.5e7 VALU instructions and from 176 to 152 us per launch at 1M Gaussians and 1280x720,
+// from 1058 to 875 us for eight views, 85 to 72 us with the maps' gradients (160k, 641x511).
 // Tried and slower: the same sums as matrix products (eight entries' w and g as the rows of
 // FP32 16x16x4 MFMAs against the pixels' factors), 202 us: the products did not overlap with
 // the other waves' VALU work, and their factors and rows halved the waves in flight.
@@ -684,12 +686,11 @@ k_blend_bwd(ViewsArg va, const float4* __restrict__ rec, int32_t N, const uint32
     const float2 m = *(const float2*)&s_r[j][0];
     const float4 w = *(const float4*)(rows + 64 * re + rp), g = *(const float4*)(rows + 64 * (kRowEntries + re) + rp);
     const float dx = rx - m.x, dy = ry - m.y;
-    const float s = (g.x + g.y) + (g.z + g.w);                           // sum of g
-    const float si = fmaf(3.f, g.w, fmaf(2.f, g.z, g.y));                // of i g
-    const float sii = fmaf(9.f, g.w, fmaf(4.f, g.z, g.y));               // of i^2 g
-    const float sx = fmaf(dx, s, si);                                    // of (dx + i) g
-    const float sy = dy * s;
-    float v[8] = {sx, sy, fmaf(dx, sx + si, sii), dy * sx, dy * sy, s, 0.f, 0.f};
+    const float d[4] = {dx, dx + 1.f, dx + 2.f, dx + 3.f};
+    const float p[4] = {g.x * d[0], g.y * d[1], g.z * d[2], g.w * d[3]};
+    const float s = (g.x + g.y) + (g.z + g.w), sx = (p[0] + p[1]) + (p[2] + p[3]), sy = dy * s;
+    const float sxx = fmaf(p[3], d[3], fmaf(p[2], d[2], fmaf(p[1], d[1], p[0] * d[0])));
+    float v[8] = {sx, sy, sxx, dy * sx, dy * sy, s, 0.f, 0.f};
     auto dot = [&](const float4& f) { return fmaf(w.w, f.w, fmaf(w.z, f.z, fmaf(w.y, f.y, w.x * f.x))); };
     v[6] = dot(F[0]);
     v[7] = dot(F[1]);

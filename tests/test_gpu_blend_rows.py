@@ -48,3 +48,34 @@ def test_backward_at_group_and_batch_edges(n, deterministic, maps):
     assert ok.all(), err.max()
     if not (tie > 0).any():
         np.testing.assert_allclose(gexp.cpu().numpy(), gE[0], rtol=1e-3, atol=1e-3 * np.abs(gE[0]).max())
+
+
+# every pixel of a lane's four: the mean 2^-16 pixels from its centre, and the only gradient
+# there, so that the position moments are small against the distance to the four's first pixel
+@pytest.mark.parametrize("deterministic", [False, True])
+@pytest.mark.parametrize("column", range(8))
+def test_moments_of_a_pixel_at_the_mean(column, deterministic):
+    torch = torch_mod()
+    cam = scenes.pinhole(48, 48, 64.0)
+    x, y = 16 + column, 16 + column
+    params = scenes.frustum_gaussians(1, 0, cam, seed=1)
+    off = 0.5 + 2.0 ** -16
+    params[0, 0:3] = (2.0 * (x + off - 24.0) / 64.0, 2.0 * (y + off - 24.0) / 64.0, 2.0)
+    params[0, 3:6] = np.log(0.1)
+    params[0, 6:10] = (1.0, 0.0, 0.0, 0.0)
+    g = np.zeros((3, 48, 48), np.float32)
+    g[:, y, x] = (1.0, -2.0, 0.5)
+    m = gpu_map(params, 0)
+    m.set_deterministic(deterministic)
+    m.render([cam])
+    m.render_backward([torch.tensor(g, device="cuda")])
+    torch.cuda.synchronize()
+    views, projs, bins, rend = oracle_forward(params, 0, [cam])
+    off_centre = np.array([x, y]) + 0.5 - projs[0]["mean2d"][0]
+    assert (np.abs(off_centre) < 2e-5).all()
+    gp, gE, tie = oracle.backward(params, 0, views, projs, bins, [g.astype(np.float64)], TIE_ALPHA, TIE_T)
+    cols = [0, 1, 3, 4]  # mean x and y, scales x and y: products of the moments without cancellation
+    got, want = m.grads().cpu().numpy()[cols, 0].astype(np.float64), gp[0, cols]
+    print(f"column {column}: {got} against {want}", flush=True)
+    assert (want != 0).all()
+    np.testing.assert_allclose(got, want, rtol=1e-3)
