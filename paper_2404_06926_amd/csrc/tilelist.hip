@@ -14,7 +14,7 @@
 //   k_cell_sort_small, k_cell_sort_large
 //                   one block per cell orders its entries in LDS and deals them out to its
 //                   tiles' lists by ballots (two sizes of block); cells of more than kSortMost
-//                   entries are ordered in chunks, which k_cell_merge merges and deals out.
+//                   entries are ordered in chunks, which k_cell_rank or k_cell_merge deals out.
 // (depth, Gaussian) is unique in a cell, so the lists do not depend on the order of arrival.
 //
 // Why cells: what bounds the placement is not its bytes but the scattered writes, which L2
@@ -1051,14 +1051,14 @@ k_cell_sort_large(uint64_t* __restrict__ entries, uint64_t* __restrict__ groups,
 // Cells of more than kRankChunks chunks are merged in segments of the whole order, three per
 // chunk, whose ends are found in all chunks at once: the cost per entry grows with the
 // logarithm of the chunks, where an entry's rank takes a search in every other chunk.
-constexpr int kRankChunks = 8;
+constexpr int kRankChunks = 3;
 constexpr int kMergeThreads = 1024, kSegMost = 8192, kSegsPerChunk = 3;
 // A segment ends within kSegSlack entries of its even share: the largest even share, one such
 // distance at either end.
 constexpr int kSegSlack = (kSegMost - (kSortMost + kSegsPerChunk - 1) / kSegsPerChunk) / 2;
 static_assert(kSortMost * kRankChunks / (kRankChunks + 1) / kSegsPerChunk > 2 * kSegSlack, "ends in order");
-constexpr int kMostPlaces = kMergeThreads / 16;  // (more than kRankChunks chunks: 16 lanes each or more)
-static_assert(kRankChunks >= 8, "kMostPlaces");
+constexpr int kMostPlaces = kMergeThreads / 4;  // (more than kRankChunks chunks: four lanes each or more)
+static_assert(kRankChunks >= 3, "kMostPlaces");
 union MergeLds {
   SortLds<kMergeThreads, kSegMost> sort;
   struct {                               // (where sort.e comes later)
@@ -1218,13 +1218,37 @@ __device__ __forceinline__ void merge_segment(MergeLds& L, uint32_t (*s_cnt)[4],
   __syncthreads();
 }
 
-// Deals out the cells ordered in chunks (none in most renders): the blocks take the parts of
-// every chunk after a cell's first in turn, and those of the first where theirs is the second.
-// Of up to kRankChunks chunks an entry per lane is ranked; what bounds that is the chain of an
-// entry's binary searches, 14 dependent loads per other chunk: 31 us for 7 chunks. More are
-// merged in segments: 34 us for a cell of 200k (13 chunks), 88 for 1M (62) and 138 for 2M (123),
-// where the ranks took some 500 and 2000; what bounds that is the first round's loads, 64 cold
-// lines per wave and step.
+// Deals out the cells ordered in chunks (none in most renders) of maps of at most kRankGaussians:
+// an entry per lane is ranked. The blocks of row y of the grid take the chunks after a cell's
+// first y, y + rows, ..., and the first with the second. What bounds it is the chain of an
+// entry's binary searches, 14 dependent loads per other chunk: 13 us for six cells of some
+// 40000 entries (3 chunks each), 23 for one cell of 100k (7), 47 of 200k (13), 67 of 260k (16).
+constexpr int kRankRows = 32, kRankThreads = 256, kRankCols = kSortMost / kRankThreads;
+constexpr int kRankGaussians = 12 * kSortMost;
+__global__ void __launch_bounds__(kRankThreads)
+k_cell_rank(const uint64_t* __restrict__ entries, const uint64_t* __restrict__ groups,
+            const uint4* __restrict__ extra, const uint32_t* __restrict__ counts, const uint32_t* __restrict__ lists,
+            ListOut o) {
+  const uint32_t count = counts[kExtra];
+  const bool first = (int)blockIdx.x >= kRankCols;
+  const int at = ((int)blockIdx.x % kRankCols) * kRankThreads + (int)threadIdx.x;
+  for (uint32_t x = blockIdx.y; x < count; x += kRankRows) {
+    const uint4 it = extra[x];
+    if (first && it.y != 1u) continue;
+    merge_chunk(entries + it.z, groups + it.z, (int)it.w, sort_chunks(it.w), first ? 0 : (int)it.y, at, kSortMost,
+                ((const uint4*)lists)[it.x], o);
+  }
+}
+
+// The same for larger maps, whose cells may have any number of chunks: the blocks take the parts
+// of every chunk after a cell's first in turn, and those of the first where theirs is the
+// second. Cells of up to kRankChunks chunks are ranked, the others merged in segments: 34 us for
+// one cell of 270k (17 chunks), 88 of 1M (62) and 139 of 2M (123), where ranking took 506 for
+// 1M and four times that for 2M. What bounds it is the first round's loads, 64 cold lines per
+// wave and step. Its large blocks spread a few chunks worse over the chip: 20 us for the six
+// cells of 40000, 33 for six of 80000 where ranking takes 24. The line between the two lies
+// where the worst map, all in one cell, costs about the same; each launches alone, as an idle
+// launch takes 4 us.
 constexpr int kMergeBlocks = 512, kMergeParts = kSortMost / kMergeThreads;
 __global__ void __launch_bounds__(kMergeThreads)
 k_cell_merge(const uint64_t* __restrict__ entries, const uint64_t* __restrict__ groups,
@@ -1310,8 +1334,11 @@ hipError_t tile_lists_build(const float4* rec, const uint4* pairs, const uint32_
     hipLaunchKernelGGL(k_cell_sort_large, dim3((unsigned)(items + more)), dim3(SortShape<true>::threads), 0, s, entries,
                        groups, ws.items, (const uint4*)extra, ws.count, ws.lists, (int)items, o);
   }
-  if (N > kSortMost)
+  if (N > kRankGaussians)
     hipLaunchKernelGGL(k_cell_merge, dim3(kMergeBlocks), dim3(kMergeThreads), 0, s, entries, groups,
+                       (const uint4*)extra, ws.count, ws.lists, o);
+  else if (N > kSortMost)
+    hipLaunchKernelGGL(k_cell_rank, dim3(2 * kRankCols, kRankRows), dim3(kRankThreads), 0, s, entries, groups,
                        (const uint4*)extra, ws.count, ws.lists, o);
   return hipGetLastError();
 }
