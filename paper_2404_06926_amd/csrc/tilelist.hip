@@ -25,7 +25,7 @@
 // Measured against the path it replaced where it applies (a depth sort of the pairs by four
 // radix passes, a scan of the counts in that order, an emission, two radix passes by tile id,
 // the ranges), in us: 1M Gaussians at 1280x720 (6.9 M instances) 257 -> 126; eight views of 1M
-// (41.6 M) 1416 -> 623; 3M at 1920x1200 (35.9 M) 917 -> 541; a street map of 520k with a long
+// (41.6 M) 1416 -> 623; 3M at 1920x1200 (35.9 M) 917 -> 526; a street map of 520k with a long
 // horizon (0.7 M) 149 -> 89; 10k at 256x192 (17.8 k) 99 -> 29, of which most were launches
 // (20 -> 6). At 1M the counting takes 27, the column and total scans 18, the placement 33 and
 // the sort 39. Counting and placing issue VALU work for more than half of their time; the sort
@@ -676,8 +676,8 @@ __device__ __forceinline__ void bitonic_sort(uint64_t* s, int n) {
 // values.
 constexpr int kBinMost = 256;
 // Up to this many entries are ranked by comparing each with all: two barriers where the bins
-// take a dozen (6435 cells of 60 entries on average: 57 us with bins alone, 45 with this; up to
-// 512 entries ranked: 49).
+// take a dozen (6435 cells of 60 entries on average: 49 us with bins alone, 36 with this; up to
+// 512 entries ranked: 40).
 constexpr int kRankMost = 128;
 // Two fine bins share a word (16 bits each: CAP < 2^16); four 4096-entry blocks fit a CU.
 template <int NT, int CAP>
@@ -1329,8 +1329,8 @@ hipError_t tile_lists_build(const float4* rec, const uint4* pairs, const uint32_
                      entries, ws, (uint4*)extra, o, sp);
   // a cell holds a Gaussian once: a small map has no items for the larger blocks
   if (N > kSortSmall) {
-    const int64_t items = std::min<int64_t>(nc, va.inst_cap / kSortSmall + 1),
-                  more = N > kSortMost ? most_extra(va.inst_cap) : 0;
+    const int64_t most = std::min<int64_t>(va.inst_cap, (int64_t)N * nc),
+                  items = std::min<int64_t>(nc, most / kSortSmall + 1), more = N > kSortMost ? most_extra(most) : 0;
     hipLaunchKernelGGL(k_cell_sort_large, dim3((unsigned)(items + more)), dim3(SortShape<true>::threads), 0, s, entries,
                        groups, ws.items, (const uint4*)extra, ws.count, ws.lists, (int)items, o);
   }
