@@ -194,7 +194,7 @@ __device__ __forceinline__ int term_of_lane(int lane) {
 // The backward is bound by its waves' instruction issue and latency: with these sums, the
 // entries' masks in scalar registers and batches of 128 entries (64 in the deterministic
 // form, whose partial sums take more LDS) at eight waves per SIMD it went from 9.4e7 to
-// 6.5e7 VALU instructions and from 176 to 152 us per launch at 1M Gaussians and 1280x720,
+// 6.5e7 VALU instructions and from 176 to 150 us per launch at 1M Gaussians and 1280x720,
 // from 1058 to 875 us for eight views, 85 to 72 us with the maps' gradients (160k, 641x511).
 // Tried and slower: the same sums as matrix products (eight entries' w and g as the rows of
 // FP32 16x16x4 MFMAs against the pixels' factors), 202 us: the products did not overlap with
