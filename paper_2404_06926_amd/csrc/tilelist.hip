@@ -47,8 +47,8 @@ constexpr int64_t kTlMaxId = int64_t(1) << (32 - kTlMaskBits);
 
 // Cells are ordered by blocks of two sizes: up to 4096 and 16384 entries (four and one of them
 // fit a CU's LDS). Larger cells are ordered in chunks of at most the larger size; the merge
-// holds a cell's chunks one per lane of a block, which bounds the Gaussians of a map (a cell
-// holds each once): larger maps take the radix path.
+// holds a cell's chunks, up to four per lane of a block, in LDS, which bounds the Gaussians of
+// a map (a cell holds each once): larger maps take the radix path.
 template <bool LARGE>
 struct SortShape {
   static constexpr int cap = 4096, threads = 512;
@@ -58,7 +58,7 @@ struct SortShape<true> {
   static constexpr int cap = 16384, threads = 1024;
 };
 constexpr int kSortSmall = SortShape<false>::cap, kSortMost = SortShape<true>::cap;
-constexpr int kMostChunks = 1024;
+constexpr int kMostChunks = 4096;
 constexpr int64_t kTlMostGaussians = (int64_t)kMostChunks * kSortMost;
 __device__ __forceinline__ int sort_chunks(uint32_t n) { return (int)((n + kSortMost - 1) / kSortMost); }
 
@@ -520,12 +520,12 @@ k_cell_offsets(ViewsArg va, CellBase cb, int32_t n_cells, int64_t cap, uint2* __
 #pragma unroll
   for (int k = 0; k < kTlOffPer; ++k) large += c[k] > (uint32_t)kSortSmall ? 1u : 0u;
   // the sums over the block's lanes, then the lanes' places in the block's own run. (The hits
-  // of 2^20 tiles by 2^24 Gaussians leave the block's large cells 20 bits; the sums of earlier
+  // of 2^20 tiles by 2^26 Gaussians leave the block's large cells 16 bits; the sums of earlier
   // tiles and cells fit 32 each where they are used.)
-  const uint64_t both = block_sum64<kTlOffThreads>((uint64_t)large << 44 | all, s_sum[0]);
+  const uint64_t both = block_sum64<kTlOffThreads>((uint64_t)large << 48 | all, s_sum[0]);
   const uint64_t before = block_sum64<kTlOffThreads>((uint64_t)cpre << 32 | pre, s_sum[1]);
-  const uint64_t total = both & ((1ull << 44) - 1ull);
-  const uint32_t n_large = (uint32_t)(both >> 44);
+  const uint64_t total = both & ((1ull << 48) - 1ull);
+  const uint32_t n_large = (uint32_t)(both >> 48);
   uint32_t at = (uint32_t)before, cell_at = (uint32_t)(before >> 32);
   uint32_t run = block_scan<kTlOffThreads>(xs, s_warp, at) - xs;
   uint32_t crun = block_scan<kTlOffThreads>(cs, s_warp, cell_at) - cs;
@@ -1059,43 +1059,48 @@ constexpr int kSegSlack = (kSegMost - (kSortMost + kSegsPerChunk - 1) / kSegsPer
 static_assert(kSortMost * kRankChunks / (kRankChunks + 1) / kSegsPerChunk > 2 * kSegSlack, "ends in order");
 constexpr int kMostPlaces = kMergeThreads / 4;  // (more than kRankChunks chunks: four lanes each or more)
 static_assert(kRankChunks >= 3, "kMostPlaces");
+template <int PER>
 union MergeLds {
+  static constexpr int chunks = PER * kMergeThreads;
   SortLds<kMergeThreads, kSegMost> sort;
-  struct {                               // (where sort.e comes later)
-    uint16_t lo[2][kMostChunks], hi[2][kMostChunks];
-    uint16_t from[kMostChunks];          // where a chunk's piece of the segment starts in it
-    uint16_t at[kMostChunks + 1];        // and in the segment
+  struct {                           // (where sort.e comes later)
+    uint16_t lo[2][chunks], hi[2][chunks];
+    uint16_t from[chunks];           // where a chunk's piece of the segment starts in it
+    uint16_t at[chunks + 1];         // and in the segment
     uint32_t below[2][kMostPlaces];
     uint32_t places[2];
     uint64_t first, last;
   } find;
+  static_assert(sizeof(find) <= sizeof(sort.e), "read while the bins are cleared");
 };
-static_assert(sizeof(MergeLds::find) <= sizeof(MergeLds::sort.e), "read while the bins are cleared");
 
 // The places in a cell's nch ordered chunks of two values with about r[0] and r[1] of its n
-// entries below them: left in F.lo. A round tries kMergeThreads / nch places at once, each of
-// which counts the entries below it by a binary search in every chunk, until a place is within
-// kSegSlack of the rank: what is found depends on the cell and the rank alone, so neighbouring
-// segments agree on their common end. The first round's places are entries of the first chunk
-// about its own share of the rank (kSpread: two standard deviations of it where the chunk is a
-// fair sample); the later ones bisect the range of values that is left, and the chunks' own
-// ranges shrink with it. (depth, id) is unique in a cell: 64 halvings reach the rank itself.
+// entries below them: left in F.lo. A round tries kMergeThreads / nch places at once (at least
+// one: a lane holds up to PER chunks), each of which counts the entries below it by a binary
+// search in every chunk, until a place is within kSegSlack of the rank: what is found depends
+// on the cell and the rank alone, so neighbouring segments agree on their common end. The first
+// round's places are entries of the first chunk about its own share of the rank (kSpread: two
+// standard deviations of it where the chunk is a fair sample); the later ones bisect the range
+// of values that is left, and the chunks' own ranges shrink with it. (depth, id) is unique in a
+// cell: 64 halvings reach the rank itself.
 constexpr int kSpread = 128;
-template <typename FIND>
+template <int PER, typename FIND>
 __device__ __forceinline__ void find_ends(FIND& F, const uint64_t* __restrict__ list, int n, int nch, const int (&r)[2]) {
   constexpr int lanes = 31 - __builtin_clz(kMergeThreads);
   const int tid = (int)threadIdx.x;
-  const int lg = 32 - __builtin_clz(nch - 1), K = kMergeThreads >> lg;  // places
-  const int k = tid >> lg, c = tid & ((1 << lg) - 1);
-  const bool mine = c < nch;
+  const int lg = min(32 - __builtin_clz(nch - 1), lanes), K = kMergeThreads >> lg;  // places
+  const int k = tid >> lg, c0 = tid & ((1 << lg) - 1);                              // place and first chunk
   const int len = n / nch, longer = n % nch;
-  const int a = chunk_begin(len, longer, min(c, nch - 1)), held = chunk_begin(len, longer, min(c, nch - 1) + 1) - a;
   if (tid == 0) {
     F.first = ~0ull;
     F.last = 0ull;
   }
   __syncthreads();
-  if (tid < nch) {
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int c = tid + q * kMergeThreads;
+    if (c >= nch) break;
+    const int a = chunk_begin(len, longer, c), held = chunk_begin(len, longer, c + 1) - a;
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
       F.lo[w][c] = (uint16_t)(r[w] == n ? held : 0);
@@ -1120,32 +1125,43 @@ __device__ __forceinline__ void find_ends(FIND& F, const uint64_t* __restrict__ 
       const uint64_t half = (H[w] - L[w]) >> (lanes - lg + 1);
       return half ? L[w] + (2u * (uint32_t)i + 1u) * half : min(L[w] + (uint64_t)i + 1u, H[w]);
     };
-    int lo[2] = {0, 0}, hi[2] = {0, 0};
-    if (mine) {
-      uint64_t v[2];
+    int lo[PER][2], sum[2] = {0, 0};
+    uint64_t v[2] = {0ull, 0ull};
+    if (c0 < nch) {
+      v[0] = place(0, k);
+      v[1] = place(1, k);
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int c = c0 + q * kMergeThreads;
+      lo[q][0] = lo[q][1] = 0;
+      if (c >= nch) break;
+      const int a = chunk_begin(len, longer, c), held = chunk_begin(len, longer, c + 1) - a;
+      int hi[2];
 #pragma unroll
       for (int w = 0; w < 2; ++w) {
-        v[w] = place(w, k);
-        lo[w] = F.lo[w][c];
-        hi[w] = done[w] ? lo[w] : F.hi[w][c];
+        lo[q][w] = F.lo[w][c];
+        hi[w] = done[w] ? lo[q][w] : F.hi[w][c];
       }
-      while (lo[0] < hi[0] || lo[1] < hi[1]) {
+      while (lo[q][0] < hi[0] || lo[q][1] < hi[1]) {
         // (a search that has ended reads the entry at its place, or the last, again)
-        const int m0 = (lo[0] + hi[0]) >> 1, m1 = (lo[1] + hi[1]) >> 1;
+        const int m0 = (lo[q][0] + hi[0]) >> 1, m1 = (lo[q][1] + hi[1]) >> 1;
         const uint64_t x0 = list[a + min(m0, held - 1)], x1 = list[a + min(m1, held - 1)];
-        if (lo[0] < hi[0]) {
-          if (x0 < v[0]) lo[0] = m0 + 1;
+        if (lo[q][0] < hi[0]) {
+          if (x0 < v[0]) lo[q][0] = m0 + 1;
           else hi[0] = m0;
         }
-        if (lo[1] < hi[1]) {
-          if (x1 < v[1]) lo[1] = m1 + 1;
+        if (lo[q][1] < hi[1]) {
+          if (x1 < v[1]) lo[q][1] = m1 + 1;
           else hi[1] = m1;
         }
       }
-#pragma unroll
-      for (int w = 0; w < 2; ++w)
-        if (lo[w] > 0) atomicAdd(&F.below[w][k], (uint32_t)lo[w]);
+      sum[0] += lo[q][0];
+      sum[1] += lo[q][1];
     }
+#pragma unroll
+    for (int w = 0; w < 2; ++w)
+      if (sum[w] > 0) atomicAdd(&F.below[w][k], (uint32_t)sum[w]);
     __syncthreads();
     if (tid < 2 * K) {
       const int w = tid >= K, i = tid & (K - 1);
@@ -1159,8 +1175,13 @@ __device__ __forceinline__ void find_ends(FIND& F, const uint64_t* __restrict__ 
       int end = -1;
       if (at > 0 && r[w] - (int)F.below[w][at - 1] <= kSegSlack) end = at - 1;
       else if (at < K && (int)F.below[w][at] - r[w] <= kSegSlack) end = at;
-      if (mine && k == (end >= 0 ? end : at - 1)) F.lo[w][c] = (uint16_t)lo[w];
-      if (mine && k == at) F.hi[w][c] = (uint16_t)lo[w];
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        const int c = c0 + q * kMergeThreads;
+        if (c >= nch) break;
+        if (k == (end >= 0 ? end : at - 1)) F.lo[w][c] = (uint16_t)lo[q][w];
+        if (k == at) F.hi[w][c] = (uint16_t)lo[q][w];
+      }
       done[w] = end >= 0;
       const uint64_t l = at > 0 ? place(w, at - 1) : L[w];
       if (at < K) H[w] = place(w, at);
@@ -1172,30 +1193,34 @@ __device__ __forceinline__ void find_ends(FIND& F, const uint64_t* __restrict__ 
 
 // Segment s of a cell's order to its tiles' lists: its pieces of the chunks are read, ordered
 // and dealt out; the lists' places follow from the hits before the pieces.
-__device__ __forceinline__ void merge_segment(MergeLds& L, uint32_t (*s_cnt)[4], uint32_t* s_warp, uint32_t* s_to,
+template <int PER>
+__device__ __forceinline__ void merge_segment(MergeLds<PER>& L, uint32_t (*s_cnt)[4], uint32_t* s_warp, uint32_t* s_to,
                                               const uint64_t* __restrict__ list, const uint64_t* __restrict__ groups,
                                               int n, int nch, int s, const uint4& to, const ListOut& o) {
   const int tid = (int)threadIdx.x, lane = tid & 63;
   const int len = n / nch, longer = n % nch, segs = kSegsPerChunk * nch;
   const int r[2] = {(int)((int64_t)s * n / segs), (int)((int64_t)(s + 1) * n / segs)};
   if (tid < 4) s_to[tid] = tid == 0 ? to.x : tid == 1 ? to.y : tid == 2 ? to.z : to.w;
-  find_ends(L.find, list, n, nch, r);
-  int p0 = 0, size = 0;
-  if (tid < nch) {
-    p0 = L.find.lo[0][tid];
-    size = L.find.lo[1][tid] - p0;
-  }
-  uint32_t total = 0;
-  const uint32_t end = block_scan<kMergeThreads>((uint32_t)size, s_warp, total);
-  uint32_t hits[4] = {0u, 0u, 0u, 0u};
-  if (tid < nch) {
-    L.find.from[tid] = (uint16_t)p0;
-    L.find.at[tid] = (uint16_t)(end - (uint32_t)size);
-    const uint64_t* g = groups + chunk_begin(len, longer, tid) + (p0 >> 6) * kGroupWords;
+  find_ends<PER>(L.find, list, n, nch, r);
+  uint32_t total = 0, hits[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    if (q > 0 && q * kMergeThreads >= nch) break;  // (uniform)
+    const int c = tid + q * kMergeThreads;
+    int p0 = 0, size = 0;
+    if (c < nch) {
+      p0 = L.find.lo[0][c];
+      size = L.find.lo[1][c] - p0;
+    }
+    const uint32_t end = block_scan<kMergeThreads>((uint32_t)size, s_warp, total);
+    if (c >= nch) continue;
+    L.find.from[c] = (uint16_t)p0;
+    L.find.at[c] = (uint16_t)(end - (uint32_t)size);
+    const uint64_t* g = groups + chunk_begin(len, longer, c) + (p0 >> 6) * kGroupWords;
     const uint64_t below = (1ull << (p0 & 63)) - 1ull;
 #pragma unroll
     for (int b = 0; b < 4; ++b)
-      hits[b] = (uint32_t)__popcll(g[b] & below) + (uint32_t)(g[4 + (b >> 1)] >> (32 * (b & 1)));
+      hits[b] += (uint32_t)__popcll(g[b] & below) + (uint32_t)(g[4 + (b >> 1)] >> (32 * (b & 1)));
   }
   if (tid == 0) L.find.at[nch] = (uint16_t)total;
 #pragma unroll
@@ -1218,43 +1243,50 @@ __device__ __forceinline__ void merge_segment(MergeLds& L, uint32_t (*s_cnt)[4],
   __syncthreads();
 }
 
-// Deals out the cells ordered in chunks (none in most renders) of maps of at most kRankGaussians:
-// an entry per lane is ranked. The blocks of row y of the grid take the chunks after a cell's
-// first y, y + rows, ..., and the first with the second. What bounds it is the chain of an
-// entry's binary searches, 14 dependent loads per other chunk: 13 us for six cells of some
-// 40000 entries (3 chunks each), 23 for one cell of 100k (7), 47 of 200k (13), 67 of 260k (16).
+// Deals out the cells ordered in up to `most` chunks (none in most renders): an entry per lane is
+// ranked. The blocks of row y of the grid take the chunks after a cell's first y, y + rows, ...,
+// and the first with the second. What bounds it is the chain of an entry's binary searches, 14
+// dependent loads per other chunk: 13 us for six cells of some 40000 entries (3 chunks each), 24
+// for six of 80000, 23 for one cell of 100k (7), 47 of 200k (13), 67 of 260k (16).
+//
+// It takes all of a map of up to kRankGaussians (12 chunks: where the worst map, all in one
+// cell, costs about as much as merged), and in a crowded image, more than kRankPerCell pairs per
+// cell on average, the cells of up to kRankCrowded chunks, which most are there. Elsewhere the
+// merge takes the few such cells as well: an idle launch costs 4 us.
 constexpr int kRankRows = 32, kRankThreads = 256, kRankCols = kSortMost / kRankThreads;
 constexpr int kRankGaussians = 12 * kSortMost;
+constexpr int64_t kRankPerCell = 4096;
+constexpr int kRankCrowded = 8;
 __global__ void __launch_bounds__(kRankThreads)
 k_cell_rank(const uint64_t* __restrict__ entries, const uint64_t* __restrict__ groups,
             const uint4* __restrict__ extra, const uint32_t* __restrict__ counts, const uint32_t* __restrict__ lists,
-            ListOut o) {
+            int most, ListOut o) {
   const uint32_t count = counts[kExtra];
   const bool first = (int)blockIdx.x >= kRankCols;
   const int at = ((int)blockIdx.x % kRankCols) * kRankThreads + (int)threadIdx.x;
   for (uint32_t x = blockIdx.y; x < count; x += kRankRows) {
     const uint4 it = extra[x];
-    if (first && it.y != 1u) continue;
-    merge_chunk(entries + it.z, groups + it.z, (int)it.w, sort_chunks(it.w), first ? 0 : (int)it.y, at, kSortMost,
+    const int nch = sort_chunks(it.w);
+    if (nch > most || (first && it.y != 1u)) continue;
+    merge_chunk(entries + it.z, groups + it.z, (int)it.w, nch, first ? 0 : (int)it.y, at, kSortMost,
                 ((const uint4*)lists)[it.x], o);
   }
 }
 
-// The same for larger maps, whose cells may have any number of chunks: the blocks take the parts
-// of every chunk after a cell's first in turn, and those of the first where theirs is the
+// The same for the cells of more than `ranked` chunks, any number of them: the blocks take the
+// parts of every chunk after a cell's first in turn, and those of the first where theirs is the
 // second. Cells of up to kRankChunks chunks are ranked, the others merged in segments: 34 us for
 // one cell of 270k (17 chunks), 88 of 1M (62) and 139 of 2M (123), where ranking took 506 for
 // 1M and four times that for 2M. What bounds it is the first round's loads, 64 cold lines per
-// wave and step. Its large blocks spread a few chunks worse over the chip: 20 us for the six
-// cells of 40000, 33 for six of 80000 where ranking takes 24. The line between the two lies
-// where the worst map, all in one cell, costs about the same; each launches alone, as an idle
-// launch takes 4 us.
+// wave and step. Its large blocks spread a few chunks worse over the chip than k_cell_rank's: 20
+// us for the six cells of 40000, 33 for the six of 80000.
 constexpr int kMergeBlocks = 512, kMergeParts = kSortMost / kMergeThreads;
+template <int PER>
 __global__ void __launch_bounds__(kMergeThreads)
 k_cell_merge(const uint64_t* __restrict__ entries, const uint64_t* __restrict__ groups,
              const uint4* __restrict__ extra, const uint32_t* __restrict__ counts, const uint32_t* __restrict__ lists,
-             ListOut o) {
-  __shared__ MergeLds L;
+             int ranked, ListOut o) {
+  __shared__ MergeLds<PER> L;
   __shared__ uint32_t s_cnt[kMergeThreads / 64][4], s_warp[kMergeThreads / 64], s_to[4];
   const uint32_t count = counts[kExtra];
   for (uint32_t u = blockIdx.x; u < 2u * kMergeParts * count; u += kMergeBlocks) {
@@ -1263,6 +1295,7 @@ k_cell_merge(const uint64_t* __restrict__ entries, const uint64_t* __restrict__ 
     const uint4 it = extra[u % count];
     if (first && it.y != 1u) continue;
     const int c = first ? 0 : (int)it.y, n = (int)it.w, nch = sort_chunks(it.w);
+    if (nch <= ranked) continue;
     const uint4 to = ((const uint4*)lists)[it.x];
     if (nch <= kRankChunks)
       merge_chunk(entries + it.z, groups + it.z, n, nch, c, part * kMergeThreads + (int)threadIdx.x, kSortMost, to, o);
@@ -1334,12 +1367,16 @@ hipError_t tile_lists_build(const float4* rec, const uint4* pairs, const uint32_
     hipLaunchKernelGGL(k_cell_sort_large, dim3((unsigned)(items + more)), dim3(SortShape<true>::threads), 0, s, entries,
                        groups, ws.items, (const uint4*)extra, ws.count, ws.lists, (int)items, o);
   }
-  if (N > kRankGaussians)
-    hipLaunchKernelGGL(k_cell_merge, dim3(kMergeBlocks), dim3(kMergeThreads), 0, s, entries, groups,
-                       (const uint4*)extra, ws.count, ws.lists, o);
-  else if (N > kSortMost)
+  const bool crowded = (int64_t)va.n * N > kRankPerCell * nc;
+  const int ranked = N <= kRankGaussians ? kMostChunks : crowded ? kRankCrowded : 0;
+  if (N > kSortMost && ranked)
     hipLaunchKernelGGL(k_cell_rank, dim3(2 * kRankCols, kRankRows), dim3(kRankThreads), 0, s, entries, groups,
-                       (const uint4*)extra, ws.count, ws.lists, o);
+                       (const uint4*)extra, ws.count, ws.lists, ranked, o);
+  if (N > kRankGaussians) {
+    auto merge = N <= (int64_t)kMergeThreads * kSortMost ? k_cell_merge<1> : k_cell_merge<4>;
+    hipLaunchKernelGGL(merge, dim3(kMergeBlocks), dim3(kMergeThreads), 0, s, entries, groups, (const uint4*)extra,
+                       ws.count, ws.lists, ranked, o);
+  }
   return hipGetLastError();
 }
 
